@@ -12,6 +12,7 @@ of the cache, compact K/V to them, attend from the chunk over retained + chunk. 
   attention - the attention call alone: over a compacted cache, or through an index list ("gather").
   sse       - pafu_sse_score, the teacher-side score the salience head is trained on.
   quantise  - the two directions of the 8-bit cache format over a whole cache.
+`exact` is what a call returns in 64 bits, in plain torch.
 
 Values follow workloads.py: N(0,1) features, Q, K, V; a per-channel key scale from U[0.5, 2]; N(0, 0.02^2) head weights;
 a tenth of the cached tokens salient (+2 on every feature, or a higher stored score).
@@ -180,7 +181,7 @@ def _prepare_layers(c, seed):
         # (every layer's score list starts at a 16-byte boundary)
         out["scores"] = torch.empty(heads, (n + Lc + 3) // 4 * 4, device=DEV)[:, :n + Lc]
     index_layer = layers - 1 if c["shared"] else None
-    args = []
+    args, given = [], []
     for l in range(layers):
         s = 0 if c["shared"] else l
         scale = mk.uniform(H) * 1.5 + 0.5
@@ -190,6 +191,7 @@ def _prepare_layers(c, seed):
         Q = mk.tokens(Lc, H).view(Lc, N, D)
         Kn, Vn = mk.tokens(Lc, H, scale).view(Lc, N, D), mk.tokens(Lc, H).view(Lc, N, D)
         scores = SL_in = x_cache = b1 = b2 = None
+        layer = {"K": Kc, "V": Vc, "Q": Q, "Kn": Kn, "Vn": Vn}
         if index_layer is None or l == index_layer:
             hot = mk.salient(n)
             W1 = (mk.normal(c["hidden"], c["segments"] * H) * 0.02).to(xdt)
@@ -206,6 +208,7 @@ def _prepare_layers(c, seed):
                 x_chunk = tuple(mk.tokens(Lc, H, dtype=xdt) for _ in range(c["segments"]))
                 SL_in = mk.normal(n) * 0.15
                 SL_in[hot] += 0.5
+            layer.update(x_cache=x_cache, x_chunk=x_chunk, W1=W1, b1=b1, W2=W2, b2=b2, SL=SL_in)
         # (with shared indices the other layers' feature, weight and score fields are ignored; they name the last
         # layer's here only because the struct is filled from tensors)
         if c["shared"] and l != index_layer:
@@ -216,10 +219,11 @@ def _prepare_layers(c, seed):
                              kv_dtype=B.PAFU_FP8_E4M3 if e4m3 else B.PAFU_BF16,
                              k_scale_log2=K_SCALE_LOG2 if e4m3 else 0, v_scale_log2=V_SCALE_LOG2 if e4m3 else 0)
         args.append(a)
+        given.append(layer)
     ws = _bytes(max(B.pafu_step_workspace_bytes(a) for a in args))
     for a in args:
         a.workspace, a.workspace_bytes = ws.data_ptr(), ws.numel()
-    return {"case": c, "args": args, "out": out, "ws": ws, "index_layer": index_layer}
+    return {"case": c, "args": args, "out": out, "ws": ws, "index_layer": index_layer, "given": given}
 
 
 def prepare(case, seed):
@@ -337,3 +341,121 @@ def tolerance(c):
     if c["kind"] == "sse":
         return {"rel": 1e-5, "max": 1e-4}
     return {"rel": 1e-2, "max": 5e-2}
+
+
+# ------------------------------------------------------------------------------------------------ in 64 bits
+def _decoded(codes, scale_log2, shape):
+    return (codes.view(torch.float8_e4m3fn).double() * 2.0 ** scale_log2).view(shape)
+
+
+def _encoded(x, scale_log2):
+    """(bf16 values are well inside fp32, where the scaling is exact; saturation comes before the cast)"""
+    y = (x.float() * 2.0 ** -scale_log2).clamp(-448.0, 448.0)
+    return y.to(torch.float8_e4m3fn).view(torch.uint8).view(x.shape[0], -1)
+
+
+def _attend(Q, K, V, kept, block):
+    """softmax(Q K^T / sqrt(D)) V per head; the keys are `kept` retained ones, then the chunk's."""
+    Lc, N, D = Q.shape
+    out = torch.empty(Lc, N, D, device=DEV, dtype=torch.float64)
+    for h in range(N):
+        q, k, v = Q[:, h].double(), K[:, h].double().contiguous(), V[:, h].double().contiguous()
+        i = 0
+        while i < Lc:  # a block of queries sees one prefix of the keys; large ones go in pieces
+            seen = kept + min((i // block + 1) * block, Lc)
+            m = min(2048, (i // block + 1) * block - i, Lc - i)
+            s = (q[i:i + m] @ k[:seen].t()) / math.sqrt(D)
+            out[i:i + m, h] = torch.softmax(s, dim=1) @ v[:seen]
+            i += m
+    return out
+
+
+def _scored(xs, w):
+    parts = []
+    for r in range(0, xs[0].shape[0], 8192):
+        h = torch.cat([x[r:r + 8192].double() for x in xs], dim=1) @ w["W1"].double().t()
+        h = h if w["b1"] is None else h + w["b1"].double()
+        o = (h * torch.sigmoid(h)) @ w["W2"].double().t()
+        parts.append((o if w["b2"] is None else o + w["b2"].double()).mean(dim=1))
+    return torch.cat(parts)
+
+
+def _exact_layers(c, st):
+    """Where the kept tokens follow from scores computed in the call ("single"), two close scores may change places:
+    the outputs that such a change moves by a row (indices, cache rows, their scores) are left out there."""
+    n, Lc, N, D = c["cached"], c["chunk"], c["heads"], c["head_dim"]
+    kept, single, e4m3 = min(c["keep"], n), c["mode"] == "single", c["kv"] == "e4m3"
+    out, ids_of, row = {"O": [], "K": [], "V": [], "ids": [], "SL": [], "scores": []}, {}, ("ids", "SL", "scores")
+    scoring = [l for l in range(c["layers"]) if st["index_layer"] in (None, l)]
+    for l in scoring:
+        w = st["given"][l]
+        new = _scored(w["x_chunk"], w)
+        stored = _scored(w["x_cache"], w) if single else w["SL"].double()
+        rank = stored.clone()
+        rank[:c["pinned"]] = math.inf
+        best = torch.sort(rank, descending=True, stable=True).indices[:kept]
+        ids_of[l] = torch.sort(best).values
+        out["ids"].append(ids_of[l].to(torch.int32))
+        out["SL"].append(stored[ids_of[l]] if single else torch.cat([stored[ids_of[l]], new]))
+        out["scores"].append(torch.cat([stored, new]))
+    for l, w in enumerate(st["given"]):
+        ids = ids_of[scoring[0] if c["shared"] else l]
+        K, V, Kn, Vn = w["K"][ids], w["V"][ids], w["Kn"], w["Vn"]
+        if e4m3:
+            Kn, Vn = _encoded(Kn, K_SCALE_LOG2), _encoded(Vn, V_SCALE_LOG2)
+        K, V = torch.cat([K, Kn]), torch.cat([V, Vn])
+        rows = kept + (Lc if e4m3 or not single else 0)
+        out["K"].append(K[:rows])
+        out["V"].append(V[:rows])
+        if e4m3:
+            K, V = _decoded(K, K_SCALE_LOG2, (-1, N, D)), _decoded(V, V_SCALE_LOG2, (-1, N, D))
+        out["O"].append(_attend(w["Q"], K, V, kept, c["block"]))
+    out = {k: torch.stack(v) for k, v in out.items()}
+    if single:
+        return {"O": out["O"], "K": None, "V": None, "ids": None, "SL": None, "scores": out["scores"]}
+    del out["scores"]
+    return out
+
+
+def _exact_sse(c, st):
+    """Per key the largest weight over the queries of later, the same and earlier blocks, averaged over the heads; the
+    score is the mean of the parts that exist (Eq. 4-5)."""
+    L, N, D = st["Q"].shape
+    block = c["block"]
+    starts = list(range(0, L, block))
+    total = torch.zeros(L, device=DEV, dtype=torch.float64)
+    own = torch.arange(L, device=DEV) // block
+    parts = (1 + (own > 0).int() + (own < len(starts) - 1).int()).double()
+    for h in range(N):
+        k = st["K"][:, h].double().contiguous()
+        best = torch.zeros(3, L, device=DEV, dtype=torch.float64)
+        for b, lo in enumerate(starts):
+            hi = min(lo + block, L)
+            for i in range(lo, hi, 2048):  # (a part with no queries stays 0)
+                q = st["Q"][i:min(i + 2048, hi), h].double()
+                top = torch.softmax((q @ k.t()) / math.sqrt(D), dim=1).amax(dim=0)
+                for part, of in enumerate((own < b, own == b, own > b)):
+                    best[part] = torch.where(of, torch.maximum(best[part], top), best[part])
+        total += best.sum(dim=0)
+    return total / N / parts
+
+
+def exact(case, seed):
+    c = dict(case)
+    st = prepare(c, seed)
+    if c["kind"] in ("step", "layers"):
+        return _exact_layers(c, st)
+    if c["kind"] == "sse":
+        return _exact_sse(c, st)
+    if c["kind"] == "quantise":
+        Kq, Vq = _encoded(st["K"], K_SCALE_LOG2), _encoded(st["V"], V_SCALE_LOG2)
+        shape = st["K"].shape
+        return [Kq, Vq, _decoded(Kq, K_SCALE_LOG2, shape), _decoded(Vq, V_SCALE_LOG2, shape)]
+    K, V, Kn, Vn = st["K"], st["V"], st["Kn"], st["Vn"]
+    if c["gather"]:
+        K, V = K[st["ids"].long()], V[st["ids"].long()]
+    K, V = torch.cat([K, Kn.view(Kn.shape[0], *K.shape[1:])]), torch.cat([V, Vn.view(Vn.shape[0], *V.shape[1:])])
+    if c["kv"] == "e4m3":
+        shape = (-1, c["heads"], c["head_dim"])
+        K, V = _decoded(K, K_SCALE_LOG2, shape), _decoded(V, V_SCALE_LOG2, shape)
+    return _attend(st["Q"], K, V, c["keep"], c["block"])
