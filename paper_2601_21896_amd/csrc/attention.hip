@@ -19,9 +19,10 @@
 // SAME wave (a wave with a matrix instruction waiting at issue blocks the vector instructions of its
 // SIMD neighbour), so each wave is software-pipelined by hand: step t issues the 16 MFMAs of S^T(t+1)
 // and the 16 MFMAs that add tile t-1 to O^T, and after each of them a slice of the online softmax of
-// tile t (vector ALU).  Two such waves share a SIMD and fill each other's stalls.  The running maximum is only raised when it
-// grows by more than 2^8 (the result is mathematically unchanged), which makes the O^T rescale a rare,
-// out-of-line event.
+// tile t (vector ALU).  Two such waves share a SIMD and fill each other's stalls.  No step looks for the
+// maximum of its tile: the weights are taken relative to the maximum of the first tile and their sum, which
+// is needed anyway, shows when a tile has outgrown it (the result is mathematically unchanged).  Raising the
+// maximum, with the rescale of O^T, is a rare out-of-line event.
 //
 // K/V tiles (64 keys) stream from global memory straight into a 4-deep LDS ring (global_load_lds, no
 // staging registers) three tiles ahead of their use; rows are stored with an XOR swizzle of their
@@ -74,7 +75,10 @@ constexpr int kAtIdStages = 8;        // ids ring depth (gather variant): a tile
                                       // K load to its V load two steps after that
 constexpr int kAtIdLead = 3;
 constexpr int kAtXcds = 8;            // accelerator dies, each with its own L2
-constexpr float kAtLazyLog2 = 8.0f;   // raise the running maximum only when it grows by more than 2^8
+// A tile's weights are taken relative to the maximum of the tiles before it; a lane's 32 of them may sum up to this much
+// before the maximum is raised.  (Above 32, so that a raised maximum always settles it; bf16 weights and fp32 sums have
+// the same relative precision at any scale.)
+constexpr float kAtMaxTileSum = 256.0f;
 // Study builds only (never the shipped library, which is built without the macro): PAFU_ATTN_ABLATE is a bit mask that
 // takes ingredients out of the inner loop so that what they cost can be measured on the same shapes and data; the
 // results of such a build are meaningless.  pafu_study_build() returns the mask.
@@ -146,6 +150,11 @@ __device__ __forceinline__ bf16x8 lds_read_vt(const lds_byte* p, int row_bytes8)
 // (masked elements of s_cur set to -inf beforehand, p_prev = 0 before the first tile, a clamped K tile when
 // there is no next tile), so this is the only implementation of the step.
 // s_*[kb] = key block kb (32 keys) of the tile; p_*[ks] = 16-key slice ks of the tile.
+// What bounds it: the issue slots that 32 matrix instructions share with the vector work of 2048 scores, at a clock that
+// the power limit sets.  A search for the tile's maximum (16 three-way maxima, a swap across the lane halves and the wait
+// for both) before the first exponential cost about an eighth of the vector instructions and left the first slots without
+// exponentials; without it a whole step takes 634 us instead of 667 (12 heads of 128, 4680 queries, 21060 keys), and 6762
+// instead of 7295 (40 heads, 10800 queries, 33480 keys).
 // issue_k / issue_v start this step's global -> LDS tile copies.  They are called a few slots into the step, not at
 // its start: right after the barrier all eight waves would queue their copies at once and sit behind the memory pipe
 // (a wave issues nothing while its copy waits), whereas an eighth and a half of the way in they find it free.
@@ -160,11 +169,10 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   constexpr int NS = 2 * KD;       // MFMAs of S^T(t+1): 2 key blocks x KD contraction steps
   constexpr int NP = 4 * DB;       // MFMAs of the O^T update: 4 key slices x DB row blocks
   constexpr int NSLOT = NS + NP;   // MFMAs per step (NS == NP for D = 64 and 128)
-  constexpr int A_SLOTS = 5;       // slots that carry the max / threshold work
+  constexpr int EPS = 32 / NSLOT;  // scores turned into weights behind each MFMA (1 for D = 128, 2 for D = 64)
   constexpr int K_ISSUE = NSLOT / 8, V_ISSUE = NSLOT / 2;  // slots behind which the tile copies are started
   static_assert(NS == NP, "the slot pattern alternates one MFMA of each product");
-  float alpha, mx, msc_new, psum = 0.f, q0 = 0.f, q1 = 0.f;
-  bool grow;
+  float psum = 0.f, q_prev = 0.f, q_even = 0.f;
 
   // slot i = 2 m + w: w = 0 -> S^T MFMA number m, w = 1 -> O^T MFMA number m.
   //   S^T MFMA m: key block m & 1, contraction step m >> 1 (the two accumulators alternate).
@@ -212,47 +220,30 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
               __float_as_uint(s_cur[kb][r + 1]), __float_as_uint(s_cur[kb][r]), 0x07060302u);
         }
       }
-      alpha = 1.f;
-      grow = false;
       psum = 1.f;
-    } else if (i < 4) {  // row maximum over a quarter of the tile's keys
-      const int kb = i >> 1, r0 = 8 * (i & 1);
-      float t = i ? mx : s_cur[0][0];
-      asm volatile("" : "+v"(t));
+    } else {  // weights of this slot's keys, relative to the running maximum of the tiles before this one
 #pragma unroll
-      for (int r = 0; r < 8; r += 2) t = fmaxf(fmaxf(t, s_cur[kb][r0 + r]), s_cur[kb][r0 + r + 1]);
-      mx = (i == 3) ? half_swap_max(t) : t;
-      asm volatile("" : "+v"(mx));
-    } else if (i == 4) {  // lazy running maximum (log2 domain), rescale factor
-      const float mxs = mx * sc;
-      grow = mxs > msc + kAtLazyLog2;
-      msc_new = grow ? mxs : msc;
-      alpha = __builtin_amdgcn_exp2f(msc - msc_new);
-      msc = msc_new;
-      asm volatile("" : "+v"(alpha), "+v"(msc_new));
-    } else {  // exponentials of the elements assigned to this slot
-#pragma unroll
-      for (int u = 0; u < 16; ++u) {  // unit = two neighbouring keys of the query
-        if (A_SLOTS + (u * (NSLOT - A_SLOTS)) / 16 == i) {
-          const int kb = u >> 3, r = 2 * (u & 7);
-          float a0 = s_cur[kb][r], a1 = s_cur[kb][r + 1];
-          asm volatile("" : "+v"(a0), "+v"(a1));  // the slice may not rise above the previous MFMA ...
-          const float pe0 = __builtin_amdgcn_exp2f(fmaf(a0, sc, -msc_new));
-          const float pe1 = __builtin_amdgcn_exp2f(fmaf(a1, sc, -msc_new));
-          // the sums and the pack of the PREVIOUS unit go here, behind this unit's exponentials: a transcendental
-          // result takes several issue slots to arrive, and adding it right away stalls the wave
-          if (u > 0) {
-            const int kbp = (u - 1) >> 3, rp = 2 * ((u - 1) & 7);
-            psum += q0;
-            psum += q1;
-            unsigned pk = pack_bf16(q0, q1);
-            asm volatile("" : "+v"(pk), "+v"(psum));
-            p_cur[2 * kbp + (rp >> 3)][(rp & 7) >> 1] = pk;
+      for (int x = 0; x < EPS; ++x) {
+        const int e = EPS * i + x, kb = e >> 4, r = e & 15;
+        // the slice may not rise above the previous MFMA ... (tied through msc: tying the score would copy it)
+        asm volatile("" : "+v"(msc));
+        float pe = __builtin_amdgcn_exp2f(fmaf(s_cur[kb][r], sc, -msc));
+        // the sum and the pack of the PREVIOUS key go here, behind this key's exponential: a transcendental result
+        // takes several issue slots to arrive, and adding it right away stalls the wave
+        if (e > 0) {
+          psum += q_prev;
+          asm volatile("" : "+v"(psum));
+          if ((e & 1) == 0) {
+            const int ep = e - 2;
+            unsigned pk = pack_bf16(q_even, q_prev);
+            asm volatile("" : "+v"(pk));
+            p_cur[ep >> 3][(ep & 7) >> 1] = pk;
+          } else {
+            q_even = q_prev;
           }
-          q0 = pe0;
-          q1 = pe1;
-          asm volatile("" : "+v"(q0), "+v"(q1));  // ... nor sink below the next one
         }
+        q_prev = pe;
+        asm volatile("" : "+v"(q_prev));  // ... nor sink below the next one
       }
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -265,19 +256,43 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
       __builtin_amdgcn_sched_barrier(0);
     }
   }
-  if (!kAblateSoftmax) {  // the last unit
-    psum += q0;
-    psum += q1;
-    p_cur[3][3] = pack_bf16(q0, q1);
+  if (kAblateSoftmax) {
+    l_run += psum;
+    return;
   }
-  l_run = fmaf(l_run, alpha, psum);
-  // O^T now holds tiles < t scaled by the old maximum; bring it to the new one before tile t is added
-  if (__builtin_amdgcn_ballot_w64(grow) != 0) {
+  psum += q_prev;  // the last key
+  p_cur[3][3] = pack_bf16(q_even, q_prev);
+  // O^T now holds the tiles < t scaled by the running maximum, and so are P^T(t) and its sums: nothing to rescale, unless
+  // the tile outgrew that maximum (or met a NaN).  Then the queries concerned take the tile's own maximum, their weights
+  // are computed once more from the scores, which are still in their registers, and what was summed before is rescaled.
+  const bool over = !(psum <= kAtMaxTileSum);
+  if (__builtin_amdgcn_ballot_w64(over) != 0) {
+    float mx = s_cur[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[kb][r]);
+    mx = half_swap_max(mx);
+    const bool grow = half_swap_max(over ? 1.f : 0.f) != 0.f;  // both halves of a query together
+    const float msc_new = grow ? fmaxf(msc, mx * sc) : msc;
+    const float alpha = __builtin_amdgcn_exp2f(msc - msc_new);
+    msc = msc_new;
+    psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 32; e += 2) {
+      const float pe0 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][e & 15], sc, -msc_new));
+      const float pe1 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][(e & 15) + 1], sc, -msc_new));
+      psum += pe0;
+      psum += pe1;
+      p_cur[e >> 3][(e & 7) >> 1] = pack_bf16(pe0, pe1);
+    }
+    l_run *= alpha;
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
       for (int r = 0; r < 16; ++r) o[b][r] *= alpha;
   }
+  l_run += psum;
 }
 
 // Block mask / ragged tail for the tile starting at key0: register r of s[kb] holds key
@@ -672,6 +687,17 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
 
+      // the running maximum starts with that of the first tile (every later tile is only checked against it)
+      if ((tb + 1) * kAtTileKeys > lim_min) attn_mask(s_a, tb * kAtTileKeys, lim, g);
+      {
+        float mx = s_a[0][0];
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_a[kb][r]);
+        msc = fmaxf(msc, half_swap_max(mx) * sc);
+      }
+
       // Step t: S^T(t+1) into the "next" registers, softmax of S^T(t), O^T += tile t-1.  Iteration T runs step 2T
       // (s_a -> p_a, next into s_b, adds p_b) and step 2T+1 (s_b -> p_b, next into s_a, adds p_a).  A segment always
       // holds an even number of tiles: a tile past the end is fully masked and contributes nothing.  Before the first
@@ -684,7 +710,7 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
           const int t = 2 * T;
           if (GATHER) issue_ids(tb + t + kAtStages + kAtIdLead);
           if (KV8) cook_step(t, 2 * n_iter);
-          if ((tb + t + 1) * kAtTileKeys > lim_min) attn_mask(s_a, (tb + t) * kAtTileKeys, lim, g);
+          if (T > 0 && (tb + t + 1) * kAtTileKeys > lim_min) attn_mask(s_a, (tb + t) * kAtTileKeys, lim, g);
           attn_step<D>(
               s_a, s_b, p_b, p_a, o, qf, msc, l_run, k_addr(t + 1), v_addr(t > 0 ? t - 1 : 0), kx2, vx2, sc,
               [&] { if (!kAblateLoads) issue_k_tile(t + LEAD); }, [&] { if (!kAblateLoads) issue_v_tile(t + LEAD); });

@@ -117,6 +117,32 @@ def test_attention_large_key_offset_and_fewer_queries():
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("case", ["every tile", "one query", "masked start", "nan query"])
+def test_attention_running_maximum_outgrown(D, case):
+    # the running maximum is the first tile's until a later tile outgrows it: for all queries of every tile, for single
+    # queries of one tile, from a first tile in which a query sees nothing; and a NaN in one query stays in that query
+    n, Lc, N = (0, 300, 2) if case == "masked start" else (700, 96, 2)
+    Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=7 + D)
+    bad = []
+    if case == "every tile":
+        Kc = wl.round_to_bf16(Kc * (0.1 * 2.0 ** (np.arange(n) // 64))[:, None, None].astype(np.float32))
+    elif case == "one query":  # keys 70, 400, 690 look at queries 3, 40, 41 with growing weight
+        for key, q, gain in ((70, 3, 2.0), (400, 40, 6.0), (690, 41, 20.0)):
+            Kc[key] = wl.round_to_bf16(Q[q] * np.float32(gain))
+    elif case == "nan query":
+        bad = [5, 77]
+        Q[bad] = np.nan
+    L_B = 1 if case == "masked start" else Lc
+    ok = np.setdiff1d(np.arange(Lc), bad)
+    want = orc.chunk_attention(np.nan_to_num(Q), Kc, Vc, Kn, Vn, block_len=L_B)
+    for ws in (None, attention_workspace(D)):
+        got = _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.float32, ws=ws)
+        max_abs, rel = attn_errors(got[ok], want[ok])
+        assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
+        assert np.isnan(got[bad]).all()
+
+
 def test_attention_strided_slabs():
     # cache rows live in a slab with spare capacity and a wider token stride
     n, Lc, N, D = 150, 70, 2, 64
