@@ -92,7 +92,9 @@ constexpr bool kAblateLoads = (PAFU_ATTN_ABLATE & 1) != 0;
 constexpr bool kAblateSoftmax = (PAFU_ATTN_ABLATE & 2) != 0;
 constexpr bool kStudySplitAlways = (PAFU_ATTN_ABLATE & 4) != 0;
 constexpr float kAtNoMax = -1.0e30f;  // running maximum before the first visible key (finite on purpose)
-constexpr int kAtMaxRuns = 256;       // most workgroups the unit list is ever cut into (one per CU)
+constexpr int kAtMaxRuns = 256;       // most runs a unit list is ever cut into (one per CU)
+constexpr int kAtMinRunUnits = 2;     // fewest units of a run
+constexpr int kAtMinCutGain = 4;      // a cut has to shorten the last round by this many units to pay for its merge pass
 
 constexpr int attn_lds_bytes(int D, bool gather = false) {
   return 2 * kAtStages * kAtTileKeys * 2 * D + (gather ? kAtIdStages * kAtTileKeys * 4 : 0);
@@ -310,21 +312,24 @@ __device__ __forceinline__ void attn_mask(f32x16 (&s)[2], int key0, int lim, int
 // ---- work decomposition -----------------------------------------------------------------------------------------
 // A work item is one (head, query tile of kAtBQ queries); its cost is counted in UNITS of two key tiles (one loop
 // iteration): units(qt) = ceil(ceil(visible keys of the tile's last query / 64) / 2).  Items are ordered head-major.
-// Whole items on a grid of one workgroup per item leave CUs idle when there are fewer items than CUs (a one-frame
-// chunk of 1560 queries is 84 items on 256 CUs), so with a workspace, and when the items fill at most four fifths of
-// the chip, the flattened unit list is instead cut into `n_wg` equal contiguous runs, one per workgroup: a run covers
-// the tail of one item, possibly some whole items, and the head of another.  A workgroup that does not see all units of an item writes its unnormalised O^T together with
-// the running maximum and the row sums into the workspace (slot 2 g for the first segment of workgroup g, 2 g + 1 for
-// its last), and attn_combine_kernel merges the partial results of such items afterwards, always in run order, so
-// the result does not depend on timing.
+// One workgroup per item leaves CUs idle in the last round of items over the CUs (a one-frame chunk of 1560 queries is 84
+// items on 256 CUs; 272 items are a full round and one of 16), so with a workspace the items of an ill-filled last round
+// are cut instead: their flattened unit list goes in `n_runs` equal contiguous runs to one workgroup each, behind the
+// `n_whole` workgroups that take an item each.  A run covers the tail of one item, possibly some whole items, and the
+// head of another.  A workgroup that does not see all units of an item writes its unnormalised O^T together with the
+// running maximum and the row sums into the workspace (slot 2 g for the first segment of run g, 2 g + 1 for its last),
+// and attn_combine_kernel merges the partial results of such items afterwards, always in run order, so the result does
+// not depend on timing.
 struct AttnWork {
-  int n_qt;        // query tiles per head
-  int units_head;  // units of one head (sum over its query tiles)
-  int uniform;     // units of every query tile when they are all equal (no block mask), else 0
-  int split;       // 1: equal runs over the unit list; 0: workgroup g takes work item g
-  int n_wg;        // logical workgroups
-  float* part_o;   // [2 n_wg][kAtBQ][D] fp32
-  float* part_ml;  // [2 n_wg][2][kAtBQ] fp32: running maximum (log2 domain), row sum
+  int n_qt;           // query tiles per head
+  int units_head;     // units of one head (sum over its query tiles)
+  int uniform;        // units of every query tile when they are all equal (no block mask), else 0
+  int n_items;        // heads * n_qt
+  int n_whole;        // workgroup g < n_whole takes item g
+  int n_runs;         // equal runs over the units of the items from n_whole on
+  long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list
+  float* part_o;      // [2 n_runs][kAtBQ][D] fp32
+  float* part_ml;     // [2 n_runs][2][kAtBQ] fp32: running maximum (log2 domain), row sum
 };
 
 __host__ __device__ inline int attn_units(int qt, int Lq, int n_kept, int Lc, int L_B) {
@@ -333,7 +338,7 @@ __host__ __device__ inline int attn_units(int qt, int Lq, int n_kept, int Lc, in
   const int vis = n_kept + (int)(e < Lc ? e : Lc);
   return ((vis + kAtTileKeys - 1) / kAtTileKeys + 1) / 2;
 }
-// first unit of logical workgroup g when U units are cut into G runs
+// first unit of run g when U units are cut into G runs
 __host__ __device__ inline long long attn_run_begin(long long g, long long U, long long G) { return g * U / G; }
 
 struct AttnArgs {
@@ -399,10 +404,12 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   const int qblk = 2 * (wave & 3) + (wave >> 2);
   const int g = lane >> 5, c = lane & 31;
   // Logical workgroup.  Workgroups are handed to the 8 XCDs round-robin in launch order and every XCD has its own
-  // L2, so XCD x (workgroups x, x + 8, ...) takes one contiguous range of the head-major work list: at any time an
-  // XCD then streams the K/V of one or two heads instead of all of them.
-  const int total = gridDim.x;
-  const int xcd = blockIdx.x % kAtXcds, xslot = blockIdx.x / kAtXcds;
+  // L2, so XCD x (workgroups x, x + 8, ...) takes one contiguous range of the head-major item list, and one of the runs
+  // behind it: at any time an XCD then streams the K/V of one or two heads instead of all of them.
+  const bool is_run = (int)blockIdx.x >= wk.n_whole;
+  const int total = is_run ? wk.n_runs : wk.n_whole;
+  const int xcd = blockIdx.x % kAtXcds;  // (whole items and runs are only mixed when n_whole is a multiple of kAtXcds)
+  const int xslot = (blockIdx.x - (is_run ? wk.n_whole : 0)) / kAtXcds;
   const int wg = xcd * (total / kAtXcds) + (xcd < total % kAtXcds ? xcd : total % kAtXcds) + xslot;
   const int L_B = p.block_len;
   const int n_total = p.n_kept + p.Lc;
@@ -444,10 +451,9 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   // ---- this workgroup's run of units [u, u_end) in the flattened (head, query tile, unit) list
   long long u, u_end;
   int qt, h, pre;  // current item and the units of its head that precede it
-  if (wk.split) {
-    const long long U = (long long)wk.units_head * (p.N_heads);
-    u = uniform_i64(attn_run_begin(wg, U, wk.n_wg));
-    u_end = uniform_i64(attn_run_begin(wg + 1, U, wk.n_wg));
+  if (is_run) {
+    u = uniform_i64(wk.u0 + attn_run_begin(wg, wk.U, wk.n_runs));
+    u_end = uniform_i64(wk.u0 + attn_run_begin(wg + 1, wk.U, wk.n_runs));
     h = uniform_i32((int)(u / wk.units_head));
     const int r = (int)(u - (long long)h * wk.units_head);
     if (wk.uniform) {
@@ -792,69 +798,59 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   }
 }
 
-// Merges the partial results of the items that more than one workgroup worked on.  kAtCombineSplit workgroups per
-// item, each taking a band of its query rows; the partials are taken in run order, whoever wrote them first.
+// Merges the partial results of the items that more than one workgroup worked on, in run order, whoever wrote them first:
 //   O = sum_p 2^(m_p - m) O_p / sum_p 2^(m_p - m) l_p   with m = max_p m_p.
-constexpr int kAtCombineSplit = 8;
-constexpr int kAtCombineRows = kAtBQ / kAtCombineSplit;
+// D / 4 lanes take one query row (16 bytes of every partial result each), a wave 256 / D rows, a workgroup four waves:
+// the launch is bound by the latency of its chain (maxima, then weights and rows), so rows are spread as wide as they
+// go instead of being walked by a few workgroups per item.
+template <int D>
+constexpr int kAtCombineRows = 4 * 256 / D;  // rows per workgroup
 template <int D, bool OUT_F32>
 __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
   const AttnParams& p = args.p;
   const AttnWork& wk = args.w;
-  __shared__ float s_m[kAtCombineRows], s_inv[kAtCombineRows];
-  const int item = blockIdx.x / kAtCombineSplit, band = blockIdx.x % kAtCombineSplit;
+  constexpr int kBands = kAtBQ / kAtCombineRows<D>;
+  const int item = wk.n_whole + blockIdx.x / kBands, band = blockIdx.x % kBands;
   const int h = item / wk.n_qt, qt = item - h * wk.n_qt;
+  const int row = band * kAtCombineRows<D> + threadIdx.x / (D / 4);  // query row inside the item
+  const int q_row = qt * kAtBQ + row;
+  if (qt * kAtBQ + band * kAtCombineRows<D> >= p.Lq) return;
   int pre = 0;
   if (wk.uniform) pre = qt * wk.uniform;
   else
     for (int q2 = 0; q2 < qt; ++q2) pre += attn_units(q2, p.Lq, p.n_kept, p.Lc, p.block_len);
   const int units = attn_units(qt, p.Lq, p.n_kept, p.Lc, p.block_len);
-  const long long U = (long long)wk.units_head * p.N_heads, G = wk.n_wg;
-  const long long s = (long long)h * wk.units_head + pre, e = s + units;
+  const long long U = wk.U, G = wk.n_runs;
+  const long long s = (long long)h * wk.units_head + pre - wk.u0, e = s + units;
   // the run that holds unit x: the largest g with floor(g U / G) <= x
   const int g_first = (int)(((s + 1) * G - 1) / U), g_last = (int)((e * G - 1) / U);
-  if (g_first == g_last) return;  // one workgroup saw the whole item and wrote O itself
+  if (g_first == g_last || q_row >= p.Lq) return;  // one workgroup saw the whole item and wrote O itself
   // slot of run gg's partial result for this item: 2 gg if the run starts inside the item, else 2 gg + 1
   const int slot_first = 2 * g_first + (attn_run_begin(g_first, U, G) >= s ? 0 : 1);
   auto slot_of = [&](int gg) { return gg == g_first ? slot_first : 2 * gg; };
-  const int rows_item = p.Lq - qt * kAtBQ < kAtBQ ? p.Lq - qt * kAtBQ : kAtBQ;
-  const int row0 = band * kAtCombineRows;
-  const int rows = rows_item - row0 < kAtCombineRows ? rows_item - row0 : kAtCombineRows;
-  if (rows <= 0) return;
-  const int tid = threadIdx.x;
-  if (tid < rows) {
-    float m = kAtNoMax;
-    for (int gg = g_first; gg <= g_last; ++gg) m = fmaxf(m, wk.part_ml[(long long)slot_of(gg) * 2 * kAtBQ + row0 + tid]);
-    float l = 0.f;
-    for (int gg = g_first; gg <= g_last; ++gg) {
-      const float* ml = wk.part_ml + (long long)slot_of(gg) * 2 * kAtBQ + row0;
-      l += ml[kAtBQ + tid] * __builtin_amdgcn_exp2f(ml[tid] - m);
-    }
-    s_m[tid] = m;
-    s_inv[tid] = 1.0f / l;
+  const int d0 = 4 * (threadIdx.x % (D / 4));
+  float m = kAtNoMax;
+  for (int gg = g_first; gg <= g_last; ++gg) m = fmaxf(m, wk.part_ml[(long long)slot_of(gg) * 2 * kAtBQ + row]);
+  float l = 0.f;
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 4
+  for (int gg = g_first; gg <= g_last; ++gg) {
+    const long long sl = slot_of(gg);
+    const float* ml = wk.part_ml + sl * 2 * kAtBQ + row;
+    const float4 v = *reinterpret_cast<const float4*>(wk.part_o + (sl * kAtBQ + row) * D + d0);
+    const float wgt = __builtin_amdgcn_exp2f(ml[0] - m);
+    l += ml[kAtBQ] * wgt;
+    acc.x = fmaf(v.x, wgt, acc.x); acc.y = fmaf(v.y, wgt, acc.y);
+    acc.z = fmaf(v.z, wgt, acc.z); acc.w = fmaf(v.w, wgt, acc.w);
   }
-  __syncthreads();
-  constexpr int C4 = D / 4;  // float4 groups per row
-  for (int e4 = tid; e4 < rows * C4; e4 += 256) {
-    const int row = e4 / C4, d0 = 4 * (e4 - row * C4);
-    const float m = s_m[row];
-    float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
-    for (int gg = g_first; gg <= g_last; ++gg) {
-      const int sl = slot_of(gg);
-      const float wgt = __builtin_amdgcn_exp2f(wk.part_ml[(long long)sl * 2 * kAtBQ + row0 + row] - m);
-      const float4 v = *reinterpret_cast<const float4*>(wk.part_o + ((long long)sl * kAtBQ + row0 + row) * D + d0);
-      acc.x = fmaf(v.x, wgt, acc.x); acc.y = fmaf(v.y, wgt, acc.y);
-      acc.z = fmaf(v.z, wgt, acc.z); acc.w = fmaf(v.w, wgt, acc.w);
-    }
-    const float inv = s_inv[row];
-    const long long off = (long long)(qt * kAtBQ + row0 + row) * p.ld_o + (long long)h * D + d0;
-    if (OUT_F32) {
-      *reinterpret_cast<float4*>(static_cast<float*>(p.O) + off) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
-    } else {
-      bf16x4 ob;
-      ob[0] = (__bf16)(acc.x * inv); ob[1] = (__bf16)(acc.y * inv); ob[2] = (__bf16)(acc.z * inv); ob[3] = (__bf16)(acc.w * inv);
-      *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(p.O) + off) = ob;
-    }
+  const float inv = 1.0f / l;
+  const long long off = (long long)q_row * p.ld_o + (long long)h * D + d0;
+  if (OUT_F32) {
+    *reinterpret_cast<float4*>(static_cast<float*>(p.O) + off) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+  } else {
+    bf16x4 ob;
+    ob[0] = (__bf16)(acc.x * inv); ob[1] = (__bf16)(acc.y * inv); ob[2] = (__bf16)(acc.z * inv); ob[3] = (__bf16)(acc.w * inv);
+    *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(p.O) + off) = ob;
   }
 }
 
@@ -863,11 +859,11 @@ int launch_variant(hipStream_t st, const AttnArgs& a) {
   static LdsLimit lds_limit;
   const int rc = set_lds_limit(lds_limit, chunk_attention_kernel<D, OUT_F32, GATHER, KV8>, attn_lds_bytes(D, GATHER));
   if (rc != PAFU_OK) return rc;
-  hipLaunchKernelGGL((chunk_attention_kernel<D, OUT_F32, GATHER, KV8>), dim3(a.w.n_wg), dim3(kAtThreads),
+  hipLaunchKernelGGL((chunk_attention_kernel<D, OUT_F32, GATHER, KV8>), dim3(a.w.n_whole + a.w.n_runs), dim3(kAtThreads),
                      attn_lds_bytes(D, GATHER), st, a);
-  if (a.w.split)
-    hipLaunchKernelGGL((attn_combine_kernel<D, OUT_F32>), dim3(a.w.n_qt * a.p.N_heads * kAtCombineSplit), dim3(256), 0,
-                       st, a);
+  if (a.w.n_runs)
+    hipLaunchKernelGGL((attn_combine_kernel<D, OUT_F32>),
+                       dim3((a.w.n_items - a.w.n_whole) * (kAtBQ / kAtCombineRows<D>)), dim3(256), 0, st, a);
   return check_launch();
 }
 
@@ -912,35 +908,59 @@ int launch_attention(hipStream_t st, const void* Q, int Lq, const void* Kc, cons
   AttnWork& w = a.w;
   w.n_qt = (Lq + kAtBQ - 1) / kAtBQ;
   long long units_head = 0;
-  int u0 = attn_units(0, Lq, n_kept, Lc, p.block_len);
+  const int u0_item = attn_units(0, Lq, n_kept, Lc, p.block_len);
   bool uniform = true;
   for (int qt = 0; qt < w.n_qt; ++qt) {
     const int cq = attn_units(qt, Lq, n_kept, Lc, p.block_len);
     units_head += cq;
-    uniform = uniform && cq == u0;
+    uniform = uniform && cq == u0_item;
   }
   w.units_head = (int)units_head;
-  w.uniform = uniform ? u0 : 0;
-  const long long items = (long long)w.n_qt * N, U = units_head * N;
-  // Equal runs pay off when whole items leave a good part of the chip idle (few query tiles, long key axis).  With the
-  // chip nearly full the launch is limited by power, not by CU time, and the merge pass only adds to it (measured on
-  // the Wan-1.3B layer: 228 items on 256 CUs, 4 percent slower with equal runs; 192 items, 12 percent faster; 84
-  // items, 2 times faster), and over several rounds contiguous runs would spread an XCD's workgroups over several
-  // heads and thrash its L2.  They need the workspace, and runs of at least a few units each.
+  w.uniform = uniform ? u0_item : 0;
+  const long long items = (long long)w.n_qt * N;
   int cus = compute_units();
   if (cus > kAtMaxRuns) cus = kAtMaxRuns;
-  const bool uneven = items * 5 <= (long long)cus * 4 || kStudySplitAlways;
-  w.split = 0;
-  w.n_wg = (int)items;
+  w.n_items = (int)items;
+  w.n_whole = (int)items;
+  w.n_runs = 0;
+  w.u0 = w.U = 0;
   w.part_o = nullptr;
   w.part_ml = nullptr;
-  if (uneven && workspace != nullptr && U >= 4ll * cus) {
-    const size_t need = (size_t)2 * cus * ((size_t)kAtBQ * D + 2 * kAtBQ) * sizeof(float);
-    if (workspace_bytes >= need && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
-      w.split = 1;
-      w.n_wg = cus;
+  // Cut the last round when it fills at most four fifths of the CUs (above that the launch is limited by power, not by CU
+  // time, and the merge pass only adds to it: 228 items on 256 CUs were 4 percent slower) and the cut shortens it by more
+  // than the merge pass takes.  Measured against whole items, start / now: 12 items of 57 units (51 queries over 7154
+  // keys, D = 64) 122 / 25 us; 12 of 44 units 126 / 28 us; 5 of 10 units (D = 64) 29 / 17 us; 84 of 71: 194 / 168 us (3 runs per item
+  // instead of 256 equal ones: 183); 272 of 44 (D = 64): 412 / 234 us; 520 of 36: 745 / 539 us.
+  const long long last = items % cus;  // items of the last round
+  const bool mixed = items > last && cus % kAtXcds != 0;  // (the kernel's XCD mapping needs whole rounds of XCDs)
+  if (last > 0 && (last * 5 <= (long long)cus * 4 || kStudySplitAlways) && !mixed && workspace != nullptr) {
+    const int first_cut = (int)(items - last);
+    long long u0 = (long long)(first_cut / w.n_qt) * units_head;
+    for (int qt = 0; qt < first_cut % w.n_qt; ++qt) u0 += attn_units(qt, Lq, n_kept, Lc, p.block_len);
+    const long long U = units_head * N - u0;
+    int longest = 0;  // what the last round takes without a cut
+    for (int qt = 0; qt < w.n_qt; ++qt) {
+      const int cq = attn_units(qt, Lq, n_kept, Lc, p.block_len);
+      longest = cq > longest ? cq : longest;
+    }
+    long long runs = U / kAtMinRunUnits < cus ? U / kAtMinRunUnits : cus;
+    if (uniform && u0_item >= 2 * kAtMinRunUnits && last * 2 <= cus) {
+      // the same number of runs in every item, unless that leaves too much of the chip idle: a run that crosses from one
+      // item to the next starts twice (queries, ring, first product), which takes about as long as 3/2 units
+      long long per_item = cus / last < u0_item / kAtMinRunUnits ? cus / last : u0_item / kAtMinRunUnits;
+      const long long run = (u0_item + per_item - 1) / per_item;
+      per_item = (u0_item + run - 1) / run;
+      if (2 * run <= 2 * ((U + runs - 1) / runs) + 3) runs = per_item * last;
+    }
+    const size_t need = (size_t)2 * runs * ((size_t)kAtBQ * D + 2 * kAtBQ) * sizeof(float);
+    if (runs > last && longest - (U + runs - 1) / runs >= kAtMinCutGain && workspace_bytes >= need &&
+        (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
+      w.n_whole = first_cut;
+      w.n_runs = (int)runs;
+      w.u0 = u0;
+      w.U = U;
       w.part_o = static_cast<float*>(workspace);
-      w.part_ml = w.part_o + (size_t)2 * cus * kAtBQ * D;
+      w.part_ml = w.part_o + (size_t)2 * runs * kAtBQ * D;
     }
   }
   const bool f32 = out_dtype == PAFU_F32;

@@ -69,9 +69,8 @@ def test_attention_peaked_softmax_and_fp32_output():
         assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (odt, max_abs, rel)
 
 
-# With a workspace the launch cuts the flattened (head, query tile, key tiles) list into equal runs, one per CU, and
-# merges the partial results of the query tiles that several workgroups worked on.  These shapes are long enough for
-# that path to be taken (a few query tiles, hundreds of key tiles each), so a query tile is shared by many runs.
+# With a workspace the launch cuts the flattened (head, query tile, key tiles) list of its last, ill-filled round into
+# equal runs, at most one per CU, and merges the partial results of the query tiles that several workgroups worked on.
 @pytest.mark.parametrize("n,Lc,N,D,L_B,odt,q_gain", [
     (16000, 600, 4, 128, 600, torch.bfloat16, 1.0),   # 12 items of 130 units each over 256 runs
     (9000, 1500, 3, 128, 500, torch.bfloat16, 1.0),   # block mask: the items have different lengths
@@ -79,6 +78,10 @@ def test_attention_peaked_softmax_and_fp32_output():
     (20000, 300, 5, 64, 300, torch.bfloat16, 1.0),    # head dim 64
     (0, 9000, 2, 128, 1, torch.bfloat16, 1.0),        # no cache, strictly causal inside the chunk
     (12345, 777, 3, 128, 100, torch.bfloat16, 1.0),   # ragged everything
+    (3000, 51, 5, 64, 51, torch.bfloat16, 1.0),       # fewer runs than compute units: 120 units in runs of two
+    (900, 40, 1, 128, 40, torch.float32, 1.0),        # one item of 8 units in 4 runs
+    (300, 1700, 40, 64, 1700, torch.bfloat16, 1.0),   # 280 items on 256 CUs: a round of whole items, 24 items cut
+    (100, 1700, 38, 128, 450, torch.float32, 1.0),    # 266 items of different lengths, 10 of them cut
 ])
 def test_attention_equal_runs_match_oracle(n, Lc, N, D, L_B, odt, q_gain):
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n + Lc + N, q_gain=q_gain)
