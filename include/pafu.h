@@ -276,7 +276,8 @@ typedef struct pafu_step_args {
    * launch when that launch is a short streaming one and the list holds at most 65536 scores, so [1]..[2] is then
    * empty; the chunk rows are appended by the compaction launch, i.e. inside [2]..[3]; only when the
    * cache was empty, or the rows do not fit that kernel, a separate copy follows [4]).  In the multi-layer steps, whose stages are reordered across
-   * layers, [0]/[1] bracket a layer's scoring and [3]/[4] its attention launch; [2] is recorded once, after the
+   * layers, [0]/[1] bracket a layer's scoring and [3]/[4] the attention launch it is part of
+   * (one for all layers that share a geometry); [2] is recorded once, after the
    * selection launch, on args[0] (pafu_step_layers) or on the index layer (pafu_step_layers_shared). */
   void* stage_events[5];
   /* Storage of the K/V cache: PAFU_BF16 (0, the default) or PAFU_FP8_E4M3.  With the 8-bit format K_cache, V_cache,

@@ -362,56 +362,123 @@ WsPart attention_ws(const pafu_step_args* a, bool scoring) {
   return WsPart{static_cast<char*>(a->workspace) + used, a->workspace_bytes - used};
 }
 
-// The cache part of a step for one layer: compact K/V (and the score list when sel_scores is given) to `ids`,
-// attend over retained + chunk, and in ROLLOUT append the chunk's K/V behind the retained rows.
-// `done`: what a batched launch of the caller has already moved for this layer.
+// The cache part of a step for one layer comes in three pieces, so that the middle one may serve several layers:
+//   enqueue_cache     - compact K/V (and the score list when sel_scores is given) to `ids`; *done gains what it moved
+//   enqueue_attention - attend over retained + chunk
+//   enqueue_append    - in ROLLOUT the chunk's K/V behind the retained rows, unless the first piece did that
+// `done`: what has already been moved for this layer.
 enum : int { kDoneNothing = 0, kDoneCompact = 1, kDoneAppend = 2 };
-int enqueue_kv(hipStream_t st, const pafu_step_args* a, const int* ids, const float* sel_scores, float* SL_out,
-               void* attn_ws, size_t attn_ws_bytes, int done = kDoneNothing) {
-  const int n_kept = a->k < a->n ? a->k : a->n;
-  const float scale = a->softmax_scale > 0.f ? a->softmax_scale : 1.0f / sqrtf((float)a->D);
+
+int kept_rows(const pafu_step_args* a) { return a->k < a->n ? a->k : a->n; }
+char* behind_kept(const pafu_step_args* a, void* slab) {
+  return static_cast<char*>(slab) + (long long)kept_rows(a) * a->ld_out * kv_dtype_bytes(a->kv_dtype);
+}
+
+int enqueue_cache(hipStream_t st, const pafu_step_args* a, const int* ids, const float* sel_scores, float* SL_out,
+                  int* done) {
+  const int n_kept = kept_rows(a);
   const bool kv8 = a->kv_dtype == PAFU_FP8_E4M3;
   const int kvb = kv8 ? 1 : 2;
   int rc;
   // In a rollout with bf16 storage the compaction launch also moves the chunk's rows behind the retained ones: the
   // append costs no launch of its own, and attention (which reads the chunk from its own buffers) does not wait for it.
-  bool appended = (done & kDoneAppend) != 0;
-  if (a->n > 0 && !(done & kDoneCompact)) {
+  if (a->n > 0 && !(*done & kDoneCompact)) {
     // (with the 8-bit cache the tail rows are quantised on the way, in both modes: the chunk always attends over codes)
     CompactTail tail{static_cast<const char*>(a->K_chunk), static_cast<const char*>(a->V_chunk),
                      (long long)a->ld_chunk * 2, a->Lc, kv8 ? 1 : 0, ldexpf(1.0f, -a->k_scale_log2),
                      ldexpf(1.0f, -a->v_scale_log2)};
-    appended = (kv8 || a->mode != PAFU_MODE_SINGLE) && compact_takes_tail(a->N * a->D * kvb);
+    const bool appended = (kv8 || a->mode != PAFU_MODE_SINGLE) && compact_takes_tail(a->N * a->D * kvb);
     rc = launch_compact(st, a->K_cache, a->V_cache, sel_scores, a->ld_cache * kvb, a->n, ids, n_kept, a->N * a->D * kvb,
                         a->K_out, a->V_out, SL_out, a->ld_out * kvb, nullptr, appended ? &tail : nullptr);
     if (rc) return rc;
+    *done = kDoneCompact | (appended ? kDoneAppend : 0);
   }
-  char* ko = static_cast<char*>(a->K_out) + (long long)n_kept * a->ld_out * kvb;
-  char* vo = static_cast<char*>(a->V_out) + (long long)n_kept * a->ld_out * kvb;
-  if (kv8 && !appended) {
+  if (kv8 && !(*done & kDoneAppend)) {
     // the chunk's K/V enter the cache as codes before attention: the chunk attends over exactly what later steps
     // will find in the cache, and in a rollout nothing is left to append
     rc = launch_quantize(st, a->K_chunk, a->V_chunk, a->ld_chunk * 2, a->Lc, a->N * a->D, a->k_scale_log2,
-                         a->v_scale_log2, ko, vo, a->ld_out);
+                         a->v_scale_log2, behind_kept(a, a->K_out), behind_kept(a, a->V_out), a->ld_out);
     if (rc) return rc;
+    *done |= kDoneAppend;
   }
-  rc = record_stage(st, a, 3);
+  return PAFU_OK;
+}
+
+// args[0 .. n_layers): layers of one attention geometry (same_attention), at most kAttnBatchMax
+int enqueue_attention(hipStream_t st, const pafu_step_args* args, int n_layers, void* attn_ws, size_t attn_ws_bytes) {
+  const pafu_step_args* a = &args[0];
+  const float scale = a->softmax_scale > 0.f ? a->softmax_scale : 1.0f / sqrtf((float)a->D);
+  const bool kv8 = a->kv_dtype == PAFU_FP8_E4M3;
+  AttnLayer layers[kAttnBatchMax];
+  int rc;
+  for (int l = 0; l < n_layers; ++l) {
+    const pafu_step_args* b = &args[l];
+    layers[l] = AttnLayer{b->Q, b->K_out, b->V_out, kv8 ? behind_kept(b, b->K_out) : b->K_chunk,
+                          kv8 ? behind_kept(b, b->V_out) : b->V_chunk, b->O};
+    if ((rc = record_stage(st, b, 3))) return rc;
+  }
+  rc = launch_attention(st, layers, n_layers, a->Lc, kept_rows(a), a->Lc, a->N, a->D, a->ld_chunk, a->ld_out,
+                        kv8 ? a->ld_out : a->ld_chunk, a->ld_o, a->block_len, scale, a->out_dtype, attn_ws, attn_ws_bytes,
+                        nullptr, 0, a->kv_dtype, kv8 ? ldexpf(1.0f, a->k_scale_log2) : 1.f,
+                        kv8 ? ldexpf(1.0f, a->v_scale_log2) : 1.f);
   if (rc) return rc;
-  if (kv8)
-    rc = launch_attention(st, a->Q, a->Lc, a->K_out, a->V_out, n_kept, ko, vo, a->Lc, a->N, a->D, a->ld_chunk, a->ld_out,
-                          a->ld_out, a->ld_o, a->block_len, scale, a->O, a->out_dtype, attn_ws, attn_ws_bytes, nullptr, 0,
-                          PAFU_FP8_E4M3, ldexpf(1.0f, a->k_scale_log2), ldexpf(1.0f, a->v_scale_log2));
-  else
-    rc = launch_attention(st, a->Q, a->Lc, a->K_out, a->V_out, n_kept, a->K_chunk, a->V_chunk, a->Lc, a->N, a->D,
-                          a->ld_chunk, a->ld_out, a->ld_chunk, a->ld_o, a->block_len, scale, a->O, a->out_dtype, attn_ws,
-                          attn_ws_bytes);
+  for (int l = 0; l < n_layers; ++l)
+    if ((rc = record_stage(st, &args[l], 4))) return rc;
+  return PAFU_OK;
+}
+
+int enqueue_append(hipStream_t st, const pafu_step_args* a, int done) {
+  if (a->mode == PAFU_MODE_SINGLE || (done & kDoneAppend)) return PAFU_OK;
+  return launch_append(st, a->K_chunk, a->V_chunk, nullptr, a->ld_chunk * 2, a->Lc, a->N * a->D * 2,
+                       behind_kept(a, a->K_out), behind_kept(a, a->V_out), nullptr, a->ld_out * 2);
+}
+
+int enqueue_kv(hipStream_t st, const pafu_step_args* a, const int* ids, const float* sel_scores, float* SL_out,
+               void* attn_ws, size_t attn_ws_bytes) {
+  int done = kDoneNothing;
+  int rc = enqueue_cache(st, a, ids, sel_scores, SL_out, &done);
   if (rc) return rc;
-  rc = record_stage(st, a, 4);
+  rc = enqueue_attention(st, a, 1, attn_ws, attn_ws_bytes);
   if (rc) return rc;
-  if (a->mode != PAFU_MODE_SINGLE && !kv8 && !appended) {
-    rc = launch_append(st, a->K_chunk, a->V_chunk, nullptr, a->ld_chunk * 2, a->Lc, a->N * a->D * 2, ko, vo, nullptr,
-                       a->ld_out * 2);
+  return enqueue_append(st, a, done);
+}
+
+// Can the attention of these two layers share a launch?
+bool same_attention(const pafu_step_args* a, const pafu_step_args* b) {
+  return a->mode == b->mode && a->N == b->N && a->D == b->D && kept_rows(a) == kept_rows(b) && a->Lc == b->Lc &&
+         a->block_len == b->block_len && a->ld_chunk == b->ld_chunk && a->ld_out == b->ld_out && a->ld_o == b->ld_o &&
+         a->softmax_scale == b->softmax_scale && a->out_dtype == b->out_dtype && a->kv_dtype == b->kv_dtype &&
+         a->k_scale_log2 == b->k_scale_log2 && a->v_scale_log2 == b->v_scale_log2;
+}
+
+// The cache part of the layers of a multi-layer step, behind their selections: caches first, then attention, one launch
+// for every stretch of layers with the same geometry (one layer's items leave the chip idle in their last round: 228 on
+// 256 CUs at the Wan-1.3B shape), then what is left to append.  `index_layer` >= 0: the one layer whose indices and score
+// list serve all of them, and whose workspace a layer without one borrows.
+int enqueue_layers_kv(hipStream_t st, const pafu_step_args* args, int n_layers, int index_layer, int done_batch) {
+  const pafu_step_args* idx = index_layer >= 0 ? &args[index_layer] : nullptr;
+  int rc;
+  for (int first = 0, last; first < n_layers; first = last) {
+    for (last = first + 1; last < n_layers && last - first < kAttnBatchMax && same_attention(&args[first], &args[last]);)
+      ++last;
+    int done[kAttnBatchMax];
+    WsPart ws{nullptr, 0};
+    for (int l = first; l < last; ++l) {
+      const pafu_step_args* a = &args[l];
+      const bool scores = idx == nullptr || l == index_layer;
+      done[l - first] = done_batch;
+      rc = enqueue_cache(st, a, idx ? idx->ids : a->ids,
+                         scores ? (a->mode == PAFU_MODE_SINGLE ? a->scores : a->SL_in) : nullptr,
+                         scores ? a->SL_out : nullptr, &done[l - first]);
+      if (rc) return rc;
+      const WsPart own = attention_ws(a, scores);
+      if (own.bytes > ws.bytes) ws = own;
+    }
+    if (ws.p == nullptr && idx != nullptr) ws = attention_ws(idx, true);
+    rc = enqueue_attention(st, &args[first], last - first, ws.p, ws.bytes);
     if (rc) return rc;
+    for (int l = first; l < last; ++l)
+      if ((rc = enqueue_append(st, &args[l], done[l - first]))) return rc;
   }
   return PAFU_OK;
 }
@@ -604,9 +671,10 @@ int pafu_chunk_attention_fp8(void* stream, const void* Q, int Lq, const void* Kc
   if (rc) return rc;
   if (workspace != nullptr && workspace_bytes > 0 && !aligned16(workspace)) return PAFU_ERR_ALIGN;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
-  return launch_attention(static_cast<hipStream_t>(stream), Q, Lq, Kc_q, Vc_q, n_kept, Kn_q, Vn_q, Lc, N, D, ld_q, ld_c,
-                          ld_n, ld_o, block_len, scale, O, out_dtype, workspace, workspace_bytes, nullptr, 0,
-                          PAFU_FP8_E4M3, ldexpf(1.0f, k_scale_log2), ldexpf(1.0f, v_scale_log2));
+  const AttnLayer layer{Q, Kc_q, Vc_q, Kn_q, Vn_q, O};
+  return launch_attention(static_cast<hipStream_t>(stream), &layer, 1, Lq, n_kept, Lc, N, D, ld_q, ld_c, ld_n, ld_o,
+                          block_len, scale, out_dtype, workspace, workspace_bytes, nullptr, 0, PAFU_FP8_E4M3,
+                          ldexpf(1.0f, k_scale_log2), ldexpf(1.0f, v_scale_log2));
 }
 
 int pafu_compact_kv_counted(void* stream, const void* K, const void* V, const float* SL, long long ld_in, int n,
@@ -635,8 +703,9 @@ int pafu_chunk_attention(void* stream, const void* Q, int Lq, const void* Kc, co
                           out_dtype);
   if (rc) return rc;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
-  return launch_attention(static_cast<hipStream_t>(stream), Q, Lq, Kc, Vc, n_kept, Kn, Vn, Lc, N, D, ld_q, ld_c, ld_n,
-                          ld_o, block_len, scale, O, out_dtype, workspace, workspace_bytes);
+  const AttnLayer layer{Q, Kc, Vc, Kn, Vn, O};
+  return launch_attention(static_cast<hipStream_t>(stream), &layer, 1, Lq, n_kept, Lc, N, D, ld_q, ld_c, ld_n, ld_o,
+                          block_len, scale, out_dtype, workspace, workspace_bytes);
 }
 
 int pafu_chunk_attention_gather(void* stream, const void* Q, int Lq, const void* K_cache, const void* V_cache,
@@ -658,8 +727,9 @@ int pafu_chunk_attention_gather(void* stream, const void* Q, int Lq, const void*
                           ld_o, O, out_dtype);
   if (rc) return rc;
   const float scale = softmax_scale > 0.f ? softmax_scale : 1.0f / sqrtf((float)D);
-  return launch_attention(static_cast<hipStream_t>(stream), Q, Lq, K_cache, V_cache, n_kept, Kn, Vn, Lc, N, D, ld_q,
-                          ld_c, ld_n, ld_o, block_len, scale, O, out_dtype, workspace, workspace_bytes, ids, n_cache);
+  const AttnLayer layer{Q, K_cache, V_cache, Kn, Vn, O};
+  return launch_attention(static_cast<hipStream_t>(stream), &layer, 1, Lq, n_kept, Lc, N, D, ld_q, ld_c, ld_n, ld_o,
+                          block_len, scale, out_dtype, workspace, workspace_bytes, ids, n_cache);
 }
 
 size_t pafu_sse_workspace_bytes(int L, int N) { return L > 0 && N > 0 ? sse_workspace_bytes(L, N) : 0; }
@@ -713,7 +783,7 @@ int pafu_step_layers(void* stream, const pafu_step_args* args, int n_layers) {
   }
   // The layers are independent, so the order of their stages is free: all scores first, then every layer's selection
   // in one launch (a selection occupies a single CU; one per layer in a row would leave the chip idle 30 times), then
-  // compaction and attention layer by layer.
+  // the compactions and the attention, each in one launch where the layers share a geometry.
   hipStream_t st = static_cast<hipStream_t>(stream);
   for (int l = 0; l < n_layers; ++l) {
     int rc = enqueue_scores(st, &args[l]);
@@ -739,14 +809,7 @@ int pafu_step_layers(void* stream, const pafu_step_args* args, int n_layers) {
   int rc_batch;
   const int done = enqueue_compact_batch(st, args, n_layers, nullptr, -1, &rc_batch);
   if (rc_batch) return rc_batch;
-  for (int l = 0; l < n_layers; ++l) {
-    const pafu_step_args* a = &args[l];
-    const WsPart ws = attention_ws(a, true);
-    int rc = enqueue_kv(st, a, a->ids, a->mode == PAFU_MODE_SINGLE ? a->scores : a->SL_in, a->SL_out, ws.p, ws.bytes,
-                        done);
-    if (rc) return rc;
-  }
-  return PAFU_OK;
+  return enqueue_layers_kv(st, args, n_layers, -1, done);
 }
 
 int pafu_step_layers_shared(void* stream, const pafu_step_args* args, int n_layers, int index_layer) {
@@ -780,16 +843,7 @@ int pafu_step_layers_shared(void* stream, const pafu_step_args* args, int n_laye
   int rc_batch;
   const int done = enqueue_compact_batch(st, args, n_layers, idx->ids, index_layer, &rc_batch);
   if (rc_batch) return rc_batch;
-  for (int l = 0; l < n_layers; ++l) {
-    const bool is_idx = l == index_layer;
-    // a layer without a workspace of its own borrows the index layer's (the layers run one after the other)
-    WsPart ws = attention_ws(&args[l], is_idx);
-    if (ws.p == nullptr) ws = attention_ws(idx, true);
-    rc = enqueue_kv(st, &args[l], idx->ids, is_idx ? sel_scores : nullptr, is_idx ? idx->SL_out : nullptr, ws.p,
-                    ws.bytes, done);
-    if (rc) return rc;
-  }
-  return PAFU_OK;
+  return enqueue_layers_kv(st, args, n_layers, index_layer, done);
 }
 
 }  // extern "C"

@@ -52,16 +52,11 @@ __device__ __forceinline__ unsigned pack_bf16(float lo, float hi) {
 }
 
 struct AttnParams {
-  const unsigned short* Q;
-  const unsigned short* Kc;
-  const unsigned short* Vc;
-  const unsigned short* Kn;
-  const unsigned short* Vn;
-  void* O;
   const int* ids;  // gather variant: retained row r of the cache segment is row ids[r] of Kc / Vc
   int n_cache;     // rows behind Kc / Vc in the gather variant
   long long ld_q, ld_c, ld_n, ld_o;
-  int Lq, n_kept, Lc, block_len, N_heads;
+  int Lq, n_kept, Lc, block_len;
+  int N_heads;  // heads per layer; the work list runs over the heads of all layers, layer by layer
   float scale_log2;  // softmax scale * log2(e)
   float k_scale, v_scale;  // 8-bit K/V: the tensors' power-of-two scales (a stored code c stands for c * scale)
 };
@@ -324,7 +319,7 @@ struct AttnWork {
   int n_qt;           // query tiles per head
   int units_head;     // units of one head (sum over its query tiles)
   int uniform;        // units of every query tile when they are all equal (no block mask), else 0
-  int n_items;        // heads * n_qt
+  int n_items;        // heads of all layers * n_qt
   int n_whole;        // workgroup g < n_whole takes item g
   int n_runs;         // equal runs over the units of the items from n_whole on
   long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list
@@ -344,6 +339,7 @@ __host__ __device__ inline long long attn_run_begin(long long g, long long U, lo
 struct AttnArgs {
   AttnParams p;
   AttnWork w;
+  AttnLayer layer[kAttnBatchMax];
 };
 
 // Wave-uniform values that come out of vector instructions (64-bit divisions are expanded on the vector ALU) are
@@ -490,7 +486,9 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
     const int n_iter = pb - pa;
     const int tb = 2 * pa;  // first key tile of the segment
     const int i_first = uniform_i32(qt) * kAtBQ;
-    const long long head_off = (long long)uniform_i32(h) * D;
+    const int layer = uniform_i32(h / p.N_heads);
+    const AttnLayer& L = args.layer[layer];
+    const long long head_off = (long long)uniform_i32(h - layer * p.N_heads) * D;
 
     // number of visible keys: per lane (its query) and the tile's first query, both cut at the segment's end
     auto visible = [&](int i) {
@@ -520,13 +518,13 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       const int id = ((const __attribute__((address_space(3))) int*)id_ring)[(tile % kAtIdStages) * kAtTileKeys + row];
       return id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1);
     };
-    auto issue_one = [&](int tile_, const unsigned short* cache, const unsigned short* chunk, lds_byte* ring,
+    auto issue_one = [&](int tile_, const void* cache, const void* chunk, lds_byte* ring,
                          unsigned offc, unsigned offn, bool is_v) {
       const int tile = uniform_i32(tile_);
       const int stage = tile % kAtStages;
       const int key0 = tile * kAtTileKeys;
-      const char* base_c = reinterpret_cast<const char*>(cache) + head_off * ELB;
-      const char* base_n = reinterpret_cast<const char*>(chunk) + head_off * ELB - (long long)p.n_kept * ldn_b;
+      const char* base_c = static_cast<const char*>(cache) + head_off * ELB;
+      const char* base_n = static_cast<const char*>(chunk) + head_off * ELB - (long long)p.n_kept * ldn_b;
       const bool all_cache = key0 + kAtTileKeys <= p.n_kept;
       const bool all_chunk = key0 >= p.n_kept && key0 + kAtTileKeys <= n_total;
       if (GATHER && all_cache) {  // workgroup-uniform
@@ -578,9 +576,9 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
     // issued into the slots of K(t) and V(t-2), whose last readers finished in step t-1.  Tiles past the end of the
     // key axis hold clamped rows and are masked or never read.
     // In the gather variant the ids of tiles kt and kt-2 must already be visible in the ids ring.
-    auto issue_k_tile = [&](int kt) { issue_one(tb + kt, p.Kc, p.Kn, k_land, k_offc, k_offn, false); };
+    auto issue_k_tile = [&](int kt) { issue_one(tb + kt, L.Kc, L.Kn, k_land, k_offc, k_offn, false); };
     auto issue_v_tile = [&](int kt) {
-      if (kt >= 2) issue_one(tb + kt - 2, p.Vc, p.Vn, v_land, v_offc, v_offn, true);
+      if (kt >= 2) issue_one(tb + kt - 2, L.Vc, L.Vn, v_land, v_offc, v_offn, true);
     };
     auto issue_tiles = [&](int kt) {  // kt relative to the segment
       issue_k_tile(kt);
@@ -620,7 +618,7 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
     bf16x8 qf[KD];
     {
       const int qi = q_row < p.Lq ? q_row : p.Lq - 1;
-      const unsigned short* qp = p.Q + (long long)qi * p.ld_q + head_off + 8 * g;
+      const unsigned short* qp = static_cast<const unsigned short*>(L.Q) + (long long)qi * p.ld_q + head_off + 8 * g;
 #pragma unroll
       for (int kk = 0; kk < KD; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + 16 * kk);
     }
@@ -762,11 +760,11 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
               const float v2 = o[b][4 * q4 + 2] * inv, v3 = o[b][4 * q4 + 3] * inv;
               const long long off = (long long)q_row * p.ld_o + head_off + d0;
               if (OUT_F32) {
-                *reinterpret_cast<float4*>(static_cast<float*>(p.O) + off) = make_float4(v0, v1, v2, v3);
+                *reinterpret_cast<float4*>(static_cast<float*>(L.O) + off) = make_float4(v0, v1, v2, v3);
               } else {
                 bf16x4 ob;
                 ob[0] = (__bf16)v0; ob[1] = (__bf16)v1; ob[2] = (__bf16)v2; ob[3] = (__bf16)v3;
-                *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(p.O) + off) = ob;
+                *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(L.O) + off) = ob;
               }
             }
         }
@@ -844,13 +842,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
     acc.z = fmaf(v.z, wgt, acc.z); acc.w = fmaf(v.w, wgt, acc.w);
   }
   const float inv = 1.0f / l;
-  const long long off = (long long)q_row * p.ld_o + (long long)h * D + d0;
+  const int layer = h / p.N_heads;
+  void* const O = args.layer[layer].O;
+  const long long off = (long long)q_row * p.ld_o + (long long)(h - layer * p.N_heads) * D + d0;
   if (OUT_F32) {
-    *reinterpret_cast<float4*>(static_cast<float*>(p.O) + off) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
+    *reinterpret_cast<float4*>(static_cast<float*>(O) + off) = make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);
   } else {
     bf16x4 ob;
     ob[0] = (__bf16)(acc.x * inv); ob[1] = (__bf16)(acc.y * inv); ob[2] = (__bf16)(acc.z * inv); ob[3] = (__bf16)(acc.w * inv);
-    *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(p.O) + off) = ob;
+    *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(O) + off) = ob;
   }
 }
 
@@ -883,21 +883,15 @@ size_t attention_workspace_bytes(int D) {
   return (size_t)2 * kAtMaxRuns * ((size_t)kAtBQ * D + 2 * kAtBQ) * sizeof(float);
 }
 
-int launch_attention(hipStream_t st, const void* Q, int Lq, const void* Kc, const void* Vc, int n_kept,
-                     const void* Kn, const void* Vn, int Lc, int N, int D, long long ld_q, long long ld_c,
-                     long long ld_n, long long ld_o, int block_len, float scale, void* O, int out_dtype,
-                     void* workspace, size_t workspace_bytes, const int* ids, int n_cache, int kv_dtype,
+int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int Lq, int n_kept, int Lc, int N, int D,
+                     long long ld_q, long long ld_c, long long ld_n, long long ld_o, int block_len, float scale,
+                     int out_dtype, void* workspace, size_t workspace_bytes, const int* ids, int n_cache, int kv_dtype,
                      float k_scale, float v_scale) {
   AttnArgs a;
   AttnParams& p = a.p;
+  for (int l = 0; l < n_layers; ++l) a.layer[l] = layers[l];
   p.ids = ids;
   p.n_cache = n_cache;
-  p.Q = static_cast<const unsigned short*>(Q);
-  p.Kc = static_cast<const unsigned short*>(Kc);
-  p.Vc = static_cast<const unsigned short*>(Vc);
-  p.Kn = static_cast<const unsigned short*>(Kn);
-  p.Vn = static_cast<const unsigned short*>(Vn);
-  p.O = O;
   p.ld_q = ld_q; p.ld_c = ld_c; p.ld_n = ld_n; p.ld_o = ld_o;
   p.Lq = Lq; p.n_kept = n_kept; p.Lc = Lc; p.N_heads = N;
   p.block_len = block_len < Lc ? block_len : Lc;  // blocks at least as long as the chunk mean "no mask"
@@ -917,7 +911,7 @@ int launch_attention(hipStream_t st, const void* Q, int Lq, const void* Kc, cons
   }
   w.units_head = (int)units_head;
   w.uniform = uniform ? u0_item : 0;
-  const long long items = (long long)w.n_qt * N;
+  const long long heads = (long long)N * n_layers, items = heads * w.n_qt;
   int cus = compute_units();
   if (cus > kAtMaxRuns) cus = kAtMaxRuns;
   w.n_items = (int)items;
@@ -937,7 +931,7 @@ int launch_attention(hipStream_t st, const void* Q, int Lq, const void* Kc, cons
     const int first_cut = (int)(items - last);
     long long u0 = (long long)(first_cut / w.n_qt) * units_head;
     for (int qt = 0; qt < first_cut % w.n_qt; ++qt) u0 += attn_units(qt, Lq, n_kept, Lc, p.block_len);
-    const long long U = units_head * N - u0;
+    const long long U = units_head * heads - u0;
     int longest = 0;  // what the last round takes without a cut
     for (int qt = 0; qt < w.n_qt; ++qt) {
       const int cq = attn_units(qt, Lq, n_kept, Lc, p.block_len);

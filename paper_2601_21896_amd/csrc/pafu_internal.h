@@ -109,10 +109,15 @@ int launch_sse(hipStream_t st, const void* Q, const void* K, int L, int N, int D
 // workspace (may be null): with attention_workspace_bytes(D) bytes the launch may cut its work into equal runs.
 size_t attention_workspace_bytes(int D);
 int attention_study_build();  // 0 in the shipped library; the ablation mask of a study build
-int launch_attention(hipStream_t st, const void* Q, int Lq, const void* Kc, const void* Vc, int n_kept,
-                     const void* Kn, const void* Vn, int Lc, int N, int D, long long ld_q, long long ld_c,
-                     long long ld_n, long long ld_o, int block_len, float scale, void* O, int out_dtype,
-                     void* workspace, size_t workspace_bytes, const int* ids = nullptr, int n_cache = 0,
+// Up to kAttnBatchMax layers of one geometry go in one launch (ids: one layer only).
+constexpr int kAttnBatchMax = 32;
+struct AttnLayer {
+  const void *Q, *Kc, *Vc, *Kn, *Vn;
+  void* O;
+};
+int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int Lq, int n_kept, int Lc, int N, int D,
+                     long long ld_q, long long ld_c, long long ld_n, long long ld_o, int block_len, float scale,
+                     int out_dtype, void* workspace, size_t workspace_bytes, const int* ids = nullptr, int n_cache = 0,
                      int kv_dtype = PAFU_BF16, float k_scale = 1.f, float v_scale = 1.f);
 // bf16 rows -> E4M3 codes (code = round(x / 2^scale_log2), saturating) and back; row_elems = N * D, strides in bytes.
 int launch_quantize(hipStream_t st, const void* K, const void* V, long long ld_in_bytes, int rows, int row_elems,
