@@ -17,7 +17,10 @@
 // accumulator registers: rowstat holds 32 queries per wave and streams the keys (online log-sum-exp per lane),
 // colmax holds 32 keys per wave and streams the queries together with their c values.
 #include <hip/hip_runtime.h>
+#include <float.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "pafu.h"
 #include "pafu_internal.h"
@@ -36,7 +39,11 @@ constexpr int kSseTile = 64;              // streamed rows per LDS tile = per st
 constexpr int kSseStages = 4;             // ring depth
 constexpr int kSseXcds = 8;
 
-constexpr int sse_lds_bytes(int D) { return kSseStages * (kSseTile * 2 * D + kSseTile * 4); }
+// a tile's c values are read one step after its rows, so their ring is deeper
+constexpr int kSseCStages = 8;
+constexpr float kSseMaxTileSum = 256.0f;  // above 32, so that a raised maximum always settles a tile
+
+constexpr int sse_lds_bytes(int D) { return kSseStages * kSseTile * 2 * D + kSseCStages * kSseTile * 4; }
 
 struct SseParams {
   const unsigned short* held;      // [L, N, D] bf16: Q in rowstat, K in colmax
@@ -79,8 +86,18 @@ __device__ __forceinline__ void wait_vmcnt() {
 
 // COLMAX = false: rowstat.  COLMAX = true: colmax.  HT = 32-row groups of the held tensor per wave: every A fragment
 // read from LDS feeds HT matrix instructions.
+//
+// The loop is software-pipelined inside a wave: step t issues the matrix instructions of tile t+1 and after each of them
+// a slice of the reduction of tile t, because on this chip the two pipes overlap reliably only for instructions of one
+// wave.  rowstat does not look for the maximum of a tile: weights are relative to the largest score of the tiles before,
+// and a lane whose 32 weights sum up to more than kSseMaxTileSum raises it out of line (the result is mathematically
+// unchanged; the fp32 sums have the same relative precision at any scale).  The reference is a whole number, so that it
+// rounds nothing where the logarithm of the sum is added to it.
+// What bounds it: the issue slots that the matrix instructions share with the exponentials (rowstat) or with one fma and
+// half a three-way maximum per score (colmax), at the clock that the power limit leaves.  32760 tokens, 12 heads of 128:
+// the same passes one after the other (product, then reduction) 5990 us, pipelined 5242 (1100 -> 1260 TFLOP/s).
 template <int D, bool COLMAX, int HT>
-__global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(SseParams p) {
+__global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
   constexpr int ROWB = 2 * D;               // bytes per row of one head
   constexpr int TILEB = kSseTile * ROWB;    // bytes per streamed tile
   constexpr int CH = D / 8;                 // 16-byte chunks per row
@@ -90,11 +107,14 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
   constexpr int KD = D / 16;
   constexpr int LOADS = LPT + (COLMAX ? 1 : 0);  // vector-memory loads per wave per tile
   constexpr int HELD = kSseWaves * 32 * HT;      // held rows per workgroup
+  constexpr int NSLOT = 2 * KD * HT;             // matrix instructions per step
+  constexpr int EPS = 32 * HT / NSLOT;           // scores of a lane reduced behind each of them
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
   lds_byte* const ring = (lds_byte*)lds_raw;
   lds_byte* const c_ring = ring + kSseStages * TILEB;  // 64 floats per stage (colmax)
 
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c = lane & 31;
   const int L = p.L;
   // workgroup -> (head, held tile), one contiguous range of the head-major list per XCD (each has its own L2)
@@ -137,7 +157,7 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
       // so that all waves count the same number of loads)
       int src_row = tile * kSseTile + 8 * wave + (lane < 8 ? lane : 7);
       src_row = src_row < L ? src_row : L - 1;
-      lds_byte* dst = c_ring + (tile % kSseStages) * (kSseTile * 4) + 8 * wave * 4;
+      lds_byte* dst = c_ring + (tile % kSseCStages) * (kSseTile * 4) + 8 * wave * 4;
       if (lane < 8)
         dma4(c_base, (unsigned)src_row * 4u, __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)dst));
     }
@@ -154,7 +174,7 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
   float mx_low[HT], mx_diag[HT], mx_up[HT];
 #pragma unroll
   for (int ht = 0; ht < HT; ++ht) {
-    m_run[ht] = -INFINITY; l_run[ht] = 0.f;
+    m_run[ht] = -FLT_MAX; l_run[ht] = 0.f;  // (finite: a half of the lanes may never see a key)
     mx_low[ht] = -INFINITY; mx_diag[ht] = -INFINITY; mx_up[ht] = -INFINITY;
   }
   // the extremes of the key blocks [lo, hi) (in query rows) over the wave's keys (colmax)
@@ -164,88 +184,115 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
   const int w_lo_max = (w_last / L_B) * L_B;
   const int w_hi_min = w_lo_min + L_B, w_hi_max = w_lo_max + L_B;
 
-#pragma unroll
-  for (int u = 0; u < kSseStages - 1; ++u) issue(u);
-  wait_vmcnt<0>();
-  __builtin_amdgcn_s_barrier();
-
-#pragma unroll 1
-  for (int t = 0; t < n_tiles; ++t) {
-    issue(t + kSseStages - 1);  // into the slot tile t-1 vacated (tiles past the end hold clamped rows, never used)
-    const lds_byte* st = ring + (t % kSseStages) * TILEB + a_off;
-    f32x16 s[HT][2];
+  // keys past the end do not exist (rowstat; the last tile only).  Register r of s[ht][rb] is streamed row
+  // 64 t + 32 rb + 8 (r/4) + 4 g + (r%4) against held row 32 ht + c.
+  auto mask_tail = [&](f32x16 (&s)[HT][2], int row0) {
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht)
 #pragma unroll
       for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s[ht][rb][r] = 0.f;
+        for (int r = 0; r < 16; ++r)
+          if (row0 + 32 * rb + 8 * (r >> 2) + 4 * g + (r & 3) >= L) s[ht][rb][r] = -INFINITY;
+  };
+  auto tile_max = [&](const f32x16 (&s)[2]) {
+    float tmax = s[0][0];
 #pragma unroll
     for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int kk = 0; kk < KD; ++kk) {
-        const bf16x8 a = *(const __attribute__((address_space(3))) bf16x8*)(st + rb * 32 * ROWB + (((2 * kk) ^ kx2) << 4));
+      for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[rb][r]);
+    return tmax;
+  };
+
+  // Step t: reduces s_cur (tile t); MM: computes tile t+1 into s_nxt meanwhile.
+  auto step = [&](auto mm, int t, f32x16 (&s_cur)[HT][2], f32x16 (&s_nxt)[HT][2]) {
+    constexpr bool MM = decltype(mm)::value;
+    const lds_byte* st = ring + ((t + 1) % kSseStages) * TILEB + a_off;
+    // fragment m of a tile: row block m & 1, contraction step m >> 1 (the accumulators alternate)
+    auto a_frag = [&](int m) {
+      return *(const __attribute__((address_space(3))) bf16x8*)(st + (m & 1) * 32 * ROWB + (((2 * (m >> 1)) ^ kx2) << 4));
+    };
+    const __attribute__((address_space(3))) f32x4* cq =
+        (const __attribute__((address_space(3))) f32x4*)(c_ring + (t % kSseCStages) * (kSseTile * 4));
+    bf16x8 af[2];
+    f32x4 cv[2];
+    if (MM) af[0] = a_frag(0);
+    if (COLMAX) cv[0] = cq[g];
+    f32x16 zero;
 #pragma unroll
-        for (int ht = 0; ht < HT; ++ht) s[ht][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hf[ht][kk], s[ht][rb], 0, 0, 0);
+    for (int r = 0; r < 16; ++r) zero[r] = 0.f;
+    float acc[HT], held_back = 0.f;  // rowstat: sums of the tile; colmax: maxima
+#pragma unroll
+    for (int ht = 0; ht < HT; ++ht) acc[ht] = COLMAX ? -INFINITY : 0.f;
+#pragma unroll
+    for (int i = 0; i < NSLOT; ++i) {
+      const int m = i / HT, ht_m = i % HT;
+      if (MM) {
+        const int rb = m & 1, kk = m >> 1;
+        if (ht_m == 0 && m + 1 < 2 * KD) af[(m + 1) & 1] = a_frag(m + 1);
+        // (the empty asm statements keep the interleaving written here: volatile ones are not reordered)
+        asm volatile("" : "+v"(af[m & 1]));
+        if (kk == 0) s_nxt[ht_m][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m & 1], hf[ht_m][kk], zero, 0, 0, 0);
+        else s_nxt[ht_m][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[m & 1], hf[ht_m][kk], s_nxt[ht_m][rb], 0, 0, 0);
+        asm volatile("" : "+v"(s_nxt[ht_m][rb]));
       }
-    // register r of s[ht][rb] is streamed row  t 64 + 32 rb + 8 (r/4) + 4 g + (r%4)  against held row 32 ht + c
-    const int row0 = t * kSseTile;
-    if (!COLMAX) {
-      // ---- online log-sum-exp over the keys
 #pragma unroll
-      for (int ht = 0; ht < HT; ++ht) {
-        if (row0 + kSseTile > L) {  // ragged last tile: keys past the end do not exist
+      for (int x = 0; x < EPS; ++x) {
+        const int e = EPS * i + x, ht = e % HT, k = e / HT, rb = k >> 4, r = k & 15;
+        if (COLMAX) {  // z - c of the element, kept in place for the tiles that need it by block relation
+          if (ht == 0 && (k & 3) == 0 && k + 4 < 32) cv[((k >> 2) + 1) & 1] = cq[2 * ((k >> 2) + 1) + g];
+          s_cur[ht][rb][r] = fmaf(s_cur[ht][rb][r], sc, -cv[(k >> 2) & 1][k & 3]);
+          if (k & 1) acc[ht] = fmaxf(fmaxf(acc[ht], s_cur[ht][rb][r - 1]), s_cur[ht][rb][r]);
+          asm volatile("" : "+v"(acc[ht]));
+        } else {  // the weight; the sum of the PREVIOUS one goes behind it, because a transcendental takes several
+          // issue slots to arrive
+          asm volatile("" : "+v"(m_run[ht]));
+          float w = __builtin_amdgcn_exp2f(fmaf(s_cur[ht][rb][r], sc, -m_run[ht]));
+          if (e > 0) {
+            acc[(e - 1) % HT] += held_back;
+            asm volatile("" : "+v"(acc[(e - 1) % HT]));
+          }
+          held_back = w;
+          asm volatile("" : "+v"(held_back));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (MM && i == NSLOT / 4) {  // not right after the barrier, where all waves would queue their copies at once
+        issue(t + kSseStages);     // into the slot tile t vacated (tiles past the end hold clamped rows, never used)
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    if (!COLMAX) {
+      acc[HT - 1] += held_back;
+      bool over = false;
+#pragma unroll
+      for (int ht = 0; ht < HT; ++ht) over = over || !(acc[ht] <= kSseMaxTileSum);
+      if (__builtin_amdgcn_ballot_w64(over) != 0) {  // a tile outgrew the maximum (or met a NaN)
+#pragma unroll
+        for (int ht = 0; ht < HT; ++ht) {
+          const float m_new = fmaxf(m_run[ht], ceilf(tile_max(s_cur[ht]) * sc));  // sc > 0
+          l_run[ht] *= __builtin_amdgcn_exp2f(m_run[ht] - m_new);
+          m_run[ht] = m_new;
+          acc[ht] = 0.f;
 #pragma unroll
           for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-              if (row0 + 32 * rb + 8 * (r >> 2) + 4 * g + (r & 3) >= L) s[ht][rb][r] = -INFINITY;
+            for (int r = 0; r < 16; ++r) acc[ht] += __builtin_amdgcn_exp2f(fmaf(s_cur[ht][rb][r], sc, -m_new));
         }
-        float tmax = s[ht][0][0];
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[ht][rb][r]);
-        const float m_new = fmaxf(m_run[ht], tmax * sc);  // sc > 0
-        float sum = 0.f;
-#pragma unroll
-        for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) sum += __builtin_amdgcn_exp2f(fmaf(s[ht][rb][r], sc, -m_new));
-        // a ragged tail can leave this half of the lanes without a real key: then everything is -inf and nothing
-        // may change
-        l_run[ht] = (m_new == -INFINITY) ? 0.f : fmaf(l_run[ht], __builtin_amdgcn_exp2f(m_run[ht] - m_new), sum);
-        m_run[ht] = m_new;
       }
+#pragma unroll
+      for (int ht = 0; ht < HT; ++ht) l_run[ht] += acc[ht];
     } else {
-      // ---- z - c per element, maxima by block relation of the query (row) to this lane's key
-      const __attribute__((address_space(3))) f32x4* cq =
-          (const __attribute__((address_space(3))) f32x4*)(c_ring + (t % kSseStages) * (kSseTile * 4));
-#pragma unroll
-      for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          const f32x4 cv = cq[(32 * rb + 8 * q4 + 4 * g) >> 2];
-#pragma unroll
-          for (int ht = 0; ht < HT; ++ht)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) s[ht][rb][4 * q4 + e] = fmaf(s[ht][rb][4 * q4 + e], sc, -cv[e]);
-        }
-      const int row1 = row0 + kSseTile;  // one past the tile's last query
+      const int row0 = t * kSseTile, row1 = row0 + kSseTile;           // one past the tile's last query
       const bool all_up = row1 <= w_lo_min;                            // every query in an earlier block than every key
       const bool all_low = row0 >= w_hi_max && row1 <= L;              // ... in a later block
       const bool all_diag = row0 >= w_lo_max && row1 <= w_hi_min && row1 <= L;
       if (all_up || all_diag || all_low) {  // wave-uniform
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) {
-          float tmax = s[ht][0][0];
-#pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) tmax = fmaxf(tmax, s[ht][rb][r]);
-          if (all_up) mx_up[ht] = fmaxf(mx_up[ht], tmax);
-          else if (all_diag) mx_diag[ht] = fmaxf(mx_diag[ht], tmax);
-          else mx_low[ht] = fmaxf(mx_low[ht], tmax);
+          if (all_up) mx_up[ht] = fmaxf(mx_up[ht], acc[ht]);
+          else if (all_diag) mx_diag[ht] = fmaxf(mx_diag[ht], acc[ht]);
+          else mx_low[ht] = fmaxf(mx_low[ht], acc[ht]);
         }
       } else {  // a tile that straddles a block boundary of some key of this wave, or the ragged last tile
 #pragma unroll
@@ -257,7 +304,7 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
               const int i = row0 + 32 * rb + 8 * (r >> 2) + 4 * g + (r & 3);
-              const float v = i < L ? s[ht][rb][r] : -INFINITY;
+              const float v = i < L ? s_cur[ht][rb][r] : -INFINITY;
               mx_up[ht] = fmaxf(mx_up[ht], i < my_lo ? v : -INFINITY);
               mx_diag[ht] = fmaxf(mx_diag[ht], (i >= my_lo && i < my_hi) ? v : -INFINITY);
               mx_low[ht] = fmaxf(mx_low[ht], i >= my_hi ? v : -INFINITY);
@@ -265,9 +312,55 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
         }
       }
     }
-    // tile t+1 must have landed before the next step; the loads of tiles t+2, t+3 may stay in flight
-    wait_vmcnt<2 * LOADS>();
-    __builtin_amdgcn_s_barrier();
+    if (MM) {
+      // tile t+2 must have landed before the next step; the loads of tiles t+3, t+4 may stay in flight
+      wait_vmcnt<2 * LOADS>();
+      __builtin_amdgcn_s_barrier();
+    }
+  };
+
+#pragma unroll
+  for (int u = 0; u < kSseStages; ++u) issue(u);
+  wait_vmcnt<0>();
+  __builtin_amdgcn_s_barrier();
+  f32x16 s_a[HT][2], s_b[HT][2];
+#pragma unroll
+  for (int ht = 0; ht < HT; ++ht)
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) s_a[ht][rb][r] = 0.f;
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) {
+      const bf16x8 a = *(const __attribute__((address_space(3))) bf16x8*)(ring + a_off + rb * 32 * ROWB + (((2 * kk) ^ kx2) << 4));
+#pragma unroll
+      for (int ht = 0; ht < HT; ++ht) s_a[ht][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hf[ht][kk], s_a[ht][rb], 0, 0, 0);
+    }
+  if (!COLMAX) {  // the running maximum starts with that of the first tile
+    if (kSseTile > L) mask_tail(s_a, 0);
+#pragma unroll
+    for (int ht = 0; ht < HT; ++ht) m_run[ht] = fmaxf(m_run[ht], ceilf(tile_max(s_a[ht]) * sc));
+  }
+  // step 0 refills the slot of tile 0: every wave must have its fragments in registers by then
+  __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+
+  int t = 0;
+#pragma unroll 1
+  for (; t + 2 < n_tiles; t += 2) {
+    step(std::true_type{}, t, s_a, s_b);
+    step(std::true_type{}, t + 1, s_b, s_a);
+  }
+  // one or two tiles are left
+  if (t + 1 < n_tiles) {
+    step(std::true_type{}, t, s_a, s_b);
+    if (!COLMAX && (t + 2) * kSseTile > L) mask_tail(s_b, (t + 1) * kSseTile);
+    step(std::false_type{}, t + 1, s_b, s_a);
+  } else {
+    if (!COLMAX && (t + 1) * kSseTile > L) mask_tail(s_a, t * kSseTile);
+    step(std::false_type{}, t, s_a, s_b);
   }
   wait_vmcnt<0>();  // nothing may still be writing this workgroup's LDS when it retires
 
@@ -279,7 +372,9 @@ __global__ __launch_bounds__(kSseThreads, HT == 1 ? 2 : 1) void sse_pass_kernel(
       const float m_o = other_half(m_run[ht], g), l_o = other_half(l_run[ht], g);
       const float m = fmaxf(m_run[ht], m_o);
       const float l = l_run[ht] * __builtin_amdgcn_exp2f(m_run[ht] - m) + l_o * __builtin_amdgcn_exp2f(m_o - m);
-      if (g == 0 && my_row < L) p.c[(long long)h * L + my_row] = m + __builtin_amdgcn_logf(l);  // v_log_f32 = log2
+      // l = 2^e x with x in [0.5, 1): m + e is exact (both are whole), so only log2 x and one addition round
+      const float me = m + (float)__builtin_amdgcn_frexp_expf(l);
+      if (g == 0 && my_row < L) p.c[(long long)h * L + my_row] = me + __builtin_amdgcn_logf(__builtin_amdgcn_frexp_mantf(l));
     } else {
       const float lo = half_swap_max(mx_low[ht]), di = half_swap_max(mx_diag[ht]), up = half_swap_max(mx_up[ht]);
       if (g == 0 && my_row < L) {
@@ -313,18 +408,25 @@ __global__ void sse_combine_kernel(const float* __restrict__ part, int L, int N,
   out[j] = acc / (float)parts;
 }
 
-template <int D, bool COLMAX>
-int launch_pass(hipStream_t st, const SseParams& p) {
-  // One 32-row group per wave and two workgroups per CU.  Two groups per wave (half the LDS reads per matrix
-  // instruction, one workgroup per CU) measured the same: LDS read bandwidth is not what bounds the passes.
-  constexpr int HT = 1;
+template <int D, bool COLMAX, int HT>
+int launch_pass_held(hipStream_t st, const SseParams& p, long long grid) {
   static LdsLimit lds_limit;
   const int rc = set_lds_limit(lds_limit, sse_pass_kernel<D, COLMAX, HT>, sse_lds_bytes(D));
   if (rc != PAFU_OK) return rc;
-  constexpr int HELD = kSseWaves * 32 * HT;
-  const int grid = ((p.L + HELD - 1) / HELD) * p.N;
-  hipLaunchKernelGGL((sse_pass_kernel<D, COLMAX, HT>), dim3(grid), dim3(kSseThreads), sse_lds_bytes(D), st, p);
+  hipLaunchKernelGGL((sse_pass_kernel<D, COLMAX, HT>), dim3((unsigned)grid), dim3(kSseThreads), sse_lds_bytes(D), st, p);
   return check_launch();
+}
+
+template <int D, bool COLMAX>
+int launch_pass(hipStream_t st, const SseParams& p) {
+  const long long grid1 = (long long)((p.L + 255) / 256) * p.N, grid2 = (long long)((p.L + 511) / 512) * p.N;
+  const long long cus = compute_units();
+  // A round of 512-row items takes 1.8 times as long as one of 256-row items (one workgroup per CU either way; one
+  // fragment read from LDS feeds two matrix instructions instead of one), so the larger ones pay unless they leave more of
+  // their last round idle.  256 / 512 rows, 12 heads of 128: 32760 tokens 5897 / 5303 us (6 and 3 rounds), 21000: 2506 /
+  // 2266 (4, 2), 11000: 896 / 1023 (3, 2), 3000: 115 / 171 (1, 1).
+  const long long cost1 = 10 * ((grid1 + cus - 1) / cus), cost2 = 18 * ((grid2 + cus - 1) / cus);
+  return cost1 < cost2 ? launch_pass_held<D, COLMAX, 1>(st, p, grid1) : launch_pass_held<D, COLMAX, 2>(st, p, grid2);
 }
 
 }  // namespace

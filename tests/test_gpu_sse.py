@@ -72,6 +72,22 @@ def test_sse_matches_oracle(L, N, D, L_B, gain):
     assert want.max() > 5e-3           # the scores are not all negligible
 
 
+@pytest.mark.parametrize("L,N,D,L_B,ramp", [
+    (513, 128, 64, 130, 0.0),     # 512-row items (two rounds of 256-row ones), one row in the last; odd number of tiles
+    (513, 128, 128, 513, 0.0),
+    (640, 128, 128, 200, 12.0),   # scores that grow along the keys: the reference of the sums is raised again and again
+    (640, 2, 64, 200, 12.0),      # ... with 256-row items
+])
+def test_sse_item_sizes_and_growing_scores(L, N, D, L_B, ramp):
+    """Same bound as above.  With a ramp the largest |z| is about 13 * 5 * log2(e) < 2^7 (five standard deviations), which
+    fp32 holds to 2^-17: 1e-5 relative in the weight, far inside it."""
+    Q, K = _qk(L, N, D, seed=L + L_B)
+    K = wl.round_to_bf16(K * (1.0 + ramp * np.arange(L, dtype=np.float32)[:, None, None] / np.float32(L)))
+    got = _run(Q, K, L_B)
+    want = orc.sse_score(Q, K, L_B)
+    assert np.all(np.abs(got - want) <= RTOL * np.abs(want) + ATOL), np.abs(got - want).max()
+
+
 def test_sse_strided_inputs_and_explicit_scale():
     Q, K = _qk(400, 2, 128, seed=9)
     got = _run(Q, K, 100, scale=0.05, pad=24)
