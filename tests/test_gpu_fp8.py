@@ -42,6 +42,31 @@ def test_quantize_matches_the_oracle_bit_for_bit():
             assert torch.all(slab[0] == 0xAB) and torch.all(slab[-1] == 0xAB) and torch.all(slab[:, N * D:] == 0xAB)
 
 
+@pytest.mark.parametrize("rows,N,D,ek,ev", [
+    (128, 4, 128, 0, 0),          # every bf16 value, as K and (in another order) as V
+    (128, 4, 128, -5, -6),
+    (128, 4, 128, 30, -64),       # deep in the subnormals; everything saturates
+    (13, 1, 16, 0, 0),            # rows of two 8-element chunks
+    (9001, 5, 64, -2, 3),         # rows that the grid's stride does not divide
+])
+def test_quantize_every_value_and_row_size(rows, N, D, ek, ev):
+    bits = (np.arange(rows * N * D, dtype=np.uint64) % 65536).astype(np.uint32).reshape(rows, N * D)
+    Kh = (bits << 16).view(np.float32)
+    Vh = Kh[::-1, ::-1].copy()
+    back = lambda a: torch.from_numpy((a.view(np.uint32) >> 16).astype(np.uint16).view(np.int16)).to(DEV).view(torch.bfloat16)
+    Kq, Vq = (torch.full((rows, N * D), 0xAB, dtype=torch.uint8, device=DEV) for _ in range(2))
+    B.pafu_quantize_kv(back(Kh).view(rows, N, D), back(Vh).view(rows, N, D), ek, ev, Kq, Vq)
+    Kb, Vb = (torch.zeros(rows, N, D, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+    B.pafu_dequantize_kv(Kq, Vq, ek, ev, Kb, Vb)
+    torch.cuda.synchronize()
+    with np.errstate(invalid="ignore", over="ignore"):
+        for got, wide, x, e in ((Kq, Kb, Kh, ek), (Vq, Vb, Vh, ev)):
+            want = orc.quantise_e4m3(x, e)
+            assert np.array_equal(got.cpu().numpy(), want)
+            want = orc.dequantise_e4m3(want, e).reshape(rows, N, D)
+            assert np.array_equal(host(wide).astype(np.float64), want, equal_nan=True)
+
+
 def test_dequantize_is_exact_for_every_code():
     codes = np.tile(np.arange(256, dtype=np.uint8), (4, 1))           # [4, 256] = N * D with N = 2, D = 128
     for ek, ev in ((0, 0), (-7, 5), (-30, 30)):
