@@ -309,48 +309,6 @@ int check_step(const pafu_step_args* a) {
   return check_step_alias(a, true);
 }
 
-// The scoring part of a step: SINGLE scores cache + chunk into a->scores, ROLLOUT the chunk into SL_out behind the
-// retained rows.
-// `selected` (may be null): in ROLLOUT the selection reads the stored list only, so it may ride in the scoring launch;
-// set when it did and the caller has no selection left to launch.
-int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nullptr) {
-  if (selected != nullptr) *selected = false;
-  const int n_kept = a->k < a->n ? a->k : a->n;
-  const bool single = a->mode == PAFU_MODE_SINGLE;
-  int rc = record_stage(st, a, 0);
-  if (rc) return rc;
-  float* chunk_scores = single ? a->scores + a->n : a->SL_out + n_kept;
-  if (single && a->n > 0) {
-    // cache and chunk features that sit back to back are scored in one launch
-    const int eb = dtype_bytes(a->x_dtype);
-    bool contiguous = true;
-    for (int s = 0; s < a->n_seg; ++s)
-      contiguous = contiguous && static_cast<const char*>(a->x_chunk[s]) ==
-                                     static_cast<const char*>(a->x_cache[s]) + (long long)a->n * a->ld_x * eb;
-    if (contiguous) {
-      rc = launch_score(st, a->x_cache[0], a->x_cache[1], a->x_cache[2], a->n_seg, a->n + a->Lc, a->Fs, a->ld_x,
-                        a->x_dtype, a->W1, a->b1, a->W2, a->b2, a->M, a->n_out, a->act, a->scores, a->workspace);
-      if (rc) return rc;
-    } else {
-      rc = launch_score(st, a->x_cache[0], a->x_cache[1], a->x_cache[2], a->n_seg, a->n, a->Fs, a->ld_x, a->x_dtype,
-                        a->W1, a->b1, a->W2, a->b2, a->M, a->n_out, a->act, a->scores, a->workspace);
-      if (rc) return rc;
-      rc = launch_score(st, a->x_chunk[0], a->x_chunk[1], a->x_chunk[2], a->n_seg, a->Lc, a->Fs, a->ld_x, a->x_dtype,
-                        a->W1, a->b1, a->W2, a->b2, a->M, a->n_out, a->act, chunk_scores, a->workspace);
-      if (rc) return rc;
-    }
-  } else {
-    // SINGLE with an empty cache, or ROLLOUT (the chunk's scores land behind the retained ones in SL_out)
-    const SelectJob job{a->SL_in, a->ids, nullptr, a->n, a->k, a->n_pinned};
-    const bool may_ride = selected != nullptr && !single && a->n > 0;
-    rc = launch_score(st, a->x_chunk[0], a->x_chunk[1], a->x_chunk[2], a->n_seg, a->Lc, a->Fs, a->ld_x, a->x_dtype,
-                      a->W1, a->b1, a->W2, a->b2, a->M, a->n_out, a->act, chunk_scores, a->workspace,
-                      may_ride ? &job : nullptr, selected);
-    if (rc) return rc;
-  }
-  return record_stage(st, a, 1);
-}
-
 // The part of a layer's workspace that the attention launch may use: what lies behind the scoring part.
 struct WsPart {
   void* p;
@@ -360,6 +318,91 @@ WsPart attention_ws(const pafu_step_args* a, bool scoring) {
   const size_t used = scoring ? step_score_workspace(a) : 0;
   if (a->workspace == nullptr || a->workspace_bytes <= used) return WsPart{nullptr, 0};
   return WsPart{static_cast<char*>(a->workspace) + used, a->workspace_bytes - used};
+}
+
+// The scoring part of a step: SINGLE scores cache + chunk into a->scores, ROLLOUT the chunk into SL_out behind the
+// retained rows.  Both read the head's weights; the attention's part of the workspace, idle until then, is the scratch.
+ScoreShape score_shape(const pafu_step_args* a, int T) {
+  return ScoreShape{a->n_seg, T, a->Fs, a->ld_x, a->x_dtype, a->M, a->n_out, a->act, a->mode == PAFU_MODE_SINGLE};
+}
+ScoreLayer score_layer(const pafu_step_args* a, const void* const* x, float* out) {
+  return ScoreLayer{{x[0], x[1], x[2]}, a->W1, a->b1, a->W2, a->b2, out};
+}
+// One launch scores everything a step scores: the chunk alone, or cache and chunk features that sit back to back.
+bool scores_in_one_launch(const pafu_step_args* a) {
+  if (a->mode != PAFU_MODE_SINGLE || a->n <= 0) return true;
+  const int eb = dtype_bytes(a->x_dtype);
+  bool contiguous = true;
+  for (int s = 0; s < a->n_seg; ++s)
+    contiguous = contiguous && static_cast<const char*>(a->x_chunk[s]) ==
+                                   static_cast<const char*>(a->x_cache[s]) + (long long)a->n * a->ld_x * eb;
+  return contiguous;
+}
+// ... its tokens and tensors
+int one_launch_tokens(const pafu_step_args* a) { return a->mode == PAFU_MODE_SINGLE && a->n > 0 ? a->n + a->Lc : a->Lc; }
+ScoreLayer one_launch_layer(const pafu_step_args* a) {
+  const bool single = a->mode == PAFU_MODE_SINGLE;
+  if (single && a->n > 0) return score_layer(a, a->x_cache, a->scores);
+  return score_layer(a, a->x_chunk, single ? a->scores + a->n : a->SL_out + (a->k < a->n ? a->k : a->n));
+}
+
+// `selected` (may be null): in ROLLOUT the selection reads the stored list only, so it may ride in the scoring launch;
+// set when it did and the caller has no selection left to launch.
+int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nullptr) {
+  if (selected != nullptr) *selected = false;
+  int rc = record_stage(st, a, 0);
+  if (rc) return rc;
+  const WsPart scratch = attention_ws(a, true);
+  if (scores_in_one_launch(a)) {
+    const SelectJob job{a->SL_in, a->ids, nullptr, a->n, a->k, a->n_pinned};
+    const bool may_ride = selected != nullptr && a->mode != PAFU_MODE_SINGLE && a->n > 0;
+    const ScoreLayer layer = one_launch_layer(a);
+    rc = launch_score(st, score_shape(a, one_launch_tokens(a)), &layer, 1, a->workspace, scratch.p, scratch.bytes,
+                      may_ride ? &job : nullptr, selected);
+    if (rc) return rc;
+  } else {
+    const ScoreLayer cache = score_layer(a, a->x_cache, a->scores), chunk = score_layer(a, a->x_chunk, a->scores + a->n);
+    rc = launch_score(st, score_shape(a, a->n), &cache, 1, a->workspace, scratch.p, scratch.bytes);
+    if (rc) return rc;
+    rc = launch_score(st, score_shape(a, a->Lc), &chunk, 1, a->workspace, scratch.p, scratch.bytes);
+    if (rc) return rc;
+  }
+  return record_stage(st, a, 1);
+}
+
+// Can the scoring of these two layers share a launch?  (One workspace: what it may overlap is checked within its layer.)
+bool same_scoring(const pafu_step_args* a, const pafu_step_args* b) {
+  return a->mode == b->mode && a->workspace == b->workspace && a->workspace_bytes == b->workspace_bytes &&
+         scores_in_one_launch(b) && one_launch_tokens(a) == one_launch_tokens(b) && a->n_seg == b->n_seg &&
+         a->Fs == b->Fs && a->ld_x == b->ld_x && a->x_dtype == b->x_dtype && a->M == b->M && a->n_out == b->n_out &&
+         a->act == b->act;
+}
+
+// The scores of the layers of a multi-layer step: one launch for every stretch of layers with the same geometry.
+int enqueue_layers_scores(hipStream_t st, const pafu_step_args* args, int n_layers) {
+  int rc;
+  for (int first = 0, last; first < n_layers; first = last) {
+    const pafu_step_args* a = &args[first];
+    const ScoreShape shape = score_shape(a, one_launch_tokens(a));
+    last = first + 1;
+    if (scores_in_one_launch(a) && score_batchable(shape))
+      while (last < n_layers && last - first < kScoreBatchMax && same_scoring(a, &args[last])) ++last;
+    if (last == first + 1) {
+      if ((rc = enqueue_scores(st, a))) return rc;
+      continue;
+    }
+    ScoreLayer layers[kScoreBatchMax];
+    const WsPart scratch = attention_ws(a, true);
+    for (int l = first; l < last; ++l) {
+      layers[l - first] = one_launch_layer(&args[l]);
+      if ((rc = record_stage(st, &args[l], 0))) return rc;
+    }
+    rc = launch_score(st, shape, layers, last - first, nullptr, scratch.p, scratch.bytes);
+    if (rc) return rc;
+    for (int l = first; l < last; ++l)
+      if ((rc = record_stage(st, &args[l], 1))) return rc;
+  }
+  return PAFU_OK;
 }
 
 // The cache part of a step for one layer comes in three pieces, so that the middle one may serve several layers:
@@ -457,9 +500,12 @@ bool same_attention(const pafu_step_args* a, const pafu_step_args* b) {
 // list serve all of them, and whose workspace a layer without one borrows.
 int enqueue_layers_kv(hipStream_t st, const pafu_step_args* args, int n_layers, int index_layer, int done_batch) {
   const pafu_step_args* idx = index_layer >= 0 ? &args[index_layer] : nullptr;
+  // (layers that bring different workspaces stay apart: what a workspace may overlap is only checked within its layer)
+  auto ws_of = [&](const pafu_step_args* a) { return a->workspace == nullptr && idx != nullptr ? idx->workspace : a->workspace; };
   int rc;
   for (int first = 0, last; first < n_layers; first = last) {
-    for (last = first + 1; last < n_layers && last - first < kAttnBatchMax && same_attention(&args[first], &args[last]);)
+    for (last = first + 1; last < n_layers && last - first < kAttnBatchMax && same_attention(&args[first], &args[last]) &&
+                           ws_of(&args[first]) == ws_of(&args[last]);)
       ++last;
     int done[kAttnBatchMax];
     WsPart ws{nullptr, 0};
@@ -598,8 +644,9 @@ int pafu_score(void* stream, const void* x0, const void* x1, const void* x2, int
                int act, float* out, void* workspace, size_t workspace_bytes) {
   int rc = check_score(x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, W2, M, n_out, act, out, workspace, workspace_bytes);
   if (rc) return rc;
-  return launch_score(static_cast<hipStream_t>(stream), x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, b1, W2, b2, M,
-                      n_out, act, out, workspace);
+  const ScoreLayer layer{{x0, x1, x2}, W1, b1, W2, b2, out};
+  return launch_score(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act, true}, &layer, 1,
+                      workspace);
 }
 
 int pafu_score_static(void* stream, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,
@@ -609,8 +656,8 @@ int pafu_score_static(void* stream, const void* x0, const void* x1, const void* 
   int rc = check_score(x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, W2, M, n_out, act, out, nullptr, SIZE_MAX);
   if (rc) return rc;
   if (M > PAFU_SCORE_STATIC_MAX_M) return PAFU_ERR_WORKSPACE;
-  return launch_score_static(static_cast<hipStream_t>(stream), x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, b1, W2, b2,
-                             M, n_out, act, out);
+  const ScoreLayer layer{{x0, x1, x2}, W1, b1, W2, b2, out};
+  return launch_score_static(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act, true}, layer);
 }
 
 size_t pafu_select_workspace_bytes(int n) {
@@ -785,8 +832,8 @@ int pafu_step_layers(void* stream, const pafu_step_args* args, int n_layers) {
   // in one launch (a selection occupies a single CU; one per layer in a row would leave the chip idle 30 times), then
   // the compactions and the attention, each in one launch where the layers share a geometry.
   hipStream_t st = static_cast<hipStream_t>(stream);
-  for (int l = 0; l < n_layers; ++l) {
-    int rc = enqueue_scores(st, &args[l]);
+  {
+    int rc = enqueue_layers_scores(st, args, n_layers);
     if (rc) return rc;
   }
   for (int first = 0; first < n_layers; first += kSelectBatchMax) {

@@ -92,17 +92,36 @@ constexpr int kSelectBatchMax = 32;  // lists per launch (the jobs travel as ker
 int launch_select_batch(hipStream_t st, const SelectJob* jobs, int count);
 int launch_select(hipStream_t st, const float* scores, int n, int k, int n_pinned, int* out_ids, int* out_count,
                   void* ws);
-int launch_score(hipStream_t st, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,
-                 long long ld_x, int x_dtype, const void* W1, const float* b1, const float* W2, const float* b2,
-                 int M, int n_out, int act, float* out, void* ws, const SelectJob* ride = nullptr,
-                 bool* rode = nullptr);
+// Scoring.  A shape is what the layers of one launch share; the tensors are a layer's own.
+struct ScoreShape {
+  int n_seg, T, Fs;
+  long long ld_x;
+  int x_dtype, M, n_out, act;
+  // The scores decide a selection in the same call, or are the call's result: a token's sums are then formed in one order
+  // whatever the launch looks like, so that two close scores never change places.  Otherwise (the chunk of a rollout) the
+  // units may be summed in other groups.
+  bool keep_order;
+};
+struct ScoreLayer {
+  const void* x[3];
+  const void* W1;
+  const float *b1, *W2, *b2;
+  float* out;
+};
+constexpr int kScoreBatchMax = 32;  // layers per launch (they travel as kernel arguments)
+constexpr int kScoreSplitMax = 8;   // most workgroups that share the hidden units of a token group
+constexpr int kScoreFoldMax = 16;   // most output rows of the second layer that the streaming kernel averages itself
+// Can several layers of this shape go in one launch?
+bool score_batchable(const ScoreShape& s);
+// fold_ws: the score workspace (one layer, n_out > 1).  scratch (may be null): with n_layers * kScoreSplitMax * T floats
+// the hidden units of a token group may be shared by several workgroups.
 // `ride`: a selection that does not depend on these scores (the stored list of a rollout step); when the launch is a
-// short streaming one it is done by one extra workgroup of the same launch and *rode is set, otherwise the caller
+// streaming one with a CU to spare it is done by one extra workgroup of the same launch and *rode is set, otherwise the caller
 // launches it.
+int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, int n_layers, void* fold_ws,
+                 void* scratch = nullptr, size_t scratch_bytes = 0, const SelectJob* ride = nullptr, bool* rode = nullptr);
 // The same with the folded second layer in the library's own static device array (no workspace, no allocation).
-int launch_score_static(hipStream_t st, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,
-                        long long ld_x, int x_dtype, const void* W1, const float* b1, const float* W2,
-                        const float* b2, int M, int n_out, int act, float* out);
+int launch_score_static(hipStream_t st, const ScoreShape& s, const ScoreLayer& layer);
 size_t sse_workspace_bytes(int L, int N);
 int launch_sse(hipStream_t st, const void* Q, const void* K, int L, int N, int D, long long ld_q, long long ld_k,
                int block_len, float scale, float* out, void* workspace);

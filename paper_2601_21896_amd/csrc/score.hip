@@ -1,23 +1,23 @@
 // Salience Estimation Head (S-MLP) forward: s[t] = mean_o( W2 . act(W1 . x[t] + b1) + b2 ).
 // App. A "S-MLP" and Sec. 3.3-3.4 of the paper (two linear layers, SiLU in between, mean over outputs).
 //
-// The mean over the outputs of a linear layer is a linear layer with the averaged weight row, so a
-// tiny pre-kernel folds W2/b2 into one row w2bar[M] and a scalar (skipped when n_out == 1); the main
-// kernel then fuses layer 1, the activation, the dot with w2bar and the bias into one pass over X.
+// The mean over the outputs of a linear layer is a linear layer with the averaged weight row: the tiled kernels average a
+// few rows of W2/b2 themselves, for many rows a tiny pre-kernel folds them into one row w2bar[M] and a scalar; layer 1,
+// the activation, the dot with the averaged row and the bias are one pass over X.
 //
 // bf16 paths: layer 1 is a skinny dense contraction [M x F] . [F x T], so it runs on the matrix cores
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulate).  H = W1.X is produced as H^T tiles (rows = hidden units,
 // columns = tokens), so one lane holds 16 hidden units of ONE token per tile and the reduction over hidden
 // units is almost entirely in-register.
-//  - score_stream_kernel (M a multiple of 256): the measured path.  W1 and the features both stream
-//    global -> LDS through a ring of 64-feature slabs; a workgroup owns several 32-token tiles so that one W1
-//    fragment feeds several matrix instructions.  Described in detail above the kernel.
+//  - score_stream_kernel (M a multiple of 128, or of 256 where a selection follows from the scores): the measured path.
+//    W1 and the features both stream global -> LDS through a ring of 64-feature slabs; a workgroup owns several 32-token
+//    tiles so that one W1 fragment feeds several matrix instructions.  Described in detail above the kernel.
 //    In a rollout step one extra workgroup of this launch runs the top-k selection on the stored score list
 //    (select_body.h), which does not depend on the chunk's scores (Alg. 2: Top-k before the chunk is appended).
-//  - score_mfma_kernel (other M a multiple of 32): a wave owns 32 tokens and loads their feature rows straight
+//  - score_mfma_kernel (M a multiple of 32): a wave owns 32 tokens and loads their feature rows straight
 //    into B-operand registers; W1 is staged through LDS in 64-feature slabs shared by the waves of a workgroup.
 //
-// generic path (fp32 inputs, or shapes the tiles do not divide): plain fp32 FMAs.
+// fp32 inputs, or shapes the tiles do not divide: plain fp32 FMAs, through LDS tiles where rows are whole 16-byte chunks.
 #include "pafu_internal.h"
 #include "select_body.h"
 
@@ -50,6 +50,48 @@ __global__ void fold_w2_kernel(const float* __restrict__ W2, const float* __rest
       for (int o = 0; o < n_out; ++o) s += b2[o];
     w2bar[M] = s * inv;
   }
+}
+
+// What a launch of the tiled kernels scores: up to kScoreBatchMax layers of one geometry.
+struct ScoreArgs {
+  int T, Fs, F;
+  long long ld_x;
+  int M, act;
+  int n_out;    // rows of W2 / b2 that the kernel averages itself (1: W2 / b2 are one row, folded or as given)
+  int groups;   // token groups of a layer
+  int splits;   // workgroups that share the hidden units of one token group; above 1 they write partial sums
+  float* part;  // [layer][split][T] partial sums, added up by score_sum_kernel
+  SelectJob ride;
+  ScoreLayer layer[kScoreBatchMax];
+};
+
+// averaged second layer of 4 hidden units from m on, in the order of fold_w2_kernel
+__device__ __forceinline__ float4 folded_w2(const float* __restrict__ W2, int M, int n_out, int m) {
+  if (n_out == 1) return *reinterpret_cast<const float4*>(W2 + m);
+  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int o = 0; o < n_out; ++o) {
+    const float4 w = *reinterpret_cast<const float4*>(W2 + (long long)o * M + m);
+    s.x += w.x; s.y += w.y; s.z += w.z; s.w += w.w;
+  }
+  const float inv = 1.0f / (float)n_out;
+  return make_float4(s.x * inv, s.y * inv, s.z * inv, s.w * inv);
+}
+__device__ __forceinline__ float folded_b2(const float* __restrict__ b2, int n_out) {
+  if (b2 == nullptr) return 0.f;
+  float s = 0.f;
+  for (int o = 0; o < n_out; ++o) s += b2[o];
+  return s * (1.0f / (float)n_out);
+}
+
+// out[t] = b2 + the partial sums of the token's splits, in order
+__global__ void score_sum_kernel(ScoreArgs a) {
+  const int t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= a.T) return;
+  const ScoreLayer& L = a.layer[blockIdx.y];
+  const float* p = a.part + (long long)blockIdx.y * a.splits * a.T + t;
+  float v = folded_b2(L.b2, a.n_out);
+  for (int i = 0; i < a.splits; ++i) v += p[(long long)i * a.T];
+  L.out[t] = v;
 }
 
 // ---------------------------------------------------------------------------------- generic path
@@ -96,6 +138,103 @@ __global__ __launch_bounds__(256) void score_generic_kernel(const void* x0, cons
   if (ml == 0 && t < T) out[t] = partial + (b2bar ? *b2bar : 0.f);
 }
 
+// The same for fp32 inputs whose rows are whole 16-byte chunks, with the same operations in the same order (a selection may
+// follow from these scores, so two scores that are close must not change places): the features of 16 tokens and the
+// weights of 32 hidden units go through LDS in pieces of 128 features, the next piece in flight meanwhile, instead of being
+// read element by element.  A step of a small model is a chain of latencies: 320 tokens, 128 features and 32 units take
+// 6.3 us (12.3 element by element), 1800 tokens, 256 features and 64 units 14.3 (37).
+constexpr int kSfPiece = 128;            // features per piece
+constexpr int kSfRow = kSfPiece + 4;     // floats per LDS row: 16 consecutive rows start in distinct banks
+constexpr int kSfUnits = 32;
+__global__ __launch_bounds__(256) void score_f32_kernel(ScoreArgs A) {
+  __shared__ __attribute__((aligned(16))) float ws[kSfUnits * kSfRow], xs[16 * kSfRow];
+  const ScoreLayer& L = A.layer[blockIdx.y];
+  const int tid = threadIdx.x, tl = tid >> 4, ml = tid & 15;
+  const int t0 = blockIdx.x * 16, t = t0 + tl;
+  const int n_seg = A.F / A.Fs, pieces = (A.Fs + kSfPiece - 1) / kSfPiece;
+  const int col = (tid & 31) * 4, row = tid >> 5;  // this thread's 16 bytes of 8 rows at a time
+  float4 wr[kSfUnits / 8], xr[2];
+  auto fetch = [&](int m0, int i) {  // piece i of the units m0 ..; columns past the segment's end are not read
+    const int seg = i / pieces, f = (i - seg * pieces) * kSfPiece + col;
+    if (f >= A.Fs) return;
+    const float* xp = static_cast<const float*>(seg == 0 ? L.x[0] : (seg == 1 ? L.x[1] : L.x[2]));
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {
+      const int tt = t0 + row + 8 * j;
+      xr[j] = *reinterpret_cast<const float4*>(xp + (long long)(tt < A.T ? tt : A.T - 1) * A.ld_x + f);
+    }
+#pragma unroll
+    for (int j = 0; j < kSfUnits / 8; ++j) {
+      const int m = m0 + row + 8 * j;
+      wr[j] = *reinterpret_cast<const float4*>(static_cast<const float*>(L.W1) + (long long)(m < A.M ? m : A.M - 1) * A.F +
+                                               (long long)seg * A.Fs + f);
+    }
+  };
+#pragma unroll
+  for (int j = 0; j < kSfUnits / 8; ++j) wr[j] = make_float4(0.f, 0.f, 0.f, 0.f);
+  xr[0] = xr[1] = wr[0];
+  float partial = 0.f;
+  fetch(0, 0);
+  for (int m0 = 0; m0 < A.M; m0 += kSfUnits) {
+    float h[2], acc[2][4];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int m = m0 + ml + 16 * u;
+      h[u] = L.b1 != nullptr && m < A.M ? L.b1[m] : 0.f;
+      acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.f;
+    }
+    for (int i = 0; i < n_seg * pieces; ++i) {
+      __syncthreads();  // the previous piece has been used
+#pragma unroll
+      for (int j = 0; j < kSfUnits / 8; ++j) *reinterpret_cast<float4*>(ws + (row + 8 * j) * kSfRow + col) = wr[j];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) *reinterpret_cast<float4*>(xs + (row + 8 * j) * kSfRow + col) = xr[j];
+      __syncthreads();
+      if (i + 1 < n_seg * pieces) fetch(m0, i + 1);
+      else if (m0 + kSfUnits < A.M) fetch(m0 + kSfUnits, 0);
+      const int in_seg = i % pieces, width = A.Fs - in_seg * kSfPiece < kSfPiece ? A.Fs - in_seg * kSfPiece : kSfPiece;
+#pragma unroll 8
+      for (int f = 0; f < width; f += 4) {
+        const float4 x = *reinterpret_cast<const float4*>(xs + tl * kSfRow + f);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float4 w = *reinterpret_cast<const float4*>(ws + (ml + 16 * u) * kSfRow + f);
+          acc[u][0] = fmaf(w.x, x.x, acc[u][0]);
+          acc[u][1] = fmaf(w.y, x.y, acc[u][1]);
+          acc[u][2] = fmaf(w.z, x.z, acc[u][2]);
+          acc[u][3] = fmaf(w.w, x.w, acc[u][3]);
+        }
+      }
+      if (in_seg == pieces - 1) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          h[u] += (acc[u][0] + acc[u][1]) + (acc[u][2] + acc[u][3]);
+          acc[u][0] = acc[u][1] = acc[u][2] = acc[u][3] = 0.f;
+        }
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int m = m0 + ml + 16 * u;
+      if (m < A.M) {
+        float w2 = 0.f;
+        if (A.n_out == 1) {
+          w2 = L.W2[m];
+        } else {
+          for (int o = 0; o < A.n_out; ++o) w2 += L.W2[(long long)o * A.M + m];
+          w2 *= 1.0f / (float)A.n_out;
+        }
+        partial = fmaf(w2, act_accurate(h[u], A.act), partial);
+      }
+    }
+  }
+  partial += __shfl_xor(partial, 8);
+  partial += __shfl_xor(partial, 4);
+  partial += __shfl_xor(partial, 2);
+  partial += __shfl_xor(partial, 1);
+  if (ml == 0 && t < A.T) L.out[t] = partial + folded_b2(L.b2, A.n_out);
+}
+
 // ---------------------------------------------------------------------------------- MFMA path
 constexpr int kScThreads = 256;
 constexpr int kScTokPerWave = 32;
@@ -110,17 +249,17 @@ __device__ __forceinline__ float fast_silu(float h) {
   return h * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
-// MB = 32-row hidden blocks per pass over X (MB*32 hidden units are accumulated at once).
+// MB = 32-row hidden blocks per pass over X (MB*32 hidden units are accumulated at once); one layer per blockIdx.y.
 template <int MB>
-__global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(const unsigned short* __restrict__ x0,
-                                                                   const unsigned short* __restrict__ x1,
-                                                                   const unsigned short* __restrict__ x2, int T,
-                                                                   int Fs, int F, long long ld_x,
-                                                                   const unsigned short* __restrict__ W1,
-                                                                   const float* __restrict__ b1,
-                                                                   const float* __restrict__ w2bar,
-                                                                   const float* __restrict__ b2bar, int M, int act,
-                                                                   float* __restrict__ out) {
+__global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) {
+  const ScoreLayer& L = A.layer[blockIdx.y];
+  const unsigned short* const x0 = static_cast<const unsigned short*>(L.x[0]);
+  const unsigned short* const x1 = static_cast<const unsigned short*>(L.x[1]);
+  const unsigned short* const x2 = static_cast<const unsigned short*>(L.x[2]);
+  const unsigned short* const W1 = static_cast<const unsigned short*>(L.W1);
+  const float* const b1 = L.b1;
+  const int T = A.T, Fs = A.Fs, F = A.F, M = A.M, act = A.act;
+  const long long ld_x = A.ld_x;
   extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int g = lane >> 5, c = lane & 31;
@@ -194,7 +333,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(const unsigne
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int m0 = mp + 32 * b + 8 * q + 4 * g;
-          const float4 w = *reinterpret_cast<const float4*>(w2bar + m0);
+          const float4 w = folded_w2(L.W2, M, A.n_out, m0);
           float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
           if (b1 != nullptr) bb = *reinterpret_cast<const float4*>(b1 + m0);
           const float h0 = acc[b][4 * q + 0] + bb.x, h1 = acc[b][4 * q + 1] + bb.y;
@@ -217,32 +356,39 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(const unsigne
 #undef PAFU_LOAD_SLAB
 #undef PAFU_STORE_SLAB
   partial += __shfl_xor(partial, 32);
-  if (g == 0 && tok < T) out[tok] = partial + (b2bar ? *b2bar : 0.f);
+  if (g == 0 && tok < T) L.out[tok] = partial + folded_b2(L.b2, A.n_out);
 }
 
 // ---------------------------------------------------------------------------------- streaming MFMA path
-// For M % 256 == 0 and Fs % 64 == 0.  With a 256-wide hidden layer the head sits near the ridge of the roofline
+// For M % 128 == 0 and Fs % 64 == 0.  With a 256-wide hidden layer the head sits near the ridge of the roofline
 // (about 256 flop per byte of features), and every CU has to pull all of W1 through its L1 once per token group, so
 // the kernel must keep the matrix cores and the memory pipe busy at the same time: an even spread of MFMA work over
 // the 1024 SIMDs, few LDS bytes per MFMA, and many bytes in flight without spending registers on them.
 //  - A workgroup owns TT 32-token tiles (TT picked at launch so that the grid needs as few rounds over the 256 CUs
-//    as possible) and one 256-unit pass of the hidden layer at a time.  Its 8 waves split the hidden units four
-//    ways and the reduction axis two ways: wave (hq, kh) accumulates hidden units [64 hq, 64 hq + 64) for all TT
-//    tiles over half of the k-steps of every slab, so one W1 fragment feeds TT MFMAs and one feature fragment two.
+//    as possible) and one pass of 128 NB hidden units at a time.  Its 8 waves split the hidden units four
+//    ways and the reduction axis two ways: wave (hq, kh) accumulates NB 32-unit blocks for all TT
+//    tiles over half of the k-steps of every slab, so one W1 fragment feeds TT MFMAs and one feature fragment NB.
 //    The two reduction halves sit on the same SIMD (waves w and w + 4) and are added through LDS at the end of a pass.
 //  - W1 and the features stream global -> LDS with global_load_lds through a ring of slabs (no staging registers,
 //    all but one slab of the ring in flight), rows XOR-swizzled in 16-byte chunks for conflict-free b128 reads.
+//  - A CU takes in about 45 bytes per clock, and a slab's W1 part (32 KB at NB = 2) costs more than its TT feature tiles.
+//    A hidden layer of several passes is therefore shared by `splits` workgroups, which makes room for a larger TT: 4680
+//    tokens of 4608 features and 1024 units took 128 us with one token tile per workgroup and all four passes in it, and
+//    take 57 us with five tiles and an eighth of the units (10800 tokens, 5120 features, 512 units: 123 -> 80 us).  The
+//    partial sums go through scratch and one more small launch (5 us).
+//  - Layers of one geometry share a launch: the token groups of one (57 at 7210 tokens) leave most of the chip idle
+//    (six of 128 units: 6 x 12.9 us one by one, 26 us together, in the kernel above).
 constexpr int kS3Slab = 64;                      // features per slab (full 128-byte lines per row)
 constexpr int kS3RowB = kS3Slab * 2;             // bytes per slab row
 constexpr int kS3Chunks = kS3RowB / 16;          // 16-byte chunks per row
 constexpr int kS3RowsPerLoad = 1024 / kS3RowB;   // rows covered by one wave-wide 16-byte-per-lane load
 constexpr int kS3Stages = 3;                     // ring depth: 3 x (32 KB + 4 TT KB) <= 156 KB
-constexpr int kS3WBytes = 256 * kS3RowB;         // W1 part of a stage (256 hidden units)
+constexpr int s3_w_bytes(int NB) { return 128 * NB * kS3RowB; }  // W1 part of a stage (128 NB hidden units)
 constexpr int kS3MaxTT = 5;
 constexpr int kS3RedBytes = 65536;               // two 32 KB regions for the end-of-pass reduction
-constexpr int s3_stage_bytes(int TT) { return kS3WBytes + 32 * TT * kS3RowB; }
-constexpr int s3_lds_bytes(int TT) {
-  return kS3Stages * s3_stage_bytes(TT) > kS3RedBytes ? kS3Stages * s3_stage_bytes(TT) : kS3RedBytes;
+constexpr int s3_stage_bytes(int TT, int NB) { return s3_w_bytes(NB) + 32 * TT * kS3RowB; }
+constexpr int s3_lds_bytes(int TT, int NB) {
+  return kS3Stages * s3_stage_bytes(TT, NB) > kS3RedBytes ? kS3Stages * s3_stage_bytes(TT, NB) : kS3RedBytes;
 }
 // chunk q of row r lives in slot q ^ swz(r): 16 consecutive rows of one chunk then cover all 64 banks
 __device__ __forceinline__ int s3_swz(int row) {
@@ -265,20 +411,45 @@ __device__ __forceinline__ void s3_wait_vmcnt() {
 // threads) on a list that does not depend on this launch's scores: the stored score list of a rollout step.  A
 // selection keeps one CU busy for about as long as the scoring of a chunk takes the others, so carried along it
 // costs nothing, where a launch of its own would leave the rest of the chip idle meanwhile.
-template <int TT, int SELW>
-__global__ __launch_bounds__(512, 1) void score_stream_kernel(
-    const unsigned short* __restrict__ x0, const unsigned short* __restrict__ x1, const unsigned short* __restrict__ x2,
-    int T, int Fs, int F, long long ld_x, const unsigned short* __restrict__ W1, const float* __restrict__ b1,
-    const float* __restrict__ w2bar, const float* __restrict__ b2bar, int M, int act, float* __restrict__ out,
-    SelectJob ride) {
+template <int TT, int NB, int SELW>
+__global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
+  int id = blockIdx.x;
   if constexpr (SELW > 0) {
-    if (blockIdx.x == 0) {
-      select_bitslice_body<SELW, 512>(ride);
+    if (id == 0) {
+      select_bitslice_body<SELW, 512>(A.ride);
       return;
     }
+    --id;
   }
-  constexpr int kStageB = s3_stage_bytes(TT);
-  constexpr int WU = 256 / kS3RowsPerLoad;             // wave-wide loads that fill the W1 part of a stage
+  // Workgroups are handed to the 8 XCDs in turn: the splits of a token group are 8 apart, so that one L2 serves its
+  // features to all of them.
+  const int per_layer = A.groups * A.splits;
+  const int li = id / per_layer;
+  int group, split;
+  {
+    const int w = id - li * per_layer, band = 8 * A.splits, full = A.groups / 8 * 8;
+    if (w < full * A.splits) {
+      const int r = w % band;
+      group = w / band * 8 + r % 8;
+      split = r / 8;
+    } else {
+      const int r = w - full * A.splits, left = A.groups - full;
+      group = full + r % left;
+      split = r / left;
+    }
+  }
+  const ScoreLayer& L = A.layer[li];
+  const unsigned short* const x0 = static_cast<const unsigned short*>(L.x[0]);
+  const unsigned short* const x1 = static_cast<const unsigned short*>(L.x[1]);
+  const unsigned short* const x2 = static_cast<const unsigned short*>(L.x[2]);
+  const unsigned short* const W1 = static_cast<const unsigned short*>(L.W1);
+  const float* const b1 = L.b1;
+  const int T = A.T, Fs = A.Fs, F = A.F, act = A.act;
+  const long long ld_x = A.ld_x;
+  constexpr int MP = 128 * NB;                         // hidden units per pass
+  constexpr int kWBytes = s3_w_bytes(NB);
+  constexpr int kStageB = s3_stage_bytes(TT, NB);
+  constexpr int WU = MP / kS3RowsPerLoad;              // wave-wide loads that fill the W1 part of a stage
   constexpr int XU = 32 * TT / kS3RowsPerLoad;         // ... and the feature part
   constexpr int LW = WU / 8;                           // W1 loads per wave per slab
   constexpr int LX = (XU + 7) / 8;                     // feature loads per wave per slab
@@ -295,7 +466,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);  // said to be uniform: LDS addresses of the loads stay scalar
   const int hq = wave & 3, kh = wave >> 2;
   const int g = lane >> 5, c = lane & 31;
-  const int tok_base = (blockIdx.x - (SELW > 0 ? 1 : 0)) * (32 * TT);
+  const int tok_base = group * (32 * TT);
   const int n_slabs = F / kS3Slab;
   const int slabs_per_seg = Fs / kS3Slab;
 
@@ -326,13 +497,14 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) partial[tt] = 0.f;
 
+  const int m_share = A.M / A.splits;
 #pragma unroll 1
-  for (int mp = 0; mp < M; mp += 256) {
-    f32x16 acc[TT][2];
+  for (int mp = split * m_share; mp < (split + 1) * m_share; mp += MP) {
+    f32x16 acc[TT][NB];
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < NB; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[tt][b][r] = 0.f;
     const unsigned short* const w_pass = W1 + (long long)mp * F;  // uniform
@@ -351,23 +523,22 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
     const unsigned short* xs_ = seg_ == 0 ? x0 : (seg_ == 1 ? x1 : x2);                                         \
     _Pragma("unroll") for (int j = 0; j < LX; ++j)                                                              \
         s3_dma(xs_ + x_wg_off + fo_, x_off[j],                                                                  \
-               (unsigned)(uintptr_t)(st_ + kS3WBytes + ((wave + 8 * j) % XU) * 1024));                          \
+               (unsigned)(uintptr_t)(st_ + kWBytes + ((wave + 8 * j) % XU) * 1024));                          \
   } while (0)
 
     // Fragments of k-step j of a slab: two W1 blocks and TT feature tiles, into fragment set B (0 or 1).
 #define PAFU_S3_READ(B, ST, J)                                                                                  \
   do {                                                                                                          \
-    fw[B][0] = *(const lds_frag*)((ST) + (hq * 64) * kS3RowB + rd[J]);                                          \
-    fw[B][1] = *(const lds_frag*)((ST) + (hq * 64 + 32) * kS3RowB + rd[J]);                                     \
+    _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                           \
+        fw[B][nb] = *(const lds_frag*)((ST) + (hq * 32 * NB + 32 * nb) * kS3RowB + rd[J]);                      \
     _Pragma("unroll") for (int tt = 0; tt < TT; ++tt)                                                           \
-        fx[B][tt] = *(const lds_frag*)((ST) + kS3WBytes + tt * 32 * kS3RowB + rd[J]);                           \
+        fx[B][tt] = *(const lds_frag*)((ST) + kWBytes + tt * 32 * kS3RowB + rd[J]);                           \
   } while (0)
 #define PAFU_S3_MMA(B)                                                                                          \
   do {                                                                                                          \
-    _Pragma("unroll") for (int tt = 0; tt < TT; ++tt) {                                                         \
-      acc[tt][0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[B][0], fx[B][tt], acc[tt][0], 0, 0, 0);           \
-      acc[tt][1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[B][1], fx[B][tt], acc[tt][1], 0, 0, 0);           \
-    }                                                                                                           \
+    _Pragma("unroll") for (int tt = 0; tt < TT; ++tt)                                                           \
+        _Pragma("unroll") for (int nb = 0; nb < NB; ++nb)                                                       \
+            acc[tt][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fw[B][nb], fx[B][tt], acc[tt][nb], 0, 0, 0);  \
   } while (0)
 
     // Software pipeline.  The fragments of the next k-step are read while the matrix instructions of the current one
@@ -375,7 +546,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
     // fragments of slab s in registers (so the slab's stage can be refilled) and where slab s+1 must have landed (so
     // its first fragments can be fetched under the last k-step of slab s).  Ring: stage of slab s being refilled
     // with slab s+3, slab s+1 ready, slab s+2 in flight.
-    bf16x8 fw[2][2], fx[2][TT];
+    bf16x8 fw[2][NB], fx[2][TT];
     const bool kh_first = kh == 0;
     __syncthreads();  // every wave is done with the LDS contents of the previous pass
 #pragma unroll
@@ -413,48 +584,54 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
 #undef PAFU_S3_MMA
 #undef PAFU_S3_ISSUE
     // ---- add the two halves of the reduction axis through LDS, one token tile at a time, alternating between two
-    // 32 KB regions so that one barrier per tile is enough.  The two waves (hq, 0) and (hq, 1) swap one 32-unit block
-    // each: wave kh ends up with the complete sums of block b = kh and applies bias, activation and second layer
-    // to it, so that both waves of a SIMD share that work.
+    // 32 KB regions so that one barrier per tile is enough.  The two waves (hq, 0) and (hq, 1) swap half of their units
+    // (a 32-unit block, or 16 units of the only one): wave kh ends up with the complete sums of the kh-th half and applies
+    // bias, activation and second layer to it, so that both waves of a SIMD share that work.
     s3_wait_vmcnt<0>();
     __syncthreads();  // all loads have landed and all fragment reads are done: the ring can be reused
+    constexpr int KQ = 2 * NB;  // quadruples of units that a wave keeps (and sends)
+    const int m_wave = mp + 32 * NB * hq + 16 * NB * kh + 4 * g;  // quadruple q of the lane: units m_wave + 8 q ..
+    float4 w2q[KQ];
+#pragma unroll
+    for (int q = 0; q < KQ; ++q) w2q[q] = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
-      lds_f4* reg = (lds_f4*)(ring + (tt & 1) * 32768) + (hq * 2 + kh) * 4 * 64 + lane;       // what this wave sends
-      const lds_f4* got = (const lds_f4*)(ring + (tt & 1) * 32768) + (hq * 2 + (kh ^ 1)) * 4 * 64 + lane;
+      lds_f4* reg = (lds_f4*)(ring + (tt & 1) * 32768) + (hq * 2 + kh) * KQ * 64 + lane;       // what this wave sends
+      const lds_f4* got = (const lds_f4*)(ring + (tt & 1) * 32768) + (hq * 2 + (kh ^ 1)) * KQ * 64 + lane;
+      // element e of quadruple q of half HALF (NB = 2: block HALF; NB = 1: the upper or lower rows of the block)
+#define PAFU_S3_HALF(HALF, Q, E) (NB == 2 ? acc[tt][NB - 1 ? (HALF) : 0][4 * (Q) + (E)] : acc[tt][0][4 * (2 * (HALF) + (Q)) % 16 + (E)])
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        if (kh == 0) reg[q * 64] = f32x4_t{acc[tt][1][4 * q], acc[tt][1][4 * q + 1], acc[tt][1][4 * q + 2], acc[tt][1][4 * q + 3]};
-        else reg[q * 64] = f32x4_t{acc[tt][0][4 * q], acc[tt][0][4 * q + 1], acc[tt][0][4 * q + 2], acc[tt][0][4 * q + 3]};
+      for (int q = 0; q < KQ; ++q) {
+        if (kh == 0) reg[q * 64] = f32x4_t{PAFU_S3_HALF(1, q, 0), PAFU_S3_HALF(1, q, 1), PAFU_S3_HALF(1, q, 2), PAFU_S3_HALF(1, q, 3)};
+        else reg[q * 64] = f32x4_t{PAFU_S3_HALF(0, q, 0), PAFU_S3_HALF(0, q, 1), PAFU_S3_HALF(0, q, 2), PAFU_S3_HALF(0, q, 3)};
       }
       __syncthreads();
-      // the lane holds token c of tile tt and hidden units mp + 64 hq + 32 kh + 8 q + 4 g + e
-      float hsum[16];
+      // the lane holds token c of tile tt and hidden units m_wave + 8 q + e
+      float hsum[4 * KQ];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
+      for (int q = 0; q < KQ; ++q) {
         const f32x4_t o = got[q * 64];
-        const int m0 = mp + 64 * hq + 32 * kh + 8 * q + 4 * g;
         float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (b1 != nullptr) bb = *reinterpret_cast<const float4*>(b1 + m0);
+        if (b1 != nullptr) bb = *reinterpret_cast<const float4*>(b1 + m_wave + 8 * q);
         const float ov[4] = {o.x, o.y, o.z, o.w}, bv[4] = {bb.x, bb.y, bb.z, bb.w};
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-          hsum[4 * q + e] = (kh == 0 ? acc[tt][0][4 * q + e] : acc[tt][1][4 * q + e]) + ov[e] + bv[e];
+          hsum[4 * q + e] = (kh == 0 ? PAFU_S3_HALF(0, q, e) : PAFU_S3_HALF(1, q, e)) + ov[e] + bv[e];
       }
+#undef PAFU_S3_HALF
       if (act == PAFU_ACT_SILU) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) hsum[i] = fast_silu(hsum[i]);
+        for (int i = 0; i < 4 * KQ; ++i) hsum[i] = fast_silu(hsum[i]);
       } else {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) hsum[i] = act_accurate(hsum[i], act);
+        for (int i = 0; i < 4 * KQ; ++i) hsum[i] = act_accurate(hsum[i], act);
       }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float4 w = *reinterpret_cast<const float4*>(w2bar + mp + 64 * hq + 32 * kh + 8 * q + 4 * g);
-        partial[tt] = fmaf(w.x, hsum[4 * q], partial[tt]);
-        partial[tt] = fmaf(w.y, hsum[4 * q + 1], partial[tt]);
-        partial[tt] = fmaf(w.z, hsum[4 * q + 2], partial[tt]);
-        partial[tt] = fmaf(w.w, hsum[4 * q + 3], partial[tt]);
+      for (int q = 0; q < KQ; ++q) {
+        partial[tt] = fmaf(w2q[q].x, hsum[4 * q], partial[tt]);
+        partial[tt] = fmaf(w2q[q].y, hsum[4 * q + 1], partial[tt]);
+        partial[tt] = fmaf(w2q[q].z, hsum[4 * q + 2], partial[tt]);
+        partial[tt] = fmaf(w2q[q].w, hsum[4 * q + 3], partial[tt]);
       }
     }
   }
@@ -470,10 +647,11 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(
   for (int i = tid; i < 32 * TT; i += 512) {
     const int tok = tok_base + i;
     if (tok < T) {
-      float v = b2bar ? *b2bar : 0.f;
+      float v = A.splits == 1 ? folded_b2(L.b2, A.n_out) : 0.f;
 #pragma unroll
       for (int w = 0; w < 8; ++w) v += red[w * (32 * TT) + i];
-      out[tok] = v;
+      if (A.splits == 1) L.out[tok] = v;
+      else A.part[((long long)li * A.splits + split) * T + tok] = v;
     }
   }
 }
@@ -507,112 +685,174 @@ int score_scratch(float** out) {
 
 }  // namespace
 
-int launch_score_static(hipStream_t st, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,
-                        long long ld_x, int x_dtype, const void* W1, const float* b1, const float* W2,
-                        const float* b2, int M, int n_out, int act, float* out) {
-  if (M > PAFU_SCORE_STATIC_MAX_M) return PAFU_ERR_WORKSPACE;
+int launch_score_static(hipStream_t st, const ScoreShape& s, const ScoreLayer& layer) {
+  if (s.M > PAFU_SCORE_STATIC_MAX_M) return PAFU_ERR_WORKSPACE;
   float* ws = nullptr;
   const int rc = score_scratch(&ws);
   if (rc != PAFU_OK) return rc;
-  return launch_score(st, x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, b1, W2, b2, M, n_out, act, out, ws);
+  return launch_score(st, s, &layer, 1, ws);
 }
 
-int launch_score(hipStream_t st, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,
-                 long long ld_x, int x_dtype, const void* W1, const float* b1, const float* W2, const float* b2, int M,
-                 int n_out, int act, float* out, void* ws, const SelectJob* ride, bool* rode) {
+namespace {
+
+// What one slab of 64 features takes a workgroup, in clocks: its matrix instructions or its fragment reads from LDS (128 TT
+// and 64 (TT + 2) per 32 features and 256 units), or the copies into LDS (W1 and TT token tiles at 45 bytes per clock),
+// whichever is longer; plus the barrier and the exposed first reads.
+long long slab_cost(int tt, int nb) {
+  const int mfma = 128 * tt * nb, lds = nb == 2 ? 128 * (tt + 2) : 128 * (tt + 1);
+  const int copies = (16 * nb + 4 * tt) * 1024 / 45 - 100;
+  const int most = mfma > lds ? mfma : lds;
+  return (most > copies ? most : copies) + 100;
+}
+
+// How the streaming kernel cuts its work: tt 32-token tiles per workgroup, nb (units per pass / 128), and how many
+// workgroups share the hidden units of a token group.
+struct ScorePlan {
+  int tt, nb, splits;
+};
+ScorePlan plan_score(int T, int F, int M, int n_layers, bool keep_order, bool may_split) {
+  ScorePlan best{1, 1, 1};
+  long long best_cost = 1ll << 60;
+  const long long cus = compute_units();
+  const int tiles = (T + 31) / 32, slabs = F / kS3Slab;
+  for (int nb = 1; nb <= 2; ++nb) {
+    if (M % (128 * nb) != 0 || (keep_order && nb == 1)) continue;
+    const int passes = M / (128 * nb);
+    for (int splits = 1; splits <= passes && splits <= kScoreSplitMax; ++splits) {
+      if (passes % splits != 0 || (splits > 1 && !may_split)) continue;
+      for (int tt = 1; tt <= kS3MaxTT; ++tt) {
+        const long long wgs = (long long)((tiles + tt - 1) / tt) * splits * n_layers;
+        // (a pass ends with about 1500 + 500 tt clocks of sums and activations; the launch that adds up the splits takes
+        // about 9000)
+        const long long cost = (wgs + cus - 1) / cus * (passes / splits) * (slabs * slab_cost(tt, nb) + 1500 + 500 * tt) +
+                               (splits > 1 ? 9000 : 0);
+        if (cost <= best_cost) { best_cost = cost; best = ScorePlan{tt, nb, splits}; }
+      }
+    }
+  }
+  return best;
+}
+
+template <int TT, int NB, int SELW>
+int launch_stream(hipStream_t st, const ScoreArgs& a, int n_layers) {
+  static LdsLimit lds_limit;
+  int lds = s3_lds_bytes(TT, NB);
+  if (SELW > 0 && lds < select_bitslice_lds_bytes(512)) lds = select_bitslice_lds_bytes(512);
+  const int rc = set_lds_limit(lds_limit, score_stream_kernel<TT, NB, SELW>, lds);
+  if (rc != PAFU_OK) return rc;
+  hipLaunchKernelGGL((score_stream_kernel<TT, NB, SELW>), dim3(a.groups * a.splits * n_layers + (SELW > 0 ? 1 : 0)), dim3(512),
+                     lds, st, a);
+  if (a.splits > 1) hipLaunchKernelGGL(score_sum_kernel, dim3((a.T + 255) / 256, n_layers), dim3(256), 0, st, a);
+  return check_launch();
+}
+template <int NB>
+int launch_stream_tt(hipStream_t st, const ScoreArgs& a, int n_layers, int tt, int selw) {
+  if (tt == 1 && selw == 2) return launch_stream<1, NB, 2>(st, a, n_layers);
+  if (tt == 1 && selw == 4) return launch_stream<1, NB, 4>(st, a, n_layers);
+  if (tt == 2 && selw == 2) return launch_stream<2, NB, 2>(st, a, n_layers);
+  if (tt == 2 && selw == 4) return launch_stream<2, NB, 4>(st, a, n_layers);
+  if (tt == 3 && selw == 2) return launch_stream<3, NB, 2>(st, a, n_layers);
+  if (tt == 3 && selw == 4) return launch_stream<3, NB, 4>(st, a, n_layers);
+  if (tt == 4 && selw == 2) return launch_stream<4, NB, 2>(st, a, n_layers);
+  if (tt == 4 && selw == 4) return launch_stream<4, NB, 4>(st, a, n_layers);
+  if (tt == 5 && selw == 2) return launch_stream<5, NB, 2>(st, a, n_layers);
+  if (tt == 5 && selw == 4) return launch_stream<5, NB, 4>(st, a, n_layers);
+  switch (tt) {
+    case 1: return launch_stream<1, NB, 0>(st, a, n_layers);
+    case 2: return launch_stream<2, NB, 0>(st, a, n_layers);
+    case 3: return launch_stream<3, NB, 0>(st, a, n_layers);
+    case 4: return launch_stream<4, NB, 0>(st, a, n_layers);
+    default: return launch_stream<5, NB, 0>(st, a, n_layers);
+  }
+}
+
+// the streaming kernel addresses rows by 32-bit byte offsets from a per-workgroup base
+bool stream_takes(const ScoreShape& s) {
+  const long long F = (long long)s.n_seg * s.Fs;
+  return s.x_dtype == PAFU_BF16 && s.Fs % kS3Slab == 0 && s.M % (s.keep_order ? 256 : 128) == 0 && s.ld_x % 8 == 0 &&
+         32ll * kS3MaxTT * s.ld_x * 2 < (1ll << 31) && 256ll * F * 2 < (1ll << 31);
+}
+
+bool mfma_takes(const ScoreShape& s) {
+  return s.x_dtype == PAFU_BF16 && s.Fs % kScSlab == 0 && s.M % 32 == 0 && s.ld_x % 8 == 0;
+}
+// (rows are 16-byte aligned by the entry points' checks)
+bool f32_takes(const ScoreShape& s) { return s.x_dtype == PAFU_F32 && s.Fs % 4 == 0; }
+
+template <int MB>
+int launch_mfma(hipStream_t st, const ScoreArgs& a, int n_layers) {
+  static LdsLimit lds_limit;
+  const int rc = set_lds_limit(lds_limit, score_mfma_kernel<MB>, sc_lds_bytes(MB));
+  if (rc != PAFU_OK) return rc;
+  hipLaunchKernelGGL(score_mfma_kernel<MB>, dim3((a.T + kScTokPerWg - 1) / kScTokPerWg, n_layers), dim3(kScThreads),
+                     sc_lds_bytes(MB), st, a);
+  return check_launch();
+}
+
+}  // namespace
+
+bool score_batchable(const ScoreShape& s) {
+  return s.n_out <= kScoreFoldMax && (stream_takes(s) || mfma_takes(s) || f32_takes(s));
+}
+
+int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, int n_layers, void* fold_ws, void* scratch,
+                 size_t scratch_bytes, const SelectJob* ride, bool* rode) {
   if (rode != nullptr) *rode = false;
-  if (T <= 0) return PAFU_OK;
-  const float* w2bar = W2;
-  const float* b2bar = b2;
-  if (n_out > 1) {
-    float* w = static_cast<float*>(ws);
-    hipLaunchKernelGGL(fold_w2_kernel, dim3((M + 1 + 255) / 256), dim3(256), 0, st, W2, b2, M, n_out, w);
+  if (s.T <= 0 || n_layers <= 0) return PAFU_OK;
+  if (n_layers > 1 && (n_layers > kScoreBatchMax || !score_batchable(s))) return PAFU_ERR_SHAPE;  // callers ask first
+  ScoreArgs a;
+  a.T = s.T; a.Fs = s.Fs; a.F = s.n_seg * s.Fs; a.ld_x = s.ld_x; a.M = s.M; a.act = s.act; a.n_out = s.n_out;
+  for (int l = 0; l < n_layers; ++l) a.layer[l] = layers[l];
+  a.groups = 0;
+  a.splits = 1;
+  a.part = nullptr;
+  a.ride = SelectJob{nullptr, nullptr, nullptr, 0, 0, 0};
+  // The kernels average a few output rows themselves (12 rows of 1024 units are 48 KB beside the 9 MB of W1 that every
+  // workgroup reads); many rows, and shapes that no tiled kernel takes, get one row folded by a launch of its own (4.7 us).
+  if (s.n_out > 1 && !score_batchable(s)) {
+    float* w = static_cast<float*>(fold_ws);
+    ScoreLayer& first = a.layer[0];
+    hipLaunchKernelGGL(fold_w2_kernel, dim3((s.M + 1 + 255) / 256), dim3(256), 0, st, first.W2, first.b2, s.M, s.n_out, w);
     int rc = check_launch();
     if (rc != PAFU_OK) return rc;
-    w2bar = w;
-    b2bar = w + M;
+    first.W2 = w;
+    first.b2 = w + s.M;
+    a.n_out = 1;
   }
-  const int F = n_seg * Fs;
-  const bool mfma = x_dtype == PAFU_BF16 && Fs % kScSlab == 0 && M % 32 == 0 && ld_x % 8 == 0;
-  if (mfma) {
-    const int grid = (T + kScTokPerWg - 1) / kScTokPerWg;
-    const int blocks = M / 32;
-#define PAFU_SCORE_CASE(MB)                                                                                          \
-  do {                                                                                                               \
-    static LdsLimit lds_limit;                                                                                       \
-    const int rc_ = set_lds_limit(lds_limit, score_mfma_kernel<MB>, sc_lds_bytes(MB));                               \
-    if (rc_ != PAFU_OK) return rc_;                                                                                  \
-    hipLaunchKernelGGL(score_mfma_kernel<MB>, dim3(grid), dim3(kScThreads), sc_lds_bytes(MB), st,                    \
-                       static_cast<const unsigned short*>(x0), static_cast<const unsigned short*>(x1),               \
-                       static_cast<const unsigned short*>(x2), T, Fs, F, ld_x, static_cast<const unsigned short*>(W1), \
-                       b1, w2bar, b2bar, M, act, out);                                                               \
-  } while (0)
-    // the streaming kernel addresses rows by 32-bit byte offsets from a per-workgroup base
-    const bool offsets_fit = 32ll * kS3MaxTT * ld_x * 2 < (1ll << 31) && 256ll * F * 2 < (1ll << 31);
-    if (blocks % 8 == 0 && Fs % 64 == 0 && offsets_fit) {
-      // streaming kernel: TT 32-token tiles per workgroup.  Per 32 features a SIMD spends about 128 TT cycles in
-      // MFMAs and the CU about 64 (TT + 2) cycles serving fragment reads; each slab adds a fixed cost for the barrier
-      // and the exposed first reads.  Pick the TT that minimises that times the number of rounds the grid needs
-      // over the 256 CUs (ties go to the larger TT).
-      const int tiles = (T + 31) / 32;
-      int best_tt = 1;
-      long long best_cost = 1ll << 60;
-      for (int tt = 1; tt <= kS3MaxTT; ++tt) {
-        const int wgs = (tiles + tt - 1) / tt;
-        const int mfma = 128 * tt, lds = 64 * (tt + 2);
-        const long long cost = (long long)((wgs + 255) / 256) * ((kS3Slab / 32) * (mfma > lds ? mfma : lds) + 100);
-        if (cost <= best_cost) { best_cost = cost; best_tt = tt; }
-      }
-#define PAFU_SCORE3_LAUNCH(TT, SELW, LDS, EXTRA)                                                                     \
-  do {                                                                                                               \
-    static LdsLimit lds_limit3;                                                                                      \
-    const int rc_ = set_lds_limit(lds_limit3, score_stream_kernel<TT, SELW>, LDS);                                   \
-    if (rc_ != PAFU_OK) return rc_;                                                                                  \
-    hipLaunchKernelGGL((score_stream_kernel<TT, SELW>), dim3((tiles + TT - 1) / TT + EXTRA), dim3(512), LDS, st,     \
-                       static_cast<const unsigned short*>(x0), static_cast<const unsigned short*>(x1),               \
-                       static_cast<const unsigned short*>(x2), T, Fs, F, ld_x, static_cast<const unsigned short*>(W1), \
-                       b1, w2bar, b2bar, M, act, out, job);                                                          \
-  } while (0)
-#define PAFU_SCORE3_CASE(TT) PAFU_SCORE3_LAUNCH(TT, 0, s3_lds_bytes(TT), 0)
-#define PAFU_SCORE3_RIDE(TT, SELW)                                                                                   \
-  PAFU_SCORE3_LAUNCH(TT, SELW,                                                                                       \
-                     (s3_lds_bytes(TT) > select_bitslice_lds_bytes(512) ? s3_lds_bytes(TT) : select_bitslice_lds_bytes(512)), 1)
-      SelectJob job{nullptr, nullptr, nullptr, 0, 0, 0};
-      // a selection rides along when the launch is short (one or two token tiles per workgroup: a chunk, not a whole
-      // cache) and the list fits the 512-thread bit-sliced selection
-      if (ride != nullptr && best_tt <= 2 && ride->n > 0 && ride->n <= 512 * 32 * 4) {
-        job = *ride;
-        if (job.n_pinned < 0) job.n_pinned = 0;
-        const bool w2 = job.n <= 512 * 32 * 2;
-        if (best_tt == 1) { if (w2) PAFU_SCORE3_RIDE(1, 2); else PAFU_SCORE3_RIDE(1, 4); }
-        else { if (w2) PAFU_SCORE3_RIDE(2, 2); else PAFU_SCORE3_RIDE(2, 4); }
-        if (rode != nullptr) *rode = true;
-        return check_launch();
-      }
-      switch (best_tt) {
-        case 1: PAFU_SCORE3_CASE(1); break;
-        case 2: PAFU_SCORE3_CASE(2); break;
-        case 3: PAFU_SCORE3_CASE(3); break;
-        case 4: PAFU_SCORE3_CASE(4); break;
-        default: PAFU_SCORE3_CASE(5); break;
-      }
-#undef PAFU_SCORE3_CASE
-#undef PAFU_SCORE3_RIDE
-#undef PAFU_SCORE3_LAUNCH
-    } else if (blocks % 8 == 0) PAFU_SCORE_CASE(8);
-    else if (blocks % 4 == 0) PAFU_SCORE_CASE(4);
-    else if (blocks % 2 == 0) PAFU_SCORE_CASE(2);
-    else PAFU_SCORE_CASE(1);
-#undef PAFU_SCORE_CASE
-  } else {
-    const int grid = (T + 15) / 16;
-    if (x_dtype == PAFU_BF16)
-      hipLaunchKernelGGL(score_generic_kernel<true>, dim3(grid), dim3(256), 0, st, x0, x1, x2, n_seg, T, Fs, ld_x, W1,
-                         b1, w2bar, b2bar, M, act, out);
-    else
-      hipLaunchKernelGGL(score_generic_kernel<false>, dim3(grid), dim3(256), 0, st, x0, x1, x2, n_seg, T, Fs, ld_x, W1,
-                         b1, w2bar, b2bar, M, act, out);
+  if (stream_takes(s)) {
+    const bool may_split = !s.keep_order && scratch != nullptr && (reinterpret_cast<uintptr_t>(scratch) & 3u) == 0 &&
+                           scratch_bytes >= (size_t)n_layers * kScoreSplitMax * s.T * sizeof(float);
+    const ScorePlan plan = plan_score(s.T, a.F, s.M, n_layers, s.keep_order, may_split);
+    a.groups = ((s.T + 31) / 32 + plan.tt - 1) / plan.tt;
+    a.splits = plan.splits;
+    a.part = static_cast<float*>(scratch);
+    int selw = 0;
+    // a selection rides along when the last round of workgroups leaves a CU for it (one more workgroup would otherwise be
+    // a round of its own) and the list fits the 512-thread bit-sliced selection
+    if (ride != nullptr && (long long)a.groups * a.splits % compute_units() != 0 && ride->n > 0 && ride->n <= 512 * 32 * 4) {
+      a.ride = *ride;
+      if (a.ride.n_pinned < 0) a.ride.n_pinned = 0;
+      selw = a.ride.n <= 512 * 32 * 2 ? 2 : 4;
+      if (rode != nullptr) *rode = true;
+    }
+    return plan.nb == 2 ? launch_stream_tt<2>(st, a, n_layers, plan.tt, selw) : launch_stream_tt<1>(st, a, n_layers, plan.tt, selw);
   }
+  if (mfma_takes(s)) {
+    if (s.M % 128 == 0) return launch_mfma<4>(st, a, n_layers);
+    return s.M % 64 == 0 ? launch_mfma<2>(st, a, n_layers) : launch_mfma<1>(st, a, n_layers);
+  }
+  if (f32_takes(s)) {
+    hipLaunchKernelGGL(score_f32_kernel, dim3((s.T + 15) / 16, n_layers), dim3(256), 0, st, a);
+    return check_launch();
+  }
+  const ScoreLayer& L = a.layer[0];
+  const dim3 grid((s.T + 15) / 16);
+  if (s.x_dtype == PAFU_BF16)
+    hipLaunchKernelGGL(score_generic_kernel<true>, grid, dim3(256), 0, st, L.x[0], L.x[1], L.x[2], s.n_seg, s.T, s.Fs, s.ld_x,
+                       L.W1, L.b1, L.W2, L.b2, s.M, s.act, L.out);
+  else
+    hipLaunchKernelGGL(score_generic_kernel<false>, grid, dim3(256), 0, st, L.x[0], L.x[1], L.x[2], s.n_seg, s.T, s.Fs, s.ld_x,
+                       L.W1, L.b1, L.W2, L.b2, s.M, s.act, L.out);
   return check_launch();
 }
 
