@@ -31,8 +31,7 @@ __global__ __launch_bounds__(kCompactThreads) void compact_rows_kernel(
   }
   // rows [0, count) are gathered through ids; rows [count, count + tail.rows) are the tail's rows in order (the
   // chunk that a rollout appends behind the retained rows, Alg. 2).  The tail rows are handed out first: quantising
-  // one is a long chain of integer arithmetic, which then runs beside the other waves' memory-bound gathers instead
-  // of trailing behind them.
+  // one takes longer than a copy, and then runs beside the other waves' memory-bound gathers instead of trailing behind.
   const int total = count + tail.rows;
   for (int w = wave; w < total; w += n_waves) {
     const int r = w < tail.rows ? count + w : w - tail.rows;
@@ -91,22 +90,29 @@ __global__ __launch_bounds__(kCompactThreads) void compact_rows_kernel(
   }
 }
 
-// The same gather for several layers in one launch (multi-layer steps): a wave takes a retained row and moves it in
-// every layer of the batch, K and V, before it goes on to its next row.  The layers share the row geometry; each
-// brings its own tensors and index list (the same list for all of them when the indices are shared, Sec. 3.3).
+// The same gather for several layers in one launch (multi-layer steps): the waves walk the rows of the first layer, then
+// those of the second, and so on.  The layers share the row geometry; each brings its own tensors and index list (the same
+// list for all of them when the indices are shared, Sec. 3.3).  A wave that took one row through all the layers waited for
+// an index and a row in each of them in turn: 6 layers of 2999 rows (8 x 64) 19.6 -> 15.1 us.
 template <int CPL>
 __global__ __launch_bounds__(kCompactThreads) void compact_rows_batch_kernel(CompactBatch B, int n_layers,
                                                                              long long ld_in, int n, int count,
                                                                              int chunks, long long ld_out,
                                                                              int tail_rows, long long ld_tail) {
   const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+  const int wave = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_waves = gridDim.x * kWavesPerBlock;
   const int total = count + tail_rows;  // rows [count, total) come from every layer's tail tensors, in order
-  for (int r = wave; r < total; r += n_waves) {
+  int r = wave;
 #pragma unroll 1
-    for (int l = 0; l < n_layers; ++l) {
-      const CompactLayer& L = B.layer[l];
+  for (int l = 0;; r += n_waves) {
+    while (r >= total && l < n_layers) {
+      r -= total;
+      ++l;
+    }
+    if (l == n_layers) break;
+    {
+      const CompactLayer& L = B.layer[__builtin_amdgcn_readfirstlane(l)];
       const u32x4 *ks, *vs;
       int id = 0;
       if (r < count) {
@@ -190,9 +196,9 @@ __global__ __launch_bounds__(kCompactThreads) void append_rows_kernel(
   }
 }
 
-int grid_for_rows(int rows) {
+int grid_for_rows(long long rows) {
   // one row per wave per iteration; enough blocks to cover the chip several times over
-  long long blocks = ((long long)rows + kWavesPerBlock - 1) / kWavesPerBlock;
+  long long blocks = (rows + kWavesPerBlock - 1) / kWavesPerBlock;
   const long long cap = 256 * 16;
   if (blocks > cap) blocks = cap;
   if (blocks < 1) blocks = 1;
@@ -256,7 +262,7 @@ int launch_compact_batch(hipStream_t st, const CompactLayer* layers, int n_layer
     const int m = n_layers - first < kCompactBatchMax ? n_layers - first : kCompactBatchMax;
     CompactBatch B;
     for (int i = 0; i < kCompactBatchMax; ++i) B.layer[i] = layers[first + (i < m ? i : 0)];
-    const dim3 grid(grid_for_rows(count + tail_rows)), block(kCompactThreads);
+    const dim3 grid(grid_for_rows(((long long)count + tail_rows) * m)), block(kCompactThreads);
 #define PAFU_COMPACT_BATCH_CASE(C)                                                                                \
   hipLaunchKernelGGL(compact_rows_batch_kernel<C>, grid, block, 0, st, B, m, ld_in_bytes, n, count, chunks,      \
                      ld_out_bytes, tail_rows, ld_tail_bytes)
