@@ -483,20 +483,20 @@ def main():
     for s_ in sets:
         B.set_stage_events(s_["args"], [None] * 5)
     ms_with_events = float(np.mean([x.elapsed_time(y) for x, y, _ in recorded]))
-    attn_ms = [sev[3].elapsed_time(sev[4]) for _, _, se in recorded for sev in se]
+    # (the attention of all layers is one launch: its time per layer)
+    attn_ms = [se[0][3].elapsed_time(se[-1][4]) / n_layers for _, _, se in recorded]
     if n_layers == 1:
         score_ms = [se[0][0].elapsed_time(se[0][1]) for _, _, se in recorded]
         select_ms = [se[0][1].elapsed_time(se[0][2]) for _, _, se in recorded]
         compact_ms = [se[0][2].elapsed_time(se[0][3]) for _, _, se in recorded]
         select_note = None
     else:
-        # Multi-layer steps: all scoring first, then ONE selection launch for up to 32 layers, then ONE compaction
-        # launch for up to 32 layers, then attention layer by layer.  The library records "after selection" once per
-        # step (on layer 0, or on the index layer); compaction = from there to the start of layer 0's attention,
-        # shared out over the layers.
+        # Multi-layer steps: all scoring, then all selections, then all compactions, then all attention, each one launch
+        # for up to 32 layers.  The library records "after selection" once per step (on layer 0, or on the index layer);
+        # compaction = from there to the start of the attention; every stage's time is shared out over the layers.
         scoring = [idx_layer] if shared else list(range(n_layers))
         sel_layer = idx_layer if shared else 0
-        score_ms = [se[l][0].elapsed_time(se[l][1]) for _, _, se in recorded for l in scoring]
+        score_ms = [se[scoring[0]][0].elapsed_time(se[scoring[-1]][1]) / len(scoring) for _, _, se in recorded]
         select_ms = [se[scoring[-1]][1].elapsed_time(se[sel_layer][2]) for _, _, se in recorded]
         compact_ms = [se[sel_layer][2].elapsed_time(se[0][3]) / n_layers for _, _, se in recorded]
         select_note = "one launch per step for %s; compaction: one launch for all %d layers, time per layer" % (

@@ -290,14 +290,17 @@ typedef struct pafu_step_args {
 } pafu_step_args;
 
 /* Workspace of a step = the scoring part (only when n_out > 1; required) followed by the attention part (optional:
- * see pafu_chunk_attention).  pafu_step_workspace_bytes returns the size of both; a workspace that only covers the
- * scoring part is accepted and the attention launch then runs without its equal-run split. */
+ * see pafu_chunk_attention; it also serves as scratch of the scoring before it).  pafu_step_workspace_bytes returns the
+ * size of both; a workspace that only covers the scoring part is accepted and the step then runs without the splits of
+ * its scoring and attention launches. */
 size_t pafu_step_workspace_bytes(const pafu_step_args* args /* host */);
 int pafu_step(void* stream, const pafu_step_args* args /* host */);
 /* The same step for n_layers independent layers (args[l] is layer l's arguments), enqueued on one stream.
- * The layers' stages are NOT enqueued layer by layer: every layer is scored first, then all selections run in one
+ * The layers' stages are NOT enqueued layer by layer: every layer is scored first (one launch for a stretch of up to 32
+ * layers of one geometry and workspace), then all selections run in one
  * launch (up to 32 score lists per launch), then all compactions (one launch per 32 layers when the layers share
- * n, k, N, D, the strides and the storage type; layer by layer otherwise), then attention layer by layer.  Every layer
+ * n, k, N, D, the strides and the storage type; layer by layer otherwise), then attention (one launch for a stretch of
+ * up to 32 layers of one geometry and workspace; such layers' stage events are recorded together).  Every layer
  * therefore needs its own scores, ids, SL_out, K_out, V_out and O buffers, and no layer's output may overlap
  * another layer's input (PAFU_ERR_ALIAS); only the workspace may be shared between layers. */
 int pafu_step_layers(void* stream, const pafu_step_args* args /* host array */, int n_layers);
