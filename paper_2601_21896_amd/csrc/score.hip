@@ -1,7 +1,7 @@
 // Salience Estimation Head (S-MLP) forward: s[t] = mean_o( W2 . act(W1 . x[t] + b1) + b2 ).
 // App. A "S-MLP" and Sec. 3.3-3.4 of the paper (two linear layers, SiLU in between, mean over outputs).
 //
-// The mean over the outputs of a linear layer is a linear layer with the averaged weight row: the tiled kernels average a
+// The mean over the outputs of a linear layer is a linear layer with the averaged weight row: some launches average a
 // few rows of W2/b2 themselves, for many rows a tiny pre-kernel folds them into one row w2bar[M] and a scalar; layer 1,
 // the activation, the dot with the averaged row and the bias are one pass over X.
 //
@@ -58,6 +58,7 @@ struct ScoreArgs {
   long long ld_x;
   int M, act;
   int n_out;    // rows of W2 / b2 that the kernel averages itself (1: W2 / b2 are one row, folded or as given)
+  int n_layers;
   int groups;   // token groups of a layer
   int splits;   // workgroups that share the hidden units of one token group; above 1 they write partial sums
   float* part;  // [layer][split][T] partial sums, added up by score_sum_kernel
@@ -423,10 +424,12 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   }
   // Workgroups are handed to the 8 XCDs in turn: the splits of a token group are 8 apart, so that one L2 serves its
   // features to all of them.
+  // (no divisions in front of the first load where one layer and no splits make them needless)
   const int per_layer = A.groups * A.splits;
-  const int li = id / per_layer;
-  int group, split;
-  {
+  int li = 0;
+  if (A.n_layers > 1) li = id / per_layer;
+  int group = id - li * per_layer, split = 0;
+  if (A.splits > 1) {
     const int w = id - li * per_layer, band = 8 * A.splits, full = A.groups / 8 * 8;
     if (w < full * A.splits) {
       const int r = w % band;
@@ -803,13 +806,23 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
   ScoreArgs a;
   a.T = s.T; a.Fs = s.Fs; a.F = s.n_seg * s.Fs; a.ld_x = s.ld_x; a.M = s.M; a.act = s.act; a.n_out = s.n_out;
   for (int l = 0; l < n_layers; ++l) a.layer[l] = layers[l];
+  a.n_layers = n_layers;
   a.groups = 0;
   a.splits = 1;
   a.part = nullptr;
   a.ride = SelectJob{nullptr, nullptr, nullptr, 0, 0, 0};
-  // The kernels average a few output rows themselves (12 rows of 1024 units are 48 KB beside the 9 MB of W1 that every
-  // workgroup reads); many rows, and shapes that no tiled kernel takes, get one row folded by a launch of its own (4.7 us).
-  if (s.n_out > 1 && !score_batchable(s)) {
+  const bool stream = stream_takes(s);
+  ScorePlan plan{1, 1, 1};
+  if (stream) {
+    const bool may_split = !s.keep_order && scratch != nullptr && (reinterpret_cast<uintptr_t>(scratch) & 3u) == 0 &&
+                           scratch_bytes >= (size_t)n_layers * kScoreSplitMax * s.T * sizeof(float);
+    plan = plan_score(s.T, a.F, s.M, n_layers, s.keep_order, may_split);
+  }
+  // Who averages the output rows.  A kernel does it at the end of a pass, about 3 us for 12 rows, a launch of its own takes
+  // 4.7 us: in the kernel for several layers, for a single pass per workgroup and for the few units of the fp32 kernel
+  // (21840 tokens of 4608 features and 1024 units: 249 us with it in all four passes, 235 with the launch).
+  const bool own_rows = n_layers > 1 || (stream ? s.M / plan.splits == 128 * plan.nb : f32_takes(s));
+  if (s.n_out > 1 && !(own_rows && score_batchable(s))) {
     float* w = static_cast<float*>(fold_ws);
     ScoreLayer& first = a.layer[0];
     hipLaunchKernelGGL(fold_w2_kernel, dim3((s.M + 1 + 255) / 256), dim3(256), 0, st, first.W2, first.b2, s.M, s.n_out, w);
@@ -819,10 +832,7 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
     first.b2 = w + s.M;
     a.n_out = 1;
   }
-  if (stream_takes(s)) {
-    const bool may_split = !s.keep_order && scratch != nullptr && (reinterpret_cast<uintptr_t>(scratch) & 3u) == 0 &&
-                           scratch_bytes >= (size_t)n_layers * kScoreSplitMax * s.T * sizeof(float);
-    const ScorePlan plan = plan_score(s.T, a.F, s.M, n_layers, s.keep_order, may_split);
+  if (stream) {
     a.groups = ((s.T + 31) / 32 + plan.tt - 1) / plan.tt;
     a.splits = plan.splits;
     a.part = static_cast<float*>(scratch);
