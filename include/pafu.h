@@ -78,6 +78,8 @@ int pafu_launch_probe(void* stream);
  *   workspace: pafu_score_workspace_bytes(M) bytes (holds the output-averaged second layer)
  * bf16 inputs with Fs % 64 == 0 and M % 32 == 0 take the MFMA paths (fp32 accumulate; M % 256 == 0 the
  * streaming kernel); anything else takes a plain fp32-FMA path.  T == 0 is a no-op.
+ * A token's score has the same bits in every call with the same head and row stride, whatever the number of tokens,
+ * and also as part of a step (any mode, workspace or number of layers).
  */
 size_t pafu_score_workspace_bytes(int M);
 int pafu_score(void* stream, const void* x0, const void* x1, const void* x2, int n_seg, int T, int Fs,

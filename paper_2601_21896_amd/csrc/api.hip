@@ -321,9 +321,13 @@ WsPart attention_ws(const pafu_step_args* a, bool scoring) {
 }
 
 // The scoring part of a step: SINGLE scores cache + chunk into a->scores, ROLLOUT the chunk into SL_out behind the
-// retained rows.  Both read the head's weights; the attention's part of the workspace, idle until then, is the scratch.
+// retained rows.  Both read the head's weights.  A rollout's chunk is a launch too short to fill the chip by its tokens:
+// it gets the attention's part of the workspace, idle until then, as scratch for sharing its hidden units.
+WsPart score_scratch_ws(const pafu_step_args* a) {
+  return a->mode == PAFU_MODE_SINGLE ? WsPart{nullptr, 0} : attention_ws(a, true);
+}
 ScoreShape score_shape(const pafu_step_args* a, int T) {
-  return ScoreShape{a->n_seg, T, a->Fs, a->ld_x, a->x_dtype, a->M, a->n_out, a->act, a->mode == PAFU_MODE_SINGLE};
+  return ScoreShape{a->n_seg, T, a->Fs, a->ld_x, a->x_dtype, a->M, a->n_out, a->act};
 }
 ScoreLayer score_layer(const pafu_step_args* a, const void* const* x, float* out) {
   return ScoreLayer{{x[0], x[1], x[2]}, a->W1, a->b1, a->W2, a->b2, out};
@@ -352,7 +356,7 @@ int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nul
   if (selected != nullptr) *selected = false;
   int rc = record_stage(st, a, 0);
   if (rc) return rc;
-  const WsPart scratch = attention_ws(a, true);
+  const WsPart scratch = score_scratch_ws(a);
   if (scores_in_one_launch(a)) {
     const SelectJob job{a->SL_in, a->ids, nullptr, a->n, a->k, a->n_pinned};
     const bool may_ride = selected != nullptr && a->mode != PAFU_MODE_SINGLE && a->n > 0;
@@ -362,9 +366,9 @@ int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nul
     if (rc) return rc;
   } else {
     const ScoreLayer cache = score_layer(a, a->x_cache, a->scores), chunk = score_layer(a, a->x_chunk, a->scores + a->n);
-    rc = launch_score(st, score_shape(a, a->n), &cache, 1, a->workspace, scratch.p, scratch.bytes);
+    rc = launch_score(st, score_shape(a, a->n), &cache, 1, a->workspace);
     if (rc) return rc;
-    rc = launch_score(st, score_shape(a, a->Lc), &chunk, 1, a->workspace, scratch.p, scratch.bytes);
+    rc = launch_score(st, score_shape(a, a->Lc), &chunk, 1, a->workspace);
     if (rc) return rc;
   }
   return record_stage(st, a, 1);
@@ -392,7 +396,7 @@ int enqueue_layers_scores(hipStream_t st, const pafu_step_args* args, int n_laye
       continue;
     }
     ScoreLayer layers[kScoreBatchMax];
-    const WsPart scratch = attention_ws(a, true);
+    const WsPart scratch = score_scratch_ws(a);
     for (int l = first; l < last; ++l) {
       layers[l - first] = one_launch_layer(&args[l]);
       if ((rc = record_stage(st, &args[l], 0))) return rc;
@@ -645,7 +649,7 @@ int pafu_score(void* stream, const void* x0, const void* x1, const void* x2, int
   int rc = check_score(x0, x1, x2, n_seg, T, Fs, ld_x, x_dtype, W1, W2, M, n_out, act, out, workspace, workspace_bytes);
   if (rc) return rc;
   const ScoreLayer layer{{x0, x1, x2}, W1, b1, W2, b2, out};
-  return launch_score(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act, true}, &layer, 1,
+  return launch_score(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act}, &layer, 1,
                       workspace);
 }
 
@@ -657,7 +661,7 @@ int pafu_score_static(void* stream, const void* x0, const void* x1, const void* 
   if (rc) return rc;
   if (M > PAFU_SCORE_STATIC_MAX_M) return PAFU_ERR_WORKSPACE;
   const ScoreLayer layer{{x0, x1, x2}, W1, b1, W2, b2, out};
-  return launch_score_static(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act, true}, layer);
+  return launch_score_static(static_cast<hipStream_t>(stream), ScoreShape{n_seg, T, Fs, ld_x, x_dtype, M, n_out, act}, layer);
 }
 
 size_t pafu_select_workspace_bytes(int n) {

@@ -97,10 +97,6 @@ struct ScoreShape {
   int n_seg, T, Fs;
   long long ld_x;
   int x_dtype, M, n_out, act;
-  // The scores decide a selection in the same call, or are the call's result: a token's sums are then formed in one order
-  // whatever the launch looks like, so that two close scores never change places.  Otherwise (the chunk of a rollout) the
-  // units may be summed in other groups.
-  bool keep_order;
 };
 struct ScoreLayer {
   const void* x[3];
@@ -113,8 +109,10 @@ constexpr int kScoreSplitMax = 8;   // most workgroups that share the hidden uni
 constexpr int kScoreFoldMax = 16;   // most output rows of the second layer that the streaming kernel averages itself
 // Can several layers of this shape go in one launch?
 bool score_batchable(const ScoreShape& s);
-// fold_ws: the score workspace (one layer, n_out > 1).  scratch (may be null): with n_layers * kScoreSplitMax * T floats
-// the hidden units of a token group may be shared by several workgroups.
+// A token's sums are formed in one order whatever the launch looks like: the scores decide selections, in the same call or
+// (the chunk of a rollout) in a later one, so two close scores must never change places.
+// fold_ws: the score workspace (one layer, n_out > 1).  scratch (may be null; 16-byte aligned): with room for the
+// activations of all hidden units of all tokens, these units may be shared by several workgroups.
 // `ride`: a selection that does not depend on these scores (the stored list of a rollout step); when the launch is a
 // streaming one with a CU to spare it is done by one extra workgroup of the same launch and *rode is set, otherwise the caller
 // launches it.

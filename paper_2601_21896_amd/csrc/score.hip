@@ -9,7 +9,7 @@
 // (v_mfma_f32_32x32x16_bf16, fp32 accumulate).  H = W1.X is produced as H^T tiles (rows = hidden units,
 // columns = tokens), so one lane holds 16 hidden units of ONE token per tile and the reduction over hidden
 // units is almost entirely in-register.
-//  - score_stream_kernel (M a multiple of 128, or of 256 where a selection follows from the scores): the measured path.
+//  - score_stream_kernel (M a multiple of 256): the measured path.
 //    W1 and the features both stream global -> LDS through a ring of 64-feature slabs; a workgroup owns several 32-token
 //    tiles so that one W1 fragment feeds several matrix instructions.  Described in detail above the kernel.
 //    In a rollout step one extra workgroup of this launch runs the top-k selection on the stored score list
@@ -18,6 +18,10 @@
 //    into B-operand registers; W1 is staged through LDS in 64-feature slabs shared by the waves of a workgroup.
 //
 // fp32 inputs, or shapes the tiles do not divide: plain fp32 FMAs, through LDS tiles where rows are whole 16-byte chunks.
+//
+// A score is compared with scores of other launches (a rollout selects on a list that many chunks have added to), so its
+// bits are a function of the token and the head alone: whatever the number of tokens, the layers in the launch and the
+// scratch, the same kernel's order of sums is kept.
 #include "pafu_internal.h"
 #include "select_body.h"
 
@@ -60,8 +64,10 @@ struct ScoreArgs {
   int n_out;    // rows of W2 / b2 that the kernel averages itself (1: W2 / b2 are one row, folded or as given)
   int n_layers;
   int groups;   // token groups of a layer
-  int splits;   // workgroups that share the hidden units of one token group; above 1 they write partial sums
-  float* part;  // [layer][split][T] partial sums, added up by score_sum_kernel
+  int splits;   // workgroups that share the hidden units of one token group; above 1 they write their activations
+  float* acts;  // [layer][M][ld_acts] activations of the hidden units, added up by score_sum_kernel
+  long long ld_acts;
+  float* w2bar;  // [layer][M] averaged second layer, written by the first token group's workgroups (n_out > 1)
   SelectJob ride;
   ScoreLayer layer[kScoreBatchMax];
 };
@@ -84,15 +90,44 @@ __device__ __forceinline__ float folded_b2(const float* __restrict__ b2, int n_o
   return s * (1.0f / (float)n_out);
 }
 
-// out[t] = b2 + the partial sums of the token's splits, in order
-__global__ void score_sum_kernel(ScoreArgs a) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= a.T) return;
+// Second layer of a token whose hidden units were shared by several workgroups.  One wave per (unit quarter, half) and 32
+// tokens: a lane adds up the units that it would have held at the end of the passes of the unsplit kernel, in the same
+// order, and the lane halves and the eight waves are added in the same order too.
+__global__ __launch_bounds__(512) void score_sum_kernel(ScoreArgs a) {
+  __shared__ float red[8 * 32];
   const ScoreLayer& L = a.layer[blockIdx.y];
-  const float* p = a.part + (long long)blockIdx.y * a.splits * a.T + t;
-  float v = folded_b2(L.b2, a.n_out);
-  for (int i = 0; i < a.splits; ++i) v += p[(long long)i * a.T];
-  L.out[t] = v;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, c = lane & 31;
+  const int t = blockIdx.x * 32 + c;
+  const int m_wave = 64 * (wave & 3) + 32 * (wave >> 2) + 4 * g;
+  const float* acts = a.acts + (long long)blockIdx.y * a.M * a.ld_acts + t;  // (ld_acts covers the last 32 tokens)
+  const float* w2 = a.n_out == 1 ? L.W2 : a.w2bar + (long long)blockIdx.y * a.M;
+  float partial = 0.f;
+  for (int mp = m_wave; mp < a.M; mp += 256) {
+    float v[16];
+    float4 w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      w[q] = *reinterpret_cast<const float4*>(w2 + mp + 8 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[4 * q + e] = acts[(mp + 8 * q + e) * a.ld_acts];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      partial = fmaf(w[q].x, v[4 * q], partial);
+      partial = fmaf(w[q].y, v[4 * q + 1], partial);
+      partial = fmaf(w[q].z, v[4 * q + 2], partial);
+      partial = fmaf(w[q].w, v[4 * q + 3], partial);
+    }
+  }
+  partial += __shfl_xor(partial, 32);
+  if (g == 0) red[wave * 32 + c] = partial;
+  __syncthreads();
+  if (threadIdx.x < 32 && t < a.T) {
+    float v = folded_b2(L.b2, a.n_out);
+#pragma unroll
+    for (int w = 0; w < 8; ++w) v += red[w * 32 + c];
+    L.out[t] = v;
+  }
 }
 
 // ---------------------------------------------------------------------------------- generic path
@@ -361,7 +396,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) 
 }
 
 // ---------------------------------------------------------------------------------- streaming MFMA path
-// For M % 128 == 0 and Fs % 64 == 0.  With a 256-wide hidden layer the head sits near the ridge of the roofline
+// For M % 256 == 0 and Fs % 64 == 0.  With a 256-wide hidden layer the head sits near the ridge of the roofline
 // (about 256 flop per byte of features), and every CU has to pull all of W1 through its L1 once per token group, so
 // the kernel must keep the matrix cores and the memory pipe busy at the same time: an even spread of MFMA work over
 // the 1024 SIMDs, few LDS bytes per MFMA, and many bytes in flight without spending registers on them.
@@ -373,10 +408,11 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) 
 //  - W1 and the features stream global -> LDS with global_load_lds through a ring of slabs (no staging registers,
 //    all but one slab of the ring in flight), rows XOR-swizzled in 16-byte chunks for conflict-free b128 reads.
 //  - A CU takes in about 45 bytes per clock, and a slab's W1 part (32 KB at NB = 2) costs more than its TT feature tiles.
-//    A hidden layer of several passes is therefore shared by `splits` workgroups, which makes room for a larger TT: 4680
+//    A hidden layer may therefore be shared by `splits` workgroups (SPLIT), which makes room for a larger TT: 4680
 //    tokens of 4608 features and 1024 units took 128 us with one token tile per workgroup and all four passes in it, and
-//    take 57 us with five tiles and an eighth of the units (10800 tokens, 5120 features, 512 units: 123 -> 80 us).  The
-//    partial sums go through scratch and one more small launch (5 us).
+//    take 62 us with five tiles and an eighth of the units (10800 tokens, 5120 features, 512 units: 123 -> 80 us).
+//    What the workgroups leave in scratch are activations, not partial sums: one more launch (6.5 us in both) then takes them through
+//    the second layer in the order of the unsplit kernel, so that a score's bits do not depend on the launch.
 //  - Layers of one geometry share a launch: the token groups of one (57 at 7210 tokens) leave most of the chip idle
 //    (six of 128 units: 6 x 12.9 us one by one, 26 us together, in the kernel above).
 constexpr int kS3Slab = 64;                      // features per slab (full 128-byte lines per row)
@@ -412,8 +448,9 @@ __device__ __forceinline__ void s3_wait_vmcnt() {
 // threads) on a list that does not depend on this launch's scores: the stored score list of a rollout step.  A
 // selection keeps one CU busy for about as long as the scoring of a chunk takes the others, so carried along it
 // costs nothing, where a launch of its own would leave the rest of the chip idle meanwhile.
-template <int TT, int NB, int SELW>
+template <int TT, int NB, bool SPLIT, int SELW>
 __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
+  static_assert(SPLIT || NB == 2, "the order of a score's sums is that of passes of 256 units");
   int id = blockIdx.x;
   if constexpr (SELW > 0) {
     if (id == 0) {
@@ -429,7 +466,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   int li = 0;
   if (A.n_layers > 1) li = id / per_layer;
   int group = id - li * per_layer, split = 0;
-  if (A.splits > 1) {
+  if constexpr (SPLIT) {
     const int w = id - li * per_layer, band = 8 * A.splits, full = A.groups / 8 * 8;
     if (w < full * A.splits) {
       const int r = w % band;
@@ -500,7 +537,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) partial[tt] = 0.f;
 
-  const int m_share = A.M / A.splits;
+  const int m_share = SPLIT ? A.M / A.splits : A.M;
 #pragma unroll 1
   for (int mp = split * m_share; mp < (split + 1) * m_share; mp += MP) {
     f32x16 acc[TT][NB];
@@ -596,7 +633,11 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
     const int m_wave = mp + 32 * NB * hq + 16 * NB * kh + 4 * g;  // quadruple q of the lane: units m_wave + 8 q ..
     float4 w2q[KQ];
 #pragma unroll
-    for (int q = 0; q < KQ; ++q) w2q[q] = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
+    for (int q = 0; q < KQ; ++q) {
+      if (!SPLIT) w2q[q] = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
+      else if (A.n_out > 1 && group == 0 && c == 0)
+        *reinterpret_cast<float4*>(A.w2bar + (long long)li * A.M + m_wave + 8 * q) = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
+    }
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
       lds_f4* reg = (lds_f4*)(ring + (tt & 1) * 32768) + (hq * 2 + kh) * KQ * 64 + lane;       // what this wave sends
@@ -629,6 +670,15 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
 #pragma unroll
         for (int i = 0; i < 4 * KQ; ++i) hsum[i] = act_accurate(hsum[i], act);
       }
+      if constexpr (SPLIT) {
+        const int tok = tok_base + 32 * tt + c;
+        float* const acts = A.acts + ((long long)li * A.M + m_wave) * A.ld_acts + tok;
+        if (tok < T) {
+#pragma unroll
+          for (int i = 0; i < 4 * KQ; ++i) acts[(8 * (i >> 2) + (i & 3)) * A.ld_acts] = hsum[i];
+        }
+        continue;
+      }
 #pragma unroll
       for (int q = 0; q < KQ; ++q) {
         partial[tt] = fmaf(w2q[q].x, hsum[4 * q], partial[tt]);
@@ -638,6 +688,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
       }
     }
   }
+  if (SPLIT) return;
   // ---- add the two lane halves, then the eight waves (each holds the part of its 32-unit blocks)
   __syncthreads();
   float* red = reinterpret_cast<float*>(lds_raw);
@@ -650,11 +701,10 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   for (int i = tid; i < 32 * TT; i += 512) {
     const int tok = tok_base + i;
     if (tok < T) {
-      float v = A.splits == 1 ? folded_b2(L.b2, A.n_out) : 0.f;
+      float v = folded_b2(L.b2, A.n_out);
 #pragma unroll
       for (int w = 0; w < 8; ++w) v += red[w * (32 * TT) + i];
-      if (A.splits == 1) L.out[tok] = v;
-      else A.part[((long long)li * A.splits + split) * T + tok] = v;
+      L.out[tok] = v;
     }
   }
 }
@@ -713,66 +763,67 @@ long long slab_cost(int tt, int nb) {
 struct ScorePlan {
   int tt, nb, splits;
 };
-ScorePlan plan_score(int T, int F, int M, int n_layers, bool keep_order, bool may_split) {
-  ScorePlan best{1, 1, 1};
+ScorePlan plan_score(int T, int F, int M, int n_layers, bool may_split) {
+  ScorePlan best{1, 2, 1};
   long long best_cost = 1ll << 60;
   const long long cus = compute_units();
   const int tiles = (T + 31) / 32, slabs = F / kS3Slab;
   for (int nb = 1; nb <= 2; ++nb) {
-    if (M % (128 * nb) != 0 || (keep_order && nb == 1)) continue;
     const int passes = M / (128 * nb);
     for (int splits = 1; splits <= passes && splits <= kScoreSplitMax; ++splits) {
-      if (passes % splits != 0 || (splits > 1 && !may_split)) continue;
+      if (passes % splits != 0 || (splits == 1 ? nb == 1 : !may_split)) continue;
       for (int tt = 1; tt <= kS3MaxTT; ++tt) {
         const long long wgs = (long long)((tiles + tt - 1) / tt) * splits * n_layers;
-        // (a pass ends with about 1500 + 500 tt clocks of sums and activations; the launch that adds up the splits takes
-        // about 9000)
+        // (a pass ends with about 1500 + 500 tt clocks of sums and activations; the launch that takes shared units through
+        // the second layer costs about 18000, the wait for it included: 60 tokens of 768 features and 512 units, 23700
+        // clocks by this sum, lose 3 us when shared, 300 of 1536 features, 43300 clocks, gain 4)
         const long long cost = (wgs + cus - 1) / cus * (passes / splits) * (slabs * slab_cost(tt, nb) + 1500 + 500 * tt) +
-                               (splits > 1 ? 9000 : 0);
+                               (splits > 1 ? 18000 + (long long)T * M * n_layers / 1000 : 0);
         if (cost <= best_cost) { best_cost = cost; best = ScorePlan{tt, nb, splits}; }
       }
     }
   }
   return best;
 }
+// scratch of shared hidden units: the activations, rounded up to whole tiles of tokens, and the averaged second layers
+long long split_ld(int T) { return ((long long)T + 31) / 32 * 32; }
+size_t split_scratch_bytes(int T, int M, int n_layers) {
+  return (size_t)n_layers * M * ((size_t)split_ld(T) + 1) * sizeof(float);
+}
 
-template <int TT, int NB, int SELW>
+template <int TT, int NB, bool SPLIT, int SELW>
 int launch_stream(hipStream_t st, const ScoreArgs& a, int n_layers) {
   static LdsLimit lds_limit;
   int lds = s3_lds_bytes(TT, NB);
   if (SELW > 0 && lds < select_bitslice_lds_bytes(512)) lds = select_bitslice_lds_bytes(512);
-  const int rc = set_lds_limit(lds_limit, score_stream_kernel<TT, NB, SELW>, lds);
+  const int rc = set_lds_limit(lds_limit, score_stream_kernel<TT, NB, SPLIT, SELW>, lds);
   if (rc != PAFU_OK) return rc;
-  hipLaunchKernelGGL((score_stream_kernel<TT, NB, SELW>), dim3(a.groups * a.splits * n_layers + (SELW > 0 ? 1 : 0)), dim3(512),
-                     lds, st, a);
-  if (a.splits > 1) hipLaunchKernelGGL(score_sum_kernel, dim3((a.T + 255) / 256, n_layers), dim3(256), 0, st, a);
+  hipLaunchKernelGGL((score_stream_kernel<TT, NB, SPLIT, SELW>), dim3(a.groups * a.splits * n_layers + (SELW > 0 ? 1 : 0)),
+                     dim3(512), lds, st, a);
+  if (SPLIT) hipLaunchKernelGGL(score_sum_kernel, dim3((a.T + 31) / 32, n_layers), dim3(512), 0, st, a);
   return check_launch();
 }
-template <int NB>
+template <int TT, int NB, bool SPLIT>
+int launch_stream_sel(hipStream_t st, const ScoreArgs& a, int n_layers, int selw) {
+  if (selw == 2) return launch_stream<TT, NB, SPLIT, 2>(st, a, n_layers);
+  if (selw == 4) return launch_stream<TT, NB, SPLIT, 4>(st, a, n_layers);
+  return launch_stream<TT, NB, SPLIT, 0>(st, a, n_layers);
+}
+template <int NB, bool SPLIT>
 int launch_stream_tt(hipStream_t st, const ScoreArgs& a, int n_layers, int tt, int selw) {
-  if (tt == 1 && selw == 2) return launch_stream<1, NB, 2>(st, a, n_layers);
-  if (tt == 1 && selw == 4) return launch_stream<1, NB, 4>(st, a, n_layers);
-  if (tt == 2 && selw == 2) return launch_stream<2, NB, 2>(st, a, n_layers);
-  if (tt == 2 && selw == 4) return launch_stream<2, NB, 4>(st, a, n_layers);
-  if (tt == 3 && selw == 2) return launch_stream<3, NB, 2>(st, a, n_layers);
-  if (tt == 3 && selw == 4) return launch_stream<3, NB, 4>(st, a, n_layers);
-  if (tt == 4 && selw == 2) return launch_stream<4, NB, 2>(st, a, n_layers);
-  if (tt == 4 && selw == 4) return launch_stream<4, NB, 4>(st, a, n_layers);
-  if (tt == 5 && selw == 2) return launch_stream<5, NB, 2>(st, a, n_layers);
-  if (tt == 5 && selw == 4) return launch_stream<5, NB, 4>(st, a, n_layers);
   switch (tt) {
-    case 1: return launch_stream<1, NB, 0>(st, a, n_layers);
-    case 2: return launch_stream<2, NB, 0>(st, a, n_layers);
-    case 3: return launch_stream<3, NB, 0>(st, a, n_layers);
-    case 4: return launch_stream<4, NB, 0>(st, a, n_layers);
-    default: return launch_stream<5, NB, 0>(st, a, n_layers);
+    case 1: return launch_stream_sel<1, NB, SPLIT>(st, a, n_layers, selw);
+    case 2: return launch_stream_sel<2, NB, SPLIT>(st, a, n_layers, selw);
+    case 3: return launch_stream_sel<3, NB, SPLIT>(st, a, n_layers, selw);
+    case 4: return launch_stream_sel<4, NB, SPLIT>(st, a, n_layers, selw);
+    default: return launch_stream_sel<5, NB, SPLIT>(st, a, n_layers, selw);
   }
 }
 
 // the streaming kernel addresses rows by 32-bit byte offsets from a per-workgroup base
 bool stream_takes(const ScoreShape& s) {
   const long long F = (long long)s.n_seg * s.Fs;
-  return s.x_dtype == PAFU_BF16 && s.Fs % kS3Slab == 0 && s.M % (s.keep_order ? 256 : 128) == 0 && s.ld_x % 8 == 0 &&
+  return s.x_dtype == PAFU_BF16 && s.Fs % kS3Slab == 0 && s.M % 256 == 0 && s.ld_x % 8 == 0 &&
          32ll * kS3MaxTT * s.ld_x * 2 < (1ll << 31) && 256ll * F * 2 < (1ll << 31);
 }
 
@@ -809,19 +860,20 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
   a.n_layers = n_layers;
   a.groups = 0;
   a.splits = 1;
-  a.part = nullptr;
+  a.acts = a.w2bar = nullptr;
+  a.ld_acts = 0;
   a.ride = SelectJob{nullptr, nullptr, nullptr, 0, 0, 0};
   const bool stream = stream_takes(s);
-  ScorePlan plan{1, 1, 1};
+  ScorePlan plan{1, 2, 1};
   if (stream) {
-    const bool may_split = !s.keep_order && scratch != nullptr && (reinterpret_cast<uintptr_t>(scratch) & 3u) == 0 &&
-                           scratch_bytes >= (size_t)n_layers * kScoreSplitMax * s.T * sizeof(float);
-    plan = plan_score(s.T, a.F, s.M, n_layers, s.keep_order, may_split);
+    const bool may_split = scratch != nullptr && aligned16(scratch) && scratch_bytes >= split_scratch_bytes(s.T, s.M, n_layers);
+    plan = plan_score(s.T, a.F, s.M, n_layers, may_split);
   }
   // Who averages the output rows.  A kernel does it at the end of a pass, about 3 us for 12 rows, a launch of its own takes
-  // 4.7 us: in the kernel for several layers, for a single pass per workgroup and for the few units of the fp32 kernel
-  // (21840 tokens of 4608 features and 1024 units: 249 us with it in all four passes, 235 with the launch).
-  const bool own_rows = n_layers > 1 || (stream ? s.M / plan.splits == 128 * plan.nb : f32_takes(s));
+  // 4.7 us: in the kernel for several layers, for a single pass per workgroup, for shared units (where one token group does
+  // it for all) and for the few units of the fp32 kernel (21840 tokens of 4608 features and 1024 units: 249 us with it in
+  // all four passes, 235 with the launch).
+  const bool own_rows = n_layers > 1 || (stream ? plan.splits > 1 || s.M == 256 : f32_takes(s));
   if (s.n_out > 1 && !(own_rows && score_batchable(s))) {
     float* w = static_cast<float*>(fold_ws);
     ScoreLayer& first = a.layer[0];
@@ -835,7 +887,11 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
   if (stream) {
     a.groups = ((s.T + 31) / 32 + plan.tt - 1) / plan.tt;
     a.splits = plan.splits;
-    a.part = static_cast<float*>(scratch);
+    if (a.splits > 1) {
+      a.acts = static_cast<float*>(scratch);
+      a.ld_acts = split_ld(s.T);
+      a.w2bar = a.acts + (long long)n_layers * s.M * a.ld_acts;
+    }
     int selw = 0;
     // a selection rides along when the last round of workgroups leaves a CU for it (one more workgroup would otherwise be
     // a round of its own) and the list fits the 512-thread bit-sliced selection
@@ -845,7 +901,9 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
       selw = a.ride.n <= 512 * 32 * 2 ? 2 : 4;
       if (rode != nullptr) *rode = true;
     }
-    return plan.nb == 2 ? launch_stream_tt<2>(st, a, n_layers, plan.tt, selw) : launch_stream_tt<1>(st, a, n_layers, plan.tt, selw);
+    if (plan.splits == 1) return launch_stream_tt<2, false>(st, a, n_layers, plan.tt, selw);
+    return plan.nb == 2 ? launch_stream_tt<2, true>(st, a, n_layers, plan.tt, selw)
+                        : launch_stream_tt<1, true>(st, a, n_layers, plan.tt, selw);
   }
   if (mfma_takes(s)) {
     if (s.M % 128 == 0) return launch_mfma<4>(st, a, n_layers);

@@ -1,5 +1,5 @@
 """The ways a step's scoring is launched: hidden units of a token group shared by workgroups (rollout), layers that share a
-launch, and the kernels whose sums keep one order because a selection follows from them."""
+launch; and that none of them changes a bit of a score, because selections compare scores of different launches."""
 import numpy as np
 import pytest
 import torch
@@ -92,6 +92,38 @@ def test_scores_that_select_do_not_depend_on_the_launch(layers, n, Lc, N, D, M, 
         assert np.array_equal(bits(alone), bits(s[:n + Lc]))
         want = orc.smlp_score(np.concatenate(h[0], axis=1), *h[1:5])
         assert np.abs(host(alone) - want).max() <= 1e-5 * max(np.abs(want).max(), 1.0)
+
+
+@pytest.mark.parametrize("Lc,N,D,M,n_out,n_seg,bias", [
+    (700, 12, 128, 1024, 12, 3, True),   # eight workgroups share a token group
+    (2000, 4, 128, 512, 20, 1, True),    # more output rows than the kernels average themselves
+    (1100, 12, 128, 256, 1, 1, False),   # one pass of 256 units, or two halves of it
+    (333, 2, 64, 768, 16, 1, True),
+    (500, 2, 64, 384, 3, 2, True),       # a hidden layer that 256 does not divide
+    (300, 4, 64, 128, 1, 1, False),
+])
+def test_a_chunks_scores_are_those_of_any_other_launch(Lc, N, D, M, n_out, n_seg, bias):
+    """A rollout stores the chunk's scores among those of other chunks: bit for bit what pafu_score gives, with and without
+    scratch, for several layers in a launch, and for a shorter chunk of the same tokens."""
+    def launch(length, layers, ws):
+        args, held, fresh = _steps(B.PAFU_MODE_ROLLOUT, layers, 96, Lc, N, D, M, n_out, n_seg, bias)
+        for a in args:
+            a.Lc = length
+            if not ws:
+                a.workspace_bytes = (B.pafu_score_workspace_bytes(M) + 255) // 256 * 256
+        B.pafu_step(args[0]) if layers == 1 else B.pafu_step_layers(args)
+        torch.cuda.synchronize()
+        for h, s in zip(held, fresh):
+            alone, w = torch.empty(Lc, device=DEV), torch.empty(M + 4, device=DEV)
+            B.pafu_score(tuple(h[5]), h[14][0], h[14][1], h[14][2], h[14][3], alone, workspace=w)
+            torch.cuda.synchronize()
+            assert np.array_equal(bits(alone[:length]), bits(s[:length])), (length, layers, ws)
+            assert torch.all(s[length:] == -9.0)
+
+    for layers in (1, 3):
+        for ws in (True, False):
+            launch(Lc, layers, ws)
+    launch(Lc // 7, 1, True)
 
 
 @pytest.mark.parametrize("T,Fs,n_seg,M,n_out", [
