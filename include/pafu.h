@@ -304,7 +304,8 @@ int pafu_step(void* stream, const pafu_step_args* args /* host */);
  * n, k, N, D, the strides and the storage type; layer by layer otherwise), then attention (one launch for a stretch of
  * up to 32 layers of one geometry and workspace; such layers' stage events are recorded together).  Every layer
  * therefore needs its own scores, ids, SL_out, K_out, V_out and O buffers, and no layer's output may overlap
- * another layer's input (PAFU_ERR_ALIAS); only the workspace may be shared between layers. */
+ * another layer's input (PAFU_ERR_ALIAS); only the workspace may be shared between layers.  A workspace whose optional
+ * part reaches into a tensor of any layer is accepted, but that part is then not used. */
 int pafu_step_layers(void* stream, const pafu_step_args* args /* host array */, int n_layers);
 
 /* pafu_step_layers_shared - the paper's own multi-layer arrangement (Sec. 3.3: the Salience Estimation Head sits on

@@ -320,12 +320,30 @@ WsPart attention_ws(const pafu_step_args* a, bool scoring) {
   return WsPart{static_cast<char*>(a->workspace) + used, a->workspace_bytes - used};
 }
 
+// The workspace that layer l of a multi-layer step brings or (with shared indices) borrows from the index layer.
+const pafu_step_args* layers_ws_owner(const pafu_step_args* args, int index_layer, int l) {
+  return args[l].workspace == nullptr && index_layer >= 0 ? &args[index_layer] : &args[l];
+}
+// Its attention part.  None if it reaches into any layer's tensors: what a layer may overlap is checked within the layer
+// only, and here stages of other layers run before and behind the ones that write the workspace.
+WsPart layers_ws(const pafu_step_args* args, int n_layers, int index_layer, int l) {
+  const pafu_step_args* owner = layers_ws_owner(args, index_layer, l);
+  const WsPart part = attention_ws(owner, index_layer < 0 || owner == &args[index_layer]);
+  const Span ws{part.p, 1, 0, (long long)part.bytes};
+  for (int m = 0; m < n_layers && part.p != nullptr; ++m) {
+    StepSpans s;
+    step_spans(&args[m], index_layer < 0 || m == index_layer, s);
+    for (int i = 0; i < s.n_in; ++i)
+      if (spans_overlap(ws, s.in[i])) return WsPart{nullptr, 0};
+    for (int i = 0; i < s.n_out; ++i)
+      if (spans_overlap(ws, s.out[i])) return WsPart{nullptr, 0};
+  }
+  return part;
+}
+
 // The scoring part of a step: SINGLE scores cache + chunk into a->scores, ROLLOUT the chunk into SL_out behind the
 // retained rows.  Both read the head's weights.  A rollout's chunk is a launch too short to fill the chip by its tokens:
 // it gets the attention's part of the workspace, idle until then, as scratch for sharing its hidden units.
-WsPart score_scratch_ws(const pafu_step_args* a) {
-  return a->mode == PAFU_MODE_SINGLE ? WsPart{nullptr, 0} : attention_ws(a, true);
-}
 ScoreShape score_shape(const pafu_step_args* a, int T) {
   return ScoreShape{a->n_seg, T, a->Fs, a->ld_x, a->x_dtype, a->M, a->n_out, a->act};
 }
@@ -350,13 +368,13 @@ ScoreLayer one_launch_layer(const pafu_step_args* a) {
   return score_layer(a, a->x_chunk, single ? a->scores + a->n : a->SL_out + (a->k < a->n ? a->k : a->n));
 }
 
-// `selected` (may be null): in ROLLOUT the selection reads the stored list only, so it may ride in the scoring launch;
+// `scratch`: the attention's part of the workspace.  `selected` (may be null): in ROLLOUT the selection reads the stored list only, so it may ride in the scoring launch;
 // set when it did and the caller has no selection left to launch.
-int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nullptr) {
+int enqueue_scores(hipStream_t st, const pafu_step_args* a, WsPart scratch, bool* selected = nullptr) {
   if (selected != nullptr) *selected = false;
   int rc = record_stage(st, a, 0);
   if (rc) return rc;
-  const WsPart scratch = score_scratch_ws(a);
+  if (a->mode == PAFU_MODE_SINGLE) scratch = WsPart{nullptr, 0};
   if (scores_in_one_launch(a)) {
     const SelectJob job{a->SL_in, a->ids, nullptr, a->n, a->k, a->n_pinned};
     const bool may_ride = selected != nullptr && a->mode != PAFU_MODE_SINGLE && a->n > 0;
@@ -374,7 +392,7 @@ int enqueue_scores(hipStream_t st, const pafu_step_args* a, bool* selected = nul
   return record_stage(st, a, 1);
 }
 
-// Can the scoring of these two layers share a launch?  (One workspace: what it may overlap is checked within its layer.)
+// Can the scoring of these two layers share a launch?
 bool same_scoring(const pafu_step_args* a, const pafu_step_args* b) {
   return a->mode == b->mode && a->workspace == b->workspace && a->workspace_bytes == b->workspace_bytes &&
          scores_in_one_launch(b) && one_launch_tokens(a) == one_launch_tokens(b) && a->n_seg == b->n_seg &&
@@ -391,12 +409,12 @@ int enqueue_layers_scores(hipStream_t st, const pafu_step_args* args, int n_laye
     last = first + 1;
     if (scores_in_one_launch(a) && score_batchable(shape))
       while (last < n_layers && last - first < kScoreBatchMax && same_scoring(a, &args[last])) ++last;
+    const WsPart scratch = a->mode == PAFU_MODE_SINGLE ? WsPart{nullptr, 0} : layers_ws(args, n_layers, -1, first);
     if (last == first + 1) {
-      if ((rc = enqueue_scores(st, a))) return rc;
+      if ((rc = enqueue_scores(st, a, scratch))) return rc;
       continue;
     }
     ScoreLayer layers[kScoreBatchMax];
-    const WsPart scratch = score_scratch_ws(a);
     for (int l = first; l < last; ++l) {
       layers[l - first] = one_launch_layer(&args[l]);
       if ((rc = record_stage(st, &args[l], 0))) return rc;
@@ -504,15 +522,16 @@ bool same_attention(const pafu_step_args* a, const pafu_step_args* b) {
 // list serve all of them, and whose workspace a layer without one borrows.
 int enqueue_layers_kv(hipStream_t st, const pafu_step_args* args, int n_layers, int index_layer, int done_batch) {
   const pafu_step_args* idx = index_layer >= 0 ? &args[index_layer] : nullptr;
-  // (layers that bring different workspaces stay apart: what a workspace may overlap is only checked within its layer)
-  auto ws_of = [&](const pafu_step_args* a) { return a->workspace == nullptr && idx != nullptr ? idx->workspace : a->workspace; };
+  auto same_ws = [&](int l, int m) {
+    const pafu_step_args *a = layers_ws_owner(args, index_layer, l), *b = layers_ws_owner(args, index_layer, m);
+    return a->workspace == b->workspace && a->workspace_bytes == b->workspace_bytes;
+  };
   int rc;
   for (int first = 0, last; first < n_layers; first = last) {
     for (last = first + 1; last < n_layers && last - first < kAttnBatchMax && same_attention(&args[first], &args[last]) &&
-                           ws_of(&args[first]) == ws_of(&args[last]);)
+                           same_ws(first, last);)
       ++last;
     int done[kAttnBatchMax];
-    WsPart ws{nullptr, 0};
     for (int l = first; l < last; ++l) {
       const pafu_step_args* a = &args[l];
       const bool scores = idx == nullptr || l == index_layer;
@@ -521,10 +540,8 @@ int enqueue_layers_kv(hipStream_t st, const pafu_step_args* args, int n_layers, 
                          scores ? (a->mode == PAFU_MODE_SINGLE ? a->scores : a->SL_in) : nullptr,
                          scores ? a->SL_out : nullptr, &done[l - first]);
       if (rc) return rc;
-      const WsPart own = attention_ws(a, scores);
-      if (own.bytes > ws.bytes) ws = own;
     }
-    if (ws.p == nullptr && idx != nullptr) ws = attention_ws(idx, true);
+    const WsPart ws = layers_ws(args, n_layers, index_layer, first);
     rc = enqueue_attention(st, &args[first], last - first, ws.p, ws.bytes);
     if (rc) return rc;
     for (int l = first; l < last; ++l)
@@ -535,7 +552,8 @@ int enqueue_layers_kv(hipStream_t st, const pafu_step_args* args, int n_layers, 
 
 int enqueue_step(hipStream_t st, const pafu_step_args* a) {
   bool selected = false;
-  int rc = enqueue_scores(st, a, &selected);
+  const WsPart ws = attention_ws(a, true);
+  int rc = enqueue_scores(st, a, ws, &selected);
   if (rc) return rc;
   const float* sel_scores = a->mode == PAFU_MODE_SINGLE ? a->scores : a->SL_in;
   if (a->n > 0 && !selected) {
@@ -544,7 +562,6 @@ int enqueue_step(hipStream_t st, const pafu_step_args* a) {
   }
   rc = record_stage(st, a, 2);
   if (rc) return rc;
-  const WsPart ws = attention_ws(a, true);
   return enqueue_kv(st, a, a->ids, sel_scores, a->SL_out, ws.p, ws.bytes);
 }
 
@@ -880,7 +897,7 @@ int pafu_step_layers_shared(void* stream, const pafu_step_args* args, int n_laye
   // ROLLOUT selects on the stored list, so the indices exist before any layer runs; the chunk's own scores are only
   // needed for the append.  SINGLE scores first.  Either way: scores, one selection, then every layer's cache.
   bool selected = false;
-  rc = enqueue_scores(st, idx, &selected);
+  rc = enqueue_scores(st, idx, layers_ws(args, n_layers, index_layer, index_layer), &selected);
   if (rc) return rc;
   const float* sel_scores = idx->mode == PAFU_MODE_SINGLE ? idx->scores : idx->SL_in;
   if (idx->n > 0 && !selected) {

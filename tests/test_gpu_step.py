@@ -10,7 +10,7 @@ import torch
 from oracle import pafu_oracle as orc
 from paper_2601_21896_amd import binding as B
 from paper_2601_21896_amd import workloads as wl
-from tests.gpu_util import ATTN_MAX_ABS, ATTN_REL_FRO, DEV, SCORE_MAX_ABS, attn_errors, dev, host
+from tests.gpu_util import ATTN_MAX_ABS, ATTN_REL_FRO, DEV, SCORE_MAX_ABS, attn_errors, dev, host, step_workspace
 
 pytestmark = pytest.mark.gpu
 
@@ -342,3 +342,72 @@ def test_step_layers_rollout_independent_indices():
         n = n_kept + Lc
         cur = 1 - cur
     assert n == k + Lc
+
+
+# ------------------------------------------------------------------ workspaces of multi-layer steps
+def _two_rollout_layers(N, D, n, Lc, M, n_out):
+    """Two rollout layers (arguments, tensors that they write), each with a workspace of its own."""
+    rng = np.random.Generator(np.random.PCG64(n + Lc))
+    draw = lambda *s: rng.standard_normal(s, dtype=np.float32)
+    args, outs = [], []
+    for _ in range(2):
+        k = n // 2
+        kv = [dev(draw(r, N, D), "bf16") for r in (n, n, Lc, Lc, Lc)]
+        out = [torch.zeros(k, dtype=torch.int32, device=DEV)] + [
+            torch.zeros(k + Lc, N, D, device=DEV, dtype=torch.bfloat16) for _ in range(2)] + [
+            torch.zeros(k + Lc, device=DEV), torch.zeros(Lc, N, D, device=DEV, dtype=torch.bfloat16)]
+        a = B.make_step_args(B.PAFU_MODE_ROLLOUT, N, D, n, Lc, k, Lc, None, dev(draw(Lc, N * D), "bf16"),
+                             dev(draw(M, N * D) * np.float32(0.05), "bf16"), None, dev(draw(n_out, M)), None, kv[0],
+                             kv[1], dev(draw(n)), kv[2], kv[3], kv[4], None, out[0], out[1], out[2], out[3], out[4])
+        step_workspace(a)
+        args.append(a)
+        outs.append(out)
+    return args, outs
+
+
+@pytest.mark.parametrize("shared", [False, True])
+def test_a_layers_workspace_may_reach_into_a_later_layer(shared):
+    # accepted, though of no use: features, queries and K of layer 1 lie in the optional part of layer 0's workspace
+    N, D, n, Lc, M = 12, 128, 900, 600, 1024
+    args, outs = _two_rollout_layers(N, D, n, Lc, M, 3)
+    run = (lambda: B.pafu_step_layers_shared(args, 0)) if shared else (lambda: B.pafu_step_layers(args))
+    run()
+    torch.cuda.synchronize()
+    want = [[host(t).copy() for t in out] for out in outs]
+    ws, a = args[0]._keep_ws, args[1]
+    at = (B.pafu_score_workspace_bytes(M) + 255) // 256 * 256
+    size = Lc * N * D * 2
+    for field, t in (("Q", a._keep[9]), ("K_chunk", a._keep[10]), ("x", a._keep[1][0])):
+        ws[at:at + size] = t.contiguous().view(torch.uint8).view(-1)
+        if field == "x":
+            a.x_chunk[0] = ws.data_ptr() + at
+        else:
+            setattr(a, field, ws.data_ptr() + at)
+        at += size
+    for out in outs:
+        for t in out:
+            t.zero_()
+    run()
+    torch.cuda.synchronize()
+    for l, out in enumerate(outs):
+        for i, t in enumerate(out):
+            if i == 4:  # attention may be cut or not: equal up to the softmax weights' rounding
+                assert max(attn_errors(host(t), want[l][i])) < ATTN_MAX_ABS
+            else:
+                assert np.array_equal(host(t), want[l][i]), (l, i)
+
+
+def test_layers_with_one_workspace_of_different_sizes_use_their_own():
+    # layer 0 brings only the scoring part of the buffer: its attention may not use what lies behind
+    args, outs = _two_rollout_layers(2, 128, 6000, 100, 256, 3)
+    args[0].workspace, args[0].workspace_bytes = args[1].workspace, (B.pafu_score_workspace_bytes(256) + 255) // 256 * 256
+    alone = []
+    for a, out in zip(args, outs):
+        B.pafu_step(a)
+        torch.cuda.synchronize()
+        alone.append(host(out[4]).copy())
+        out[4].zero_()
+    B.pafu_step_layers(args)
+    torch.cuda.synchronize()
+    for out, want in zip(outs, alone):
+        assert np.array_equal(host(out[4]), want)
