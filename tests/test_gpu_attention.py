@@ -146,6 +146,25 @@ def test_attention_running_maximum_outgrown(D, case):
         assert np.isnan(got[bad]).all()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bits,stairs", [(20, 1), (26, 1), (95, 1), (104, 1), (300, 1), (30, 5), (110, 5)])
+def test_attention_reference_raised_by(D, bits, stairs):
+    # scores that jump by up to `bits` powers of two (less for the first queries) once or in every further tile: below the
+    # limit of 2^24, scaled by a power of two (up to 2^100), or computed once more
+    n, Lc, N = 384, 96, 2
+    Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=D + bits + stairs)
+    gain = np.linspace(0.1, 1.0, Lc, dtype=np.float32)[:, None, None]
+    step = np.float32(bits / (np.log2(np.e) * np.sqrt(D)))
+    level = np.clip(np.arange(n) // 64 - 2 if stairs == 1 else np.arange(n) // 64, 0, stairs)
+    Q = wl.round_to_bf16(Q * np.float32(0.3) + gain)
+    Kc = wl.round_to_bf16(Kc * np.float32(0.3) + (step * level)[:, None, None].astype(np.float32))
+    Kn = wl.round_to_bf16(Kn * np.float32(0.3) + step * np.float32(stairs))
+    want = orc.chunk_attention(Q, Kc, Vc, Kn, Vn, block_len=Lc)
+    got = _run(Q, Kc, Vc, Kn, Vn, Lc, out_dtype=torch.float32)
+    max_abs, rel = attn_errors(got, want)
+    assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
+
+
 def test_attention_strided_slabs():
     # cache rows live in a slab with spare capacity and a wider token stride
     n, Lc, N, D = 150, 70, 2, 64
