@@ -41,7 +41,9 @@ constexpr int kSseXcds = 8;
 
 // a tile's c values are read one step after its rows, so their ring is deeper
 constexpr int kSseCStages = 8;
-constexpr float kSseMaxTileSum = 256.0f;  // above 32, so that a raised maximum always settles a tile
+// 32 weights of a lane that sum up to more raise its reference (an exponent rounds by its size, so the large weights are
+// kept near 1; a raise is a few instructions), and beyond 2^100, where some may be infinite, they are computed once more
+constexpr float kSseMaxTileSum = 256.0f, kSseMaxScaledSum = 1.2676506e30f;
 
 constexpr int sse_lds_bytes(int D) { return kSseStages * kSseTile * 2 * D + kSseCStages * kSseTile * 4; }
 
@@ -89,13 +91,15 @@ __device__ __forceinline__ void wait_vmcnt() {
 //
 // The loop is software-pipelined inside a wave: step t issues the matrix instructions of tile t+1 and after each of them
 // a slice of the reduction of tile t, because on this chip the two pipes overlap reliably only for instructions of one
-// wave.  rowstat does not look for the maximum of a tile: weights are relative to the largest score of the tiles before,
-// and a lane whose 32 weights sum up to more than kSseMaxTileSum raises it out of line (the result is mathematically
-// unchanged; the fp32 sums have the same relative precision at any scale).  The reference is a whole number, so that it
+// wave.  rowstat does not look for the maximum of a tile: weights are relative to the largest score of the first tile,
+// and a lane whose 32 weights sum up to more than kSseMaxTileSum raises it out of line, by the power of two in the sum (the
+// result is mathematically unchanged; the fp32 sums have the same relative precision at any scale).  The reference is a whole number, so that it
 // rounds nothing where the logarithm of the sum is added to it.
 // What bounds it: the issue slots that the matrix instructions share with the exponentials (rowstat) or with one fma and
 // half a three-way maximum per score (colmax), at the clock that the power limit leaves.  32760 tokens, 12 heads of 128:
 // the same passes one after the other (product, then reduction) 5990 us, pipelined 5242 (1100 -> 1260 TFLOP/s).
+// Raised references cost little: 12000 tokens, 8 heads of 64, 380 us; keys growing sixteenfold 394, NaN rows 388 (494 and 572
+// when a raise computed the weights once more).
 template <int D, bool COLMAX, int HT>
 __global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
   constexpr int ROWB = 2 * D;               // bytes per row of one head
@@ -264,20 +268,30 @@ __global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
     }
     if (!COLMAX) {
       acc[HT - 1] += held_back;
-      bool over = false;
+      float most = acc[0];
 #pragma unroll
-      for (int ht = 0; ht < HT; ++ht) over = over || !(acc[ht] <= kSseMaxTileSum);
-      if (__builtin_amdgcn_ballot_w64(over) != 0) {  // a tile outgrew the maximum (or met a NaN)
+      for (int ht = 1; ht < HT; ++ht) most = fmaxf(most, acc[ht]);  // (a NaN goes on as it is: so does its row's result)
+      if (__builtin_amdgcn_ballot_w64(most > kSseMaxTileSum) != 0) {
+        if (__builtin_amdgcn_ballot_w64(most > kSseMaxScaledSum) != 0) {  // far above (the first keys that a half sees)
+#pragma unroll
+          for (int ht = 0; ht < HT; ++ht) {
+            const float m_new = fmaxf(m_run[ht], ceilf(tile_max(s_cur[ht]) * sc));  // sc > 0
+            l_run[ht] *= __builtin_amdgcn_exp2f(m_run[ht] - m_new);
+            m_run[ht] = m_new;
+            acc[ht] = 0.f;
+#pragma unroll
+            for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) acc[ht] += __builtin_amdgcn_exp2f(fmaf(s_cur[ht][rb][r], sc, -m_new));
+          }
+        }
 #pragma unroll
         for (int ht = 0; ht < HT; ++ht) {
-          const float m_new = fmaxf(m_run[ht], ceilf(tile_max(s_cur[ht]) * sc));  // sc > 0
-          l_run[ht] *= __builtin_amdgcn_exp2f(m_run[ht] - m_new);
-          m_run[ht] = m_new;
-          acc[ht] = 0.f;
-#pragma unroll
-          for (int rb = 0; rb < 2; ++rb)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[ht] += __builtin_amdgcn_exp2f(fmaf(s_cur[ht][rb][r], sc, -m_new));
+          const float up = acc[ht] > kSseMaxTileSum ? (float)__builtin_amdgcn_frexp_expf(acc[ht]) : 0.f;
+          const float scale = __builtin_amdgcn_exp2f(-up);
+          m_run[ht] += up;
+          l_run[ht] *= scale;
+          acc[ht] *= scale;
         }
       }
 #pragma unroll

@@ -88,6 +88,21 @@ def test_sse_item_sizes_and_growing_scores(L, N, D, L_B, ramp):
     assert np.all(np.abs(got - want) <= RTOL * np.abs(want) + ATOL), np.abs(got - want).max()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("bits,stairs", [(7, 1), (40, 1), (98, 1), (104, 1), (30, 6)])
+def test_sse_reference_raised_by(D, bits, stairs):
+    """Scores that jump by up to `bits` powers of two, once or in every tile: around the limit of a tile's sum, scaled by a
+    power of two, or computed once more.  |z| < 200 is held by fp32 to 2^-17, 6e-6 in the weight: inside the bound."""
+    L, N = 448, 2
+    Q, K = _qk(L, N, D, seed=bits + D)
+    step = np.float32(bits / (np.log2(np.e) * np.sqrt(D)))
+    level = np.clip(np.arange(L) // 64 - 2 if stairs == 1 else np.arange(L) // 64, 0, stairs)[:, None, None]
+    Q = wl.round_to_bf16(Q * np.float32(0.3) + np.linspace(0.1, 1.0, L, dtype=np.float32)[:, None, None])
+    K = wl.round_to_bf16(K * np.float32(0.3) + (step * level).astype(np.float32))
+    got, want = _run(Q, K, 150), orc.sse_score(Q, K, 150)
+    assert np.all(np.abs(got - want) <= RTOL * np.abs(want) + ATOL), np.abs(got - want).max()
+
+
 def test_sse_strided_inputs_and_explicit_scale():
     Q, K = _qk(400, 2, 128, seed=9)
     got = _run(Q, K, 100, scale=0.05, pad=24)
