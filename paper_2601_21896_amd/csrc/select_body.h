@@ -154,32 +154,32 @@ __device__ __forceinline__ void select_bitslice_body(const SelectProblem& P) {
   // their k-th key from its neighbour (about 17 of 32 for 256 scores), equal ones at the k-th place take all passes.
   // (Entries past the end are candidates only while no key is below the candidates; then there are more of them than
   // places, because k < n.)
-  // 256 scores 10.1 -> 7.1 us.  Only for one word per thread: with more, the branches of the unrolled passes cost more
-  // than they save (32760 scores, two words: 20 -> 29 us).
+  // Looked at in front of three passes only: 1000 scores of a normal distribution 9.5 -> 7.3 us, equal ones 10.6 -> 10.7,
+  // ones that differ in their last bits 9.5 -> 9.8 (a look in front of every pass: 7.4, 12.3, 11.1).  Only for one word per
+  // thread: with more, the branches of the unrolled passes cost more than they save (32760 scores, two words: 20 -> 29 us).
   uint32_t cand[W], gt[W];
 #pragma unroll
   for (int w = 0; w < W; ++w) { cand[w] = 0xffffffffu; gt[w] = 0u; }
-  int remaining = P.k, candidates = NT * 32 * W;
+  int missing = -P.k;                // minus the places that the candidates fill
+  int surplus = NT * 32 * W - P.k;   // candidates that get none
 #pragma unroll
   for (int p = 31; p >= 0; --p) {
-    if (W == 1 && candidates == remaining) break;
+    if (W == 1 && (p == 19 || p == 15 || p == 11) && __builtin_amdgcn_readfirstlane(surplus) == 0) break;
     int cnt = 0;
 #pragma unroll
     for (int w = 0; w < W; ++w) cnt += __builtin_popcount(cand[w] & plane[w][p]);
     const int wsum = wave_sum(cnt);
     if (lane == 0) part[(p & 1) * kWaves + wave] = wsum;
     __syncthreads();
-    int total = 0;
+    int over = missing;  // candidates with the bit set, minus the places
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) total += part[(p & 1) * kWaves + i];
-    if (W == 1) total = __builtin_amdgcn_readfirstlane(total);
-    if (total >= remaining) {  // the k-th key has this bit set
-      candidates = total;
+    for (int i = 0; i < kWaves; ++i) over += part[(p & 1) * kWaves + i];
+    if (over >= 0) {  // the k-th key has this bit set
+      surplus = over;
 #pragma unroll
       for (int w = 0; w < W; ++w) cand[w] &= plane[w][p];
     } else {  // it does not: candidates with the bit set are above it
-      remaining -= total;
-      candidates -= total;
+      missing = over;
 #pragma unroll
       for (int w = 0; w < W; ++w) {
         gt[w] |= cand[w] & plane[w][p];
@@ -187,9 +187,9 @@ __device__ __forceinline__ void select_bitslice_body(const SelectProblem& P) {
       }
     }
   }
-  // now cand = keys that match the k-th key as far as it was looked at, gt = keys above, remaining = how many of cand are
-  // kept (>= 1): all, or the first ones of equal keys
-  const uint32_t need_eq = (uint32_t)remaining;
+  // now cand = keys that match the k-th key as far as it was looked at, gt = keys above, -missing = how many of cand
+  // are kept (>= 1): all, or the first ones of equal keys
+  const uint32_t need_eq = (uint32_t)-missing;
 
   // Ranks in index order = word by word, thread by thread inside a word: one block-wide exclusive scan of
   // (#above, #equal) per word, carried over the words.

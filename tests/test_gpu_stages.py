@@ -169,6 +169,20 @@ def test_select_special_values_in_long_lists(n):
         assert np.array_equal(_run_select(s, k), orc.select_topk(s, k)), (n, k)
 
 
+@pytest.mark.parametrize("bit", [21, 20, 19, 18, 16, 15, 14, 12, 11, 10, 0])
+def test_select_ends_at_the_bit_that_tells_the_kth_key(bit):
+    # the k-th key and the next one differ in this bit first, or are equal; entries past the end must never be kept
+    for n, k in ((5, 2), (8, 7), (200, 100), (8192, 4097)):
+        lo = np.array([0x3f800000], dtype=np.uint32).view(np.float32)[0]
+        hi = np.array([0x3f800000 | 1 << bit], dtype=np.uint32).view(np.float32)[0]
+        rng = np.random.default_rng(n + bit)
+        for above in (k, k - 1, k + 1):
+            s = np.full(n, lo, np.float32)
+            s[rng.permutation(n)[:above]] = hi
+            for t in (s, -s):
+                assert np.array_equal(_run_select(t, k), orc.select_topk(t, k)), (n, k, above)
+
+
 def test_select_is_deterministic_across_runs():
     rng = np.random.default_rng(0)
     s = (rng.integers(0, 3, size=32760)).astype(np.float32)
