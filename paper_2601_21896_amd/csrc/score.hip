@@ -62,6 +62,7 @@ struct ScoreArgs {
   long long ld_x;
   int M, act;
   int n_out;    // rows of W2 / b2 that the kernel averages itself (1: W2 / b2 are one row, folded or as given)
+  float inv_out;
   int n_layers;
   int groups;   // token groups of a layer
   int splits;   // workgroups that share the hidden units of one token group; above 1 they write their activations
@@ -72,22 +73,32 @@ struct ScoreArgs {
   ScoreLayer layer[kScoreBatchMax];
 };
 
+// The layer that a workgroup works on.  Arguments are read from memory where they are used, and a launch starts with as many
+// round trips as the code in front of its first load has steps (six were 1 us of 13.5: 4680 tokens, 1536 features, 256
+// units).  So everything that one layer needs is asked for at once, and only further layers go through the table.
+__device__ __forceinline__ ScoreLayer layer_args(const ScoreArgs& A, int li) {
+  ScoreLayer L = A.layer[0];
+  asm volatile("" ::"s"(A.T), "s"(A.Fs), "s"(A.F), "s"(A.ld_x), "s"(A.M), "s"(A.act), "s"(A.n_out), "s"(A.inv_out), "s"(L.x[0]),
+               "s"(L.x[1]), "s"(L.x[2]), "s"(L.W1), "s"(L.b1), "s"(L.W2), "s"(L.b2), "s"(L.out), "s"(A.n_layers), "s"(A.groups),
+               "s"(A.splits));
+  if (li > 0) L = A.layer[li];
+  return L;
+}
+
 // averaged second layer of 4 hidden units from m on, in the order of fold_w2_kernel
-__device__ __forceinline__ float4 folded_w2(const float* __restrict__ W2, int M, int n_out, int m) {
-  if (n_out == 1) return *reinterpret_cast<const float4*>(W2 + m);
+__device__ __forceinline__ float4 averaged_w2(const float* __restrict__ W2, int M, int n_out, float inv, int m) {
   float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
   for (int o = 0; o < n_out; ++o) {
     const float4 w = *reinterpret_cast<const float4*>(W2 + (long long)o * M + m);
     s.x += w.x; s.y += w.y; s.z += w.z; s.w += w.w;
   }
-  const float inv = 1.0f / (float)n_out;
   return make_float4(s.x * inv, s.y * inv, s.z * inv, s.w * inv);
 }
-__device__ __forceinline__ float folded_b2(const float* __restrict__ b2, int n_out) {
+__device__ __forceinline__ float folded_b2(const float* __restrict__ b2, int n_out, float inv) {
   if (b2 == nullptr) return 0.f;
   float s = 0.f;
   for (int o = 0; o < n_out; ++o) s += b2[o];
-  return s * (1.0f / (float)n_out);
+  return s * inv;
 }
 
 // Second layer of a token whose hidden units were shared by several workgroups.  One wave per (unit quarter, half) and 32
@@ -95,7 +106,7 @@ __device__ __forceinline__ float folded_b2(const float* __restrict__ b2, int n_o
 // order, and the lane halves and the eight waves are added in the same order too.
 __global__ __launch_bounds__(512) void score_sum_kernel(ScoreArgs a) {
   __shared__ float red[8 * 32];
-  const ScoreLayer& L = a.layer[blockIdx.y];
+  const ScoreLayer L = layer_args(a, blockIdx.y);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, g = lane >> 5, c = lane & 31;
   const int t = blockIdx.x * 32 + c;
   const int m_wave = 64 * (wave & 3) + 32 * (wave >> 2) + 4 * g;
@@ -123,7 +134,7 @@ __global__ __launch_bounds__(512) void score_sum_kernel(ScoreArgs a) {
   if (g == 0) red[wave * 32 + c] = partial;
   __syncthreads();
   if (threadIdx.x < 32 && t < a.T) {
-    float v = folded_b2(L.b2, a.n_out);
+    float v = folded_b2(L.b2, a.n_out, a.inv_out);
 #pragma unroll
     for (int w = 0; w < 8; ++w) v += red[w * 32 + c];
     L.out[t] = v;
@@ -258,7 +269,7 @@ __global__ __launch_bounds__(256) void score_f32_kernel(ScoreArgs A) {
           w2 = L.W2[m];
         } else {
           for (int o = 0; o < A.n_out; ++o) w2 += L.W2[(long long)o * A.M + m];
-          w2 *= 1.0f / (float)A.n_out;
+          w2 *= A.inv_out;
         }
         partial = fmaf(w2, act_accurate(h[u], A.act), partial);
       }
@@ -268,7 +279,7 @@ __global__ __launch_bounds__(256) void score_f32_kernel(ScoreArgs A) {
   partial += __shfl_xor(partial, 4);
   partial += __shfl_xor(partial, 2);
   partial += __shfl_xor(partial, 1);
-  if (ml == 0 && t < A.T) L.out[t] = partial + folded_b2(L.b2, A.n_out);
+  if (ml == 0 && t < A.T) L.out[t] = partial + folded_b2(L.b2, A.n_out, A.inv_out);
 }
 
 // ---------------------------------------------------------------------------------- MFMA path
@@ -288,7 +299,7 @@ __device__ __forceinline__ float fast_silu(float h) {
 // MB = 32-row hidden blocks per pass over X (MB*32 hidden units are accumulated at once); one layer per blockIdx.y.
 template <int MB>
 __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) {
-  const ScoreLayer& L = A.layer[blockIdx.y];
+  const ScoreLayer L = layer_args(A, blockIdx.y);
   const unsigned short* const x0 = static_cast<const unsigned short*>(L.x[0]);
   const unsigned short* const x1 = static_cast<const unsigned short*>(L.x[1]);
   const unsigned short* const x2 = static_cast<const unsigned short*>(L.x[2]);
@@ -363,13 +374,13 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) 
     }
     // activation and second layer for this pass's hidden units; lane holds token c, units
     // mp + 32 b + 8 (r/4) + 4 g + (r%4)
+    auto second_layer = [&](auto w2_of) {
 #pragma unroll
-    for (int b = 0; b < kScMBlocks; ++b) {
-      {
+      for (int b = 0; b < kScMBlocks; ++b) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int m0 = mp + 32 * b + 8 * q + 4 * g;
-          const float4 w = folded_w2(L.W2, M, A.n_out, m0);
+          const float4 w = w2_of(m0);
           float4 bb = make_float4(0.f, 0.f, 0.f, 0.f);
           if (b1 != nullptr) bb = *reinterpret_cast<const float4*>(b1 + m0);
           const float h0 = acc[b][4 * q + 0] + bb.x, h1 = acc[b][4 * q + 1] + bb.y;
@@ -387,12 +398,14 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) 
           }
         }
       }
-    }
+    };
+    if (A.n_out == 1) second_layer([&](int m) { return *reinterpret_cast<const float4*>(L.W2 + m); });
+    else second_layer([&](int m) { return averaged_w2(L.W2, M, A.n_out, A.inv_out, m); });
   }
 #undef PAFU_LOAD_SLAB
 #undef PAFU_STORE_SLAB
   partial += __shfl_xor(partial, 32);
-  if (g == 0 && tok < T) L.out[tok] = partial + folded_b2(L.b2, A.n_out);
+  if (g == 0 && tok < T) L.out[tok] = partial + folded_b2(L.b2, A.n_out, A.inv_out);
 }
 
 // ---------------------------------------------------------------------------------- streaming MFMA path
@@ -427,6 +440,7 @@ constexpr int s3_stage_bytes(int TT, int NB) { return s3_w_bytes(NB) + 32 * TT *
 constexpr int s3_lds_bytes(int TT, int NB) {
   return kS3Stages * s3_stage_bytes(TT, NB) > kS3RedBytes ? kS3Stages * s3_stage_bytes(TT, NB) : kS3RedBytes;
 }
+static_assert(s3_lds_bytes(1, 2) >= kS3RedBytes + 256 * 4, "room for a pass's averaged second layer behind the two regions");
 // chunk q of row r lives in slot q ^ swz(r): 16 consecutive rows of one chunk then cover all 64 banks
 __device__ __forceinline__ int s3_swz(int row) {
   return kS3RowB == 64 ? (row >> 2) & 3 : (row >> 1) & 7;
@@ -448,7 +462,9 @@ __device__ __forceinline__ void s3_wait_vmcnt() {
 // threads) on a list that does not depend on this launch's scores: the stored score list of a rollout step.  A
 // selection keeps one CU busy for about as long as the scoring of a chunk takes the others, so carried along it
 // costs nothing, where a launch of its own would leave the rest of the chip idle meanwhile.
-template <int TT, int NB, bool SPLIT, int SELW>
+// OWN_ROWS: the kernel averages the rows of the second layer (n_out > 1).  A variant of its own, because the choice at run
+// time kept the one row's loads from overlapping the activations (1 us of 13.5).
+template <int TT, int NB, bool SPLIT, bool OWN_ROWS, int SELW>
 __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   static_assert(SPLIT || NB == 2, "the order of a score's sums is that of passes of 256 units");
   int id = blockIdx.x;
@@ -462,6 +478,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   // Workgroups are handed to the 8 XCDs in turn: the splits of a token group are 8 apart, so that one L2 serves its
   // features to all of them.
   // (no divisions in front of the first load where one layer and no splits make them needless)
+  ScoreLayer L = layer_args(A, 0);
   const int per_layer = A.groups * A.splits;
   int li = 0;
   if (A.n_layers > 1) li = id / per_layer;
@@ -478,7 +495,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
       split = r / left;
     }
   }
-  const ScoreLayer& L = A.layer[li];
+  if (A.n_layers > 1) L = A.layer[li];
   const unsigned short* const x0 = static_cast<const unsigned short*>(L.x[0]);
   const unsigned short* const x1 = static_cast<const unsigned short*>(L.x[1]);
   const unsigned short* const x2 = static_cast<const unsigned short*>(L.x[2]);
@@ -631,12 +648,15 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
     __syncthreads();  // all loads have landed and all fragment reads are done: the ring can be reused
     constexpr int KQ = 2 * NB;  // quadruples of units that a wave keeps (and sends)
     const int m_wave = mp + 32 * NB * hq + 16 * NB * kh + 4 * g;  // quadruple q of the lane: units m_wave + 8 q ..
-    float4 w2q[KQ];
-#pragma unroll
-    for (int q = 0; q < KQ; ++q) {
-      if (!SPLIT) w2q[q] = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
-      else if (A.n_out > 1 && group == 0 && c == 0)
-        *reinterpret_cast<float4*>(A.w2bar + (long long)li * A.M + m_wave + 8 * q) = folded_w2(L.W2, A.M, A.n_out, m_wave + 8 * q);
+    // the pass's averaged second layer, behind the two regions (the first barrier below shows it to all waves); every wave
+    // averaging what it needs took 2 us more (256 units, 12 rows)
+    typedef __attribute__((address_space(3))) float lds_float;
+    if (OWN_ROWS && tid < MP && (!SPLIT || (A.n_out > 1 && group == 0))) {
+      float w = 0.f;
+      for (int o = 0; o < A.n_out; ++o) w += L.W2[(long long)o * A.M + mp + tid];
+      w *= A.inv_out;
+      if (SPLIT) A.w2bar[(long long)li * A.M + mp + tid] = w;
+      else ((lds_float*)(ring + kS3RedBytes))[tid] = w;
     }
 #pragma unroll
     for (int tt = 0; tt < TT; ++tt) {
@@ -681,10 +701,12 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
       }
 #pragma unroll
       for (int q = 0; q < KQ; ++q) {
-        partial[tt] = fmaf(w2q[q].x, hsum[4 * q], partial[tt]);
-        partial[tt] = fmaf(w2q[q].y, hsum[4 * q + 1], partial[tt]);
-        partial[tt] = fmaf(w2q[q].z, hsum[4 * q + 2], partial[tt]);
-        partial[tt] = fmaf(w2q[q].w, hsum[4 * q + 3], partial[tt]);
+        const f32x4_t w = OWN_ROWS ? *(const lds_f4*)(ring + kS3RedBytes + (m_wave - mp + 8 * q) * 4)
+                                   : *reinterpret_cast<const f32x4_t*>(L.W2 + m_wave + 8 * q);
+        partial[tt] = fmaf(w.x, hsum[4 * q], partial[tt]);
+        partial[tt] = fmaf(w.y, hsum[4 * q + 1], partial[tt]);
+        partial[tt] = fmaf(w.z, hsum[4 * q + 2], partial[tt]);
+        partial[tt] = fmaf(w.w, hsum[4 * q + 3], partial[tt]);
       }
     }
   }
@@ -701,7 +723,7 @@ __global__ __launch_bounds__(512, 1) void score_stream_kernel(ScoreArgs A) {
   for (int i = tid; i < 32 * TT; i += 512) {
     const int tok = tok_base + i;
     if (tok < T) {
-      float v = folded_b2(L.b2, A.n_out);
+      float v = folded_b2(L.b2, A.n_out, A.inv_out);
 #pragma unroll
       for (int w = 0; w < 8; ++w) v += red[w * (32 * TT) + i];
       L.out[tok] = v;
@@ -791,32 +813,38 @@ size_t split_scratch_bytes(int T, int M, int n_layers) {
   return (size_t)n_layers * M * ((size_t)split_ld(T) + 1) * sizeof(float);
 }
 
-template <int TT, int NB, bool SPLIT, int SELW>
+template <int TT, int NB, bool SPLIT, bool OWN_ROWS, int SELW>
 int launch_stream(hipStream_t st, const ScoreArgs& a, int n_layers) {
   static LdsLimit lds_limit;
   int lds = s3_lds_bytes(TT, NB);
   if (SELW > 0 && lds < select_bitslice_lds_bytes(512)) lds = select_bitslice_lds_bytes(512);
-  const int rc = set_lds_limit(lds_limit, score_stream_kernel<TT, NB, SPLIT, SELW>, lds);
+  const int rc = set_lds_limit(lds_limit, score_stream_kernel<TT, NB, SPLIT, OWN_ROWS, SELW>, lds);
   if (rc != PAFU_OK) return rc;
-  hipLaunchKernelGGL((score_stream_kernel<TT, NB, SPLIT, SELW>), dim3(a.groups * a.splits * n_layers + (SELW > 0 ? 1 : 0)),
-                     dim3(512), lds, st, a);
+  hipLaunchKernelGGL((score_stream_kernel<TT, NB, SPLIT, OWN_ROWS, SELW>),
+                     dim3(a.groups * a.splits * n_layers + (SELW > 0 ? 1 : 0)), dim3(512), lds, st, a);
   if (SPLIT) hipLaunchKernelGGL(score_sum_kernel, dim3((a.T + 31) / 32, n_layers), dim3(512), 0, st, a);
   return check_launch();
 }
-template <int TT, int NB, bool SPLIT>
+template <int TT, int NB, bool SPLIT, bool OWN_ROWS>
 int launch_stream_sel(hipStream_t st, const ScoreArgs& a, int n_layers, int selw) {
-  if (selw == 2) return launch_stream<TT, NB, SPLIT, 2>(st, a, n_layers);
-  if (selw == 4) return launch_stream<TT, NB, SPLIT, 4>(st, a, n_layers);
-  return launch_stream<TT, NB, SPLIT, 0>(st, a, n_layers);
+  if (selw == 2) return launch_stream<TT, NB, SPLIT, OWN_ROWS, 2>(st, a, n_layers);
+  if (selw == 4) return launch_stream<TT, NB, SPLIT, OWN_ROWS, 4>(st, a, n_layers);
+  return launch_stream<TT, NB, SPLIT, OWN_ROWS, 0>(st, a, n_layers);
+}
+// (with shared units the rows are averaged by one token group on the side: no variant of its own)
+template <int TT, int NB, bool SPLIT>
+int launch_stream_rows(hipStream_t st, const ScoreArgs& a, int n_layers, int selw) {
+  return SPLIT || a.n_out > 1 ? launch_stream_sel<TT, NB, SPLIT, true>(st, a, n_layers, selw)
+                              : launch_stream_sel<TT, NB, SPLIT, SPLIT>(st, a, n_layers, selw);
 }
 template <int NB, bool SPLIT>
 int launch_stream_tt(hipStream_t st, const ScoreArgs& a, int n_layers, int tt, int selw) {
   switch (tt) {
-    case 1: return launch_stream_sel<1, NB, SPLIT>(st, a, n_layers, selw);
-    case 2: return launch_stream_sel<2, NB, SPLIT>(st, a, n_layers, selw);
-    case 3: return launch_stream_sel<3, NB, SPLIT>(st, a, n_layers, selw);
-    case 4: return launch_stream_sel<4, NB, SPLIT>(st, a, n_layers, selw);
-    default: return launch_stream_sel<5, NB, SPLIT>(st, a, n_layers, selw);
+    case 1: return launch_stream_rows<1, NB, SPLIT>(st, a, n_layers, selw);
+    case 2: return launch_stream_rows<2, NB, SPLIT>(st, a, n_layers, selw);
+    case 3: return launch_stream_rows<3, NB, SPLIT>(st, a, n_layers, selw);
+    case 4: return launch_stream_rows<4, NB, SPLIT>(st, a, n_layers, selw);
+    default: return launch_stream_rows<5, NB, SPLIT>(st, a, n_layers, selw);
   }
 }
 
@@ -856,6 +884,7 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
   if (n_layers > 1 && (n_layers > kScoreBatchMax || !score_batchable(s))) return PAFU_ERR_SHAPE;  // callers ask first
   ScoreArgs a;
   a.T = s.T; a.Fs = s.Fs; a.F = s.n_seg * s.Fs; a.ld_x = s.ld_x; a.M = s.M; a.act = s.act; a.n_out = s.n_out;
+  a.inv_out = 1.0f / (float)s.n_out;
   for (int l = 0; l < n_layers; ++l) a.layer[l] = layers[l];
   a.n_layers = n_layers;
   a.groups = 0;
@@ -883,6 +912,7 @@ int launch_score(hipStream_t st, const ScoreShape& s, const ScoreLayer* layers, 
     first.W2 = w;
     first.b2 = w + s.M;
     a.n_out = 1;
+    a.inv_out = 1.f;
   }
   if (stream) {
     a.groups = ((s.T + 31) / 32 + plan.tt - 1) / plan.tt;
