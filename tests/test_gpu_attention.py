@@ -72,7 +72,7 @@ def test_attention_peaked_softmax_and_fp32_output():
 # With a workspace the launch cuts the flattened (head, query tile, key tiles) list of its last, ill-filled round into
 # equal runs, at most one per CU, and merges the partial results of the query tiles that several workgroups worked on.
 @pytest.mark.parametrize("n,Lc,N,D,L_B,odt,q_gain", [
-    (16000, 600, 4, 128, 600, torch.bfloat16, 1.0),   # 12 items of 130 units each over 256 runs
+    (16000, 600, 4, 128, 600, torch.bfloat16, 1.0),   # 12 items of 130 units each, 19 runs per item
     (9000, 1500, 3, 128, 500, torch.bfloat16, 1.0),   # block mask: the items have different lengths
     (9000, 1500, 3, 128, 500, torch.float32, 8.0),    # ... peaked softmax, fp32 output
     (20000, 300, 5, 64, 300, torch.bfloat16, 1.0),    # head dim 64
@@ -125,7 +125,9 @@ def test_attention_large_key_offset_and_fewer_queries():
 def test_attention_running_maximum_outgrown(D, case):
     # the running maximum is the first tile's until a later tile outgrows it: for all queries of every tile, for single
     # queries of one tile, from a first tile in which a query sees nothing; and a NaN in one query stays in that query
-    n, Lc, N = (0, 300, 2) if case == "masked start" else (700, 96, 2)
+    # (masked start: 12 items per head of 2 to 24 units, the last one of 23: cut in runs of two, those of the second head
+    # start in the middle of an item's last 256 keys, of which its first queries see none)
+    n, Lc, N = (0, 2900, 2) if case == "masked start" else (700, 96, 2)
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=7 + D)
     bad = []
     if case == "every tile":
