@@ -161,10 +161,11 @@ int pafu_compact_kv_counted(void* stream, const void* K, const void* V, const fl
  *   Query i is chunk token i (Lq <= Lc on this path).  The tensors may be of any size, but 64 consecutive K/V rows
  *   must span less than 4 GiB (ld_c, ld_n below 2^25 elements), else PAFU_ERR_SHAPE.
  *   workspace : optional (NULL / 0 allowed).  With pafu_attention_workspace_bytes(Lq, N, D) bytes (16-byte aligned,
- *               apart from every tensor of the call) a launch whose (head, 256-query tile) items would fill at most
- *               four fifths of the GPU's compute units cuts its work into equal runs over the key axis, one per
- *               compute unit, and merges the partial results in a second pass: the same result up to the rounding
- *               of the softmax weights, several times faster for short chunks over a long cache.  The contents of
+ *               apart from every tensor of the call) a launch whose (head, 256-query tile) items fill at most four
+ *               fifths of the GPU's compute units in their last round cuts the items of that round into runs over
+ *               the key axis, at most one per compute unit, and merges the partial results in a second pass: the
+ *               same result up to the rounding of the softmax weights, several times faster for short chunks over
+ *               a long cache.  The contents of
  *               the workspace need not be initialised and are not kept.  Results do not depend on timing either way.
  */
 size_t pafu_attention_workspace_bytes(int Lq, int N, int D);
@@ -275,12 +276,12 @@ typedef struct pafu_step_args {
   /* Optional timing hooks (host handles, hipEvent_t passed as void*, each NULL = not recorded): recorded on the
    * step's stream before scoring [0], after scoring [1], after selection [2], after compaction [3] and after
    * attention [4] (ROLLOUT: the selection reads the stored list only and is done by one workgroup of the scoring
-   * launch when that launch is a short streaming one and the list holds at most 65536 scores, so [1]..[2] is then
-   * empty; the chunk rows are appended by the compaction launch, i.e. inside [2]..[3]; only when the
-   * cache was empty, or the rows do not fit that kernel, a separate copy follows [4]).  In the multi-layer steps, whose stages are reordered across
-   * layers, [0]/[1] bracket a layer's scoring and [3]/[4] the attention launch it is part of
-   * (one for all layers that share a geometry); [2] is recorded once, after the
-   * selection launch, on args[0] (pafu_step_layers) or on the index layer (pafu_step_layers_shared). */
+   * launch when that launch is a streaming one whose last round leaves a compute unit free and the list holds at most
+   * 65536 scores, so [1]..[2] is then empty; the chunk rows are appended by the compaction launch, i.e. inside
+   * [2]..[3]; only when the cache was empty, or the rows do not fit that kernel, a separate copy follows [4]).  In the
+   * multi-layer steps, whose stages are reordered across layers, [0]/[1] bracket the scoring launch and [3]/[4] the
+   * attention launch that a layer is part of (one for a stretch of layers that share a geometry); [2] is recorded
+   * once, after the selection launch, on args[0] (pafu_step_layers) or on the index layer (pafu_step_layers_shared). */
   void* stage_events[5];
   /* Storage of the K/V cache: PAFU_BF16 (0, the default) or PAFU_FP8_E4M3.  With the 8-bit format K_cache, V_cache,
    * K_out and V_out hold codes (ld_cache / ld_out count bytes; D must be 128), K_chunk / V_chunk / Q stay bf16, and
@@ -316,8 +317,9 @@ int pafu_step_layers(void* stream, const pafu_step_args* args /* host array */, 
  * equal the index layer's - N, D, block_len, softmax_scale, out_dtype, ld_cache/ld_out/ld_chunk/ld_o, K_cache,
  * V_cache, Q, K_chunk, V_chunk, K_out, V_out, O); their feature, weight, score, ids and SL fields are ignored and
  * may be NULL.  The score list is compacted and extended for the index layer only.
- * The index layer's scoring and the selection are enqueued first, then the layers' caches in array order, on one
- * stream; outputs of one layer must not overlap inputs or outputs of another (PAFU_ERR_ALIAS).
+ * The index layer's scoring and the selection are enqueued first, then the layers' compactions, then their attention,
+ * both as in pafu_step_layers, on one stream; outputs of one layer must not overlap inputs or outputs of another
+ * (PAFU_ERR_ALIAS).  A layer whose workspace is NULL borrows the index layer's.
  */
 int pafu_step_layers_shared(void* stream, const pafu_step_args* args /* host array */, int n_layers,
                             int index_layer);

@@ -81,14 +81,12 @@ constexpr float kAtMaxScaledSum = 1.2676506e30f;  // 2^100
 // results of such a build are meaningless.  pafu_study_build() returns the mask.
 //   1: no global -> LDS tile copies inside the loop (the ring keeps the tiles of the prologue)
 //   2: no softmax arithmetic (P = the upper halves of S, one byte-permute per pair; sums and maxima untouched)
-//   4: equal runs whenever a workspace is given, also when the items fill the chip (results stay correct)
 #ifndef PAFU_ATTN_ABLATE
 #define PAFU_ATTN_ABLATE 0
 #endif
 constexpr bool kAblateLoads = (PAFU_ATTN_ABLATE & 1) != 0;
 constexpr bool kAblateSoftmax = (PAFU_ATTN_ABLATE & 2) != 0;
-constexpr bool kStudySplitAlways = (PAFU_ATTN_ABLATE & 4) != 0;
-constexpr float kAtNoMax = -1.0e30f;  // running maximum before the first visible key (finite on purpose)
+constexpr float kAtNoMax = -1.0e30f;  // reference before the first visible key (finite on purpose)
 constexpr int kAtMaxRuns = 256;       // most runs a unit list is ever cut into (one per CU)
 constexpr int kAtMinRunUnits = 2;     // fewest units of a run
 constexpr int kAtMinCutGain = 4;      // a cut has to shorten the last round by this many units to pay for its merge pass
@@ -220,7 +218,7 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
         }
       }
       psum = 1.f;
-    } else {  // weights of this slot's keys, relative to the running maximum of the tiles before this one
+    } else {  // weights of this slot's keys, relative to the reference that the tiles before this one left
 #pragma unroll
       for (int x = 0; x < EPS; ++x) {
         const int e = EPS * i + x, kb = e >> 4, r = e & 15;
@@ -337,7 +335,7 @@ __device__ __forceinline__ void attn_mask(f32x16 (&s)[2], int key0, int lim, int
 // are cut instead: their flattened unit list goes in `n_runs` equal contiguous runs to one workgroup each, behind the
 // `n_whole` workgroups that take an item each.  A run covers the tail of one item, possibly some whole items, and the
 // head of another.  A workgroup that does not see all units of an item writes its unnormalised O^T together with the
-// running maximum and the row sums into the workspace (slot 2 g for the first segment of run g, 2 g + 1 for its last),
+// reference and the row sums into the workspace (slot 2 g for the first segment of run g, 2 g + 1 for its last),
 // and attn_combine_kernel merges the partial results of such items afterwards, always in run order, so the result does
 // not depend on timing.
 struct AttnWork {
@@ -349,7 +347,7 @@ struct AttnWork {
   int n_runs;         // equal runs over the units of the items from n_whole on
   long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list
   float* part_o;      // [2 n_runs][kAtBQ][D] fp32
-  float* part_ml;     // [2 n_runs][2][kAtBQ] fp32: running maximum (log2 domain), row sum
+  float* part_ml;     // [2 n_runs][2][kAtBQ] fp32: reference (log2 domain), row sum
 };
 
 __host__ __device__ inline int attn_units(int qt, int Lq, int n_kept, int Lc, int L_B) {
@@ -698,7 +696,7 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
         for (int e = 0; e < 4; ++e) { p_a[ks][e] = 0u; p_b[ks][e] = 0u; }
-      // The running maximum starts at a finite sentinel, not at -inf: a segment may begin with tiles that are masked
+      // The reference starts at a finite sentinel, not at -inf: a segment may begin with tiles that are masked
       // entirely for some queries, and (-inf) - (-inf) in the rescale factor would poison their sums.
       float msc = kAtNoMax, l_run = 0.f;
 #pragma unroll
@@ -718,7 +716,7 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
       __builtin_amdgcn_s_barrier();
 
-      // the running maximum starts with that of the first tile (every later tile is only checked against it)
+      // the reference starts with the maximum of the first tile (every later tile is only checked against it)
       if ((tb + 1) * kAtTileKeys > lim_min) attn_mask(s_a, tb * kAtTileKeys, lim, g);
       {
         float mx = s_a[0][0];
@@ -965,7 +963,7 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
   // instead of 256 equal ones: 183); 272 of 44 (D = 64): 412 / 234 us; 520 of 36: 745 / 539 us.
   const long long last = items % cus;  // items of the last round
   const bool mixed = items > last && cus % kAtXcds != 0;  // (the kernel's XCD mapping needs whole rounds of XCDs)
-  if (last > 0 && (last * 5 <= (long long)cus * 4 || kStudySplitAlways) && !mixed && workspace != nullptr) {
+  if (last > 0 && last * 5 <= (long long)cus * 4 && !mixed && workspace != nullptr) {
     const int first_cut = (int)(items - last);
     long long u0 = (long long)(first_cut / w.n_qt) * units_head;
     for (int qt = 0; qt < first_cut % w.n_qt; ++qt) u0 += attn_units(qt, Lq, n_kept, Lc, p.block_len);

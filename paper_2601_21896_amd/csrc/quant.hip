@@ -15,8 +15,9 @@ typedef __attribute__((ext_vector_type(2))) unsigned int u32x2;
 
 // Both kernels walk the (row, 8-element chunk) list with the whole grid, one chunk of K and of V per thread at a time.
 // Row and chunk advance by the grid's stride, which the host has divided by the chunks of a row: a division per chunk
-// takes as many instructions as its conversion.  Bound by HBM: 32760 rows of 12 x 128 to codes and back 125 -> 101 us
-// (6.0 TB/s), 80000 of 40 x 128 1029 -> 960.  Two or four chunks per thread were slower (104, 108 us); stores that bypass
+// takes as many instructions as its conversion.  Bound by HBM: 32760 rows of 12 x 128 to codes and back 130 -> 111 us on
+// new inputs (5.4 TB/s; 125 -> 102 us when the same ones are repeated, some of them then in the caches), 80000 of 40 x 128
+// 1050 us before and after.  On repeated inputs two or four chunks per thread were slower (104, 108 us); stores that bypass
 // the caches leave more of the codes there for whoever reads them next (118 us without).
 struct Walk {
   unsigned rows, chunks;    // 8-element chunks per row

@@ -427,7 +427,7 @@ __global__ __launch_bounds__(kScThreads, 2) void score_mfma_kernel(ScoreArgs A) 
 //    What the workgroups leave in scratch are activations, not partial sums: one more launch (6.5 us in both) then takes them through
 //    the second layer in the order of the unsplit kernel, so that a score's bits do not depend on the launch.
 //  - Layers of one geometry share a launch: the token groups of one (57 at 7210 tokens) leave most of the chip idle
-//    (six of 128 units: 6 x 12.9 us one by one, 26 us together, in the kernel above).
+//    (six of 128 units: 6 x 12.9 us one by one, 24 us together, in the kernel above).
 constexpr int kS3Slab = 64;                      // features per slab (full 128-byte lines per row)
 constexpr int kS3RowB = kS3Slab * 2;             // bytes per slab row
 constexpr int kS3Chunks = kS3RowB / 16;          // 16-byte chunks per row

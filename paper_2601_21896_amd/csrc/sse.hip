@@ -172,7 +172,7 @@ __global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
   const int a_off = c * ROWB;
 
   const float sc = p.scale_log2;
-  // rowstat state: running maximum and sum of this lane's half of the keys
+  // rowstat state: reference and sum of this lane's half of the keys
   float m_run[HT], l_run[HT];
   // colmax state: maxima of z - c over the queries seen so far, by block relation
   float mx_low[HT], mx_diag[HT], mx_up[HT];
@@ -352,7 +352,7 @@ __global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
 #pragma unroll
       for (int ht = 0; ht < HT; ++ht) s_a[ht][rb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, hf[ht][kk], s_a[ht][rb], 0, 0, 0);
     }
-  if (!COLMAX) {  // the running maximum starts with that of the first tile
+  if (!COLMAX) {  // the reference starts with the maximum of the first tile
     if (kSseTile > L) mask_tail(s_a, 0);
 #pragma unroll
     for (int ht = 0; ht < HT; ++ht) m_run[ht] = fmaxf(m_run[ht], ceilf(tile_max(s_a[ht]) * sc));

@@ -2,7 +2,7 @@
 
 This module only draws numbers and lays them out; it holds none of the method's
 arithmetic (no scoring, selection, gathering or attention), so both the device
-path and the CPU checker may be fed from it.
+path and the oracle may be fed from it.
 
 Shapes follow the paper's Appendix A (1560 latent tokens per frame, chunks of 3
 frames = 4680 tokens, a 21-frame cache = 32760 tokens, 12 heads x 128).  The
@@ -14,7 +14,7 @@ structured.
 
 All tensors are returned as float32 NumPy arrays.  For a bf16 workload every
 value is first rounded to the nearest bf16 (ties to even), so a later cast to
-bf16 on the device is exact and the CPU checker sees the same numbers.
+bf16 on the device is exact and the oracle sees the same numbers.
 """
 
 from __future__ import annotations
