@@ -267,8 +267,9 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   // as long again.  1203 queries over 2999 keys (8 heads of 64, no workspace, fp32): scores that grow eightfold along the
   // cache 106 -> 75 us (74 without growth), one NaN query in each wave 98 -> 74 us; 4680 over 16380 keys (12 heads of 128)
   // 640 -> 558 (542) and 656 -> 541 us.
-  // (An else branch that left P^T alone, or a shift that was not done in place, put copies of P^T into every step: + 4 %.)
-  if (__builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0) {
+  // (An else branch that left P^T alone, or a shift that was not done in place, put copies of P^T into every step: + 4 %.
+  // Laid out inside the loop, all this cost the 8-bit variant 1 %.)
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0, 0)) {
     float alpha = 1.f;
     // far above the reference (the first tile that a query sees, behind masked ones): take its own maximum
     if (__builtin_amdgcn_ballot_w64(psum > kAtMaxScaledSum) != 0) {
