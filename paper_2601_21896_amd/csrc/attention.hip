@@ -116,12 +116,14 @@ __device__ __forceinline__ void dma_row_chunks(const void* src, unsigned lds_add
                : "memory");
 }
 
-// The same copy addressed as a wave-uniform base plus a 32-bit per-lane byte offset.
-__device__ __forceinline__ void dma_row_chunks_at(const void* base_uniform, unsigned byte_off, unsigned lds_addr_uniform) {
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+// The same copy addressed as a wave-uniform base plus a 32-bit per-lane byte offset, to lds_addr + lds_more.  (The sum goes
+// straight into m0: sums that the compiler sees are kept in scalar registers for the whole loop, sixteen of them.)
+__device__ __forceinline__ void dma_row_chunks_at(const void* base_uniform, unsigned byte_off, unsigned lds_addr_uniform,
+                                                  int lds_more) {
+  asm volatile("s_add_u32 m0, %0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
                :
-               : "s"(lds_addr_uniform), "v"(byte_off), "s"(base_uniform)
-               : "memory");
+               : "s"(lds_addr_uniform), "v"(byte_off), "s"(base_uniform), "s"(lds_more)
+               : "memory", "scc");
 }
 
 // s_waitcnt vmcnt(N) with the other counters left alone (gfx9 encoding: vmcnt = bits 3:0 and 15:14).
@@ -152,14 +154,17 @@ __device__ __forceinline__ bf16x8 lds_read_vt(const lds_byte* p, int row_bytes8)
 // for both) before the first exponential cost about an eighth of the vector instructions and left the first slots without
 // exponentials; without it a whole step takes 634 us instead of 667 (12 heads of 128, 4680 queries, 21060 keys), and 6762
 // instead of 7295 (40 heads, 10800 queries, 33480 keys).
+// k_at[kk] / v_at[db]: this lane's LDS addresses of the fragments in ring slot 0; the tiles are K_TILE / V_TILE bytes on,
+// which goes into the offset field of the reads.
 // issue_k / issue_v start this step's global -> LDS tile copies.  They are called a few slots into the step, not at
 // its start: right after the barrier all eight waves would queue their copies at once and sit behind the memory pipe
 // (a wave issues nothing while its copy waits), whereas an eighth and a half of the way in they find it free.
-template <int D, typename IssueK, typename IssueV>
+template <int D, int K_TILE, int V_TILE, typename IssueK, typename IssueV>
 __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_nxt)[2], const u32x4 (&p_prev)[4],
                                           u32x4 (&p_cur)[4], f32x16 (&o)[D / 32], const bf16x8 (&qf)[D / 16],
-                                          float& msc, float& l_run, const lds_byte* k_tile, const lds_byte* v_tile,
-                                          int kx2, int vx2, float sc, IssueK&& issue_k, IssueV&& issue_v) {
+                                          float& msc, float& l_run, const lds_byte* const (&k_at)[D / 16],
+                                          const lds_byte* const (&v_at)[D / 32], float sc, IssueK&& issue_k,
+                                          IssueV&& issue_v) {
   constexpr int ROWB = 2 * D;
   constexpr int KD = D / 16;
   constexpr int DB = D / 32;
@@ -175,10 +180,8 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   //   S^T MFMA m: key block m & 1, contraction step m >> 1 (the two accumulators alternate).
   //   O^T MFMA m: key slice m / DB, row block m % DB (an accumulator comes back every DB MFMAs).
   // The fragments of MFMA pair m+1 are read from LDS while pair m runs.
-  auto k_frag = [&](int m) { return lds_read_k(k_tile + (m & 1) * 32 * ROWB + (((2 * (m >> 1)) ^ kx2) << 4)); };
-  auto v_frag = [&](int m) {
-    return lds_read_vt(v_tile + (16 * (m / DB)) * ROWB + (((4 * (m % DB)) ^ vx2) << 4), 8 * ROWB);
-  };
+  auto k_frag = [&](int m) { return lds_read_k(k_at[m >> 1] + K_TILE + (m & 1) * 32 * ROWB); };
+  auto v_frag = [&](int m) { return lds_read_vt(v_at[m % DB] + V_TILE + (16 * (m / DB)) * ROWB, 8 * ROWB); };
   bf16x8 kf[2], vf[2];
   kf[0] = k_frag(0);
   vf[0] = v_frag(0);
@@ -316,6 +319,11 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   l_run += psum;
 }
 
+template <int N>
+struct Phase {
+  static constexpr int value = N;
+};
+
 // Block mask / ragged tail for the tile starting at key0: register r of s[kb] holds key
 // key0 + 32 kb + 8 (r/4) + 4 g + (r%4).
 __device__ __forceinline__ void attn_mask(f32x16 (&s)[2], int key0, int lim, int g) {
@@ -375,6 +383,14 @@ __device__ __forceinline__ long long uniform_i64(long long v) {
   return (long long)(((unsigned long long)hi << 32) | lo);
 }
 
+// The kernel's one argument where it lies, for code that shall read it anew.
+typedef const __attribute__((address_space(4))) AttnArgs* KernelArgs;
+__device__ __forceinline__ KernelArgs kernel_args() {
+  KernelArgs a = (KernelArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(a));
+  return a;
+}
+
 // GATHER: the cache segment is read through an index list (index-based Select, Sec. 3.4; Eq. 7): K/V stay
 // uncompacted and tile row r comes from cache row ids[r].  The 64 ids of a tile travel global -> LDS like the tiles
 // themselves (one 4-byte-per-lane load per wave and step, three steps ahead of the K tile that needs them, into a
@@ -432,27 +448,16 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   const int xslot = (blockIdx.x - (is_run ? wk.n_whole : 0)) / kAtXcds;
   const int wg = xcd * (total / kAtXcds) + (xcd < total % kAtXcds ? xcd : total % kAtXcds) + xslot;
   const int L_B = p.block_len;
-  const int n_total = p.n_kept + p.Lc;
-  const long long ldc_b = p.ld_c * ELB, ldn_b = p.ld_n * ELB;
 
-  // ---- per-lane constants of the global -> LDS tile loads.  Load j of this wave fills LDS rows
-  // (wave + W j) * RPI .. + RPI of a tile; lane -> (row, slot); the slot receives chunk (slot ^ swizzle(row)) of that
-  // row.  Rows past the end are masked later, so they read a valid row instead.  The chunk segment's base is
-  // pre-shifted by -n_kept rows so that both segments are addressed as base + key_index * stride.  A tile that lies
-  // inside one segment (all but one or two) needs only a scalar tile base plus a per-lane byte offset prepared here.
-  // (the swizzled chunk does not depend on j: consecutive loads of a wave are kAtWaves * RPI rows apart, a multiple
-  // of the swizzle period, so load j is load 0 with the scalar base moved on by j * kAtWaves * RPI rows)
-  unsigned k_offc, k_offn, v_offc, v_offn;
-  {
-    const int row = wave * RPI + lane / SCH;
-    const int slot = lane % SCH;
-    const int kch = KV8 ? slot : slot ^ ((row / RPB) & (CH - 1));          // raw 8-bit tiles are not swizzled
-    const int vch = KV8 ? slot : slot ^ (4 * ((row / RPB) & (CH / 4 - 1)));
-    k_offc = (unsigned)(row * ldc_b) + kch * 16;
-    k_offn = (unsigned)(row * ldn_b) + kch * 16;
-    v_offc = (unsigned)(row * ldc_b) + vch * 16;
-    v_offn = (unsigned)(row * ldn_b) + vch * 16;
-  }
+  // ---- global -> LDS tile loads.  Load j of this wave fills LDS rows (wave + W j) * RPI .. + RPI of a tile; lane ->
+  // (row, slot); the slot receives chunk (slot ^ swizzle(row)) of that row (raw 8-bit tiles are not swizzled).  The chunk
+  // does not depend on j: consecutive loads of a wave are kAtWaves * RPI rows apart, a multiple of the swizzle period.
+  auto lane_chunk = [](int wave, int lane, bool is_v) {
+    const int row = wave * RPI + lane / SCH, slot = lane % SCH;
+    if (KV8) return slot;
+    return is_v ? slot ^ (4 * ((row / RPB) & (CH / 4 - 1))) : slot ^ ((row / RPB) & (CH - 1));
+  };
+  const unsigned lds_wave = __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)(lds_byte*)lds_raw + wave * 1024);
   // ---- LDS read offsets (bytes inside a tile)
   // K fragment (A operand): lane (key row c, half g) reads chunk (2 kk + g) of row c; its slot is (2 kk) ^ kx2
   const int kx2 = g ^ ((c / RPB) & (CH - 1));
@@ -465,6 +470,12 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   const int vx2 = 4 * ((rr / RPB) & (CH / 4 - 1));
   const int cl = 2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1);
   const int v_off = rr * ROWB + ((i16 & 1) << 3) + (cl << 4);
+  const lds_byte* k_at[KD];
+  const lds_byte* v_at[DB];
+#pragma unroll
+  for (int kk = 0; kk < KD; ++kk) k_at[kk] = k_ring + k_off + (((2 * kk) ^ kx2) << 4);
+#pragma unroll
+  for (int b = 0; b < DB; ++b) v_at[b] = v_ring + v_off + (((4 * b) ^ vx2) << 4);
   const float sc = p.scale_log2;
   int* const id_ring = reinterpret_cast<int*>(lds_raw + 2 * kAtStages * TILEB);  // gather variant (bf16 K/V only)
 
@@ -544,84 +555,123 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       const int id = ((const __attribute__((address_space(3))) int*)id_ring)[(tile % kAtIdStages) * kAtTileKeys + row];
       return id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1);
     };
-    auto issue_one = [&](int tile_, const void* cache, const void* chunk, lds_byte* ring,
-                         unsigned offc, unsigned offn, bool is_v) {
-      const int tile = uniform_i32(tile_);
-      const int stage = tile % kAtStages;
-      const int key0 = tile * kAtTileKeys;
-      const char* base_c = static_cast<const char*>(cache) + head_off * ELB;
-      const char* base_n = static_cast<const char*>(chunk) + head_off * ELB - (long long)p.n_kept * ldn_b;
-      const bool all_cache = key0 + kAtTileKeys <= p.n_kept;
-      const bool all_chunk = key0 >= p.n_kept && key0 + kAtTileKeys <= n_total;
-      if (GATHER && all_cache) {  // workgroup-uniform
-        // Registers are scarce here, so nothing per-lane is kept between steps: the swizzled chunk is recomputed (it
-        // does not depend on j: consecutive loads of a wave are 8 RPI rows apart) and the address is the head's
-        // base plus a 32-bit offset (the host rejects caches of 4 GiB or more per tensor for this variant).
-        const int rl = lane / CH, slot = lane % CH;
-        const int row0 = wave * RPI + rl;  // the tile row of load 0
-        const unsigned chunk16 =
-            (unsigned)((is_v ? slot ^ (4 * ((row0 / RPB) & (CH / 4 - 1))) : slot ^ ((row0 / RPB) & (CH - 1))) << 4);
+    // Tile t of the segment goes to ring slot t % kAtStages.
+    auto lds_slot = [&](bool is_v, int slot, int j) {  // this wave's load j of a slot, from lds_wave on
+      return (int)((is_v ? v_land : k_land) - (lds_byte*)lds_raw) + slot * STILEB + kAtWaves * j * 1024;
+    };
+    // What follows up to copy_tile is rare.  It takes its arguments from memory and its lane number through an opaque copy:
+    // what the compiler may hoist out of the loop for it would fill the registers that the loop needs.
+    struct Rare {
+      KernelArgs a;
+      int lane, wave;
+    };
+    auto rare = [&] {
+      Rare r{kernel_args(), lane, wave};
+      asm volatile("" : "+v"(r.lane));
+      asm volatile("" : "+s"(r.wave));
+      return r;
+    };
+    auto head_base = [&](const Rare& r, bool is_v, bool chunk) {  // row 0 of the key axis of this head
+      const auto& l = r.a->layer[layer];
+      const void* t = is_v ? (chunk ? l.Vn : l.Vc) : (chunk ? l.Kn : l.Kc);
+      return static_cast<const char*>(t) + head_off * ELB - (chunk ? (long long)r.a->p.n_kept * r.a->p.ld_n * ELB : 0);
+    };
+    // The general copy works row by row: a tile that straddles the two key segments, or the end of the keys (rows past it
+    // are masked later, so they read a valid one instead).
+    auto copy_rows = [&](int tile, int slot, bool is_v) {
+      const Rare r = rare();
+      const char *base_c = head_base(r, is_v, false), *base_n = head_base(r, is_v, true);
+      const int kept = r.a->p.n_kept, keys = kept + r.a->p.Lc;
+      const unsigned ldc_b = (unsigned)(r.a->p.ld_c * ELB), ldn_b = (unsigned)(r.a->p.ld_n * ELB);  // (below 4 GiB)
 #pragma unroll
-        for (int j = 0; j < LPT; ++j) {
-          const int id = tile_id(tile, (wave + kAtWaves * j) * RPI + rl);
-          lds_byte* dst = ring + stage * STILEB + (wave + kAtWaves * j) * 1024;
-          dma_row_chunks_at(base_c, (unsigned)id * (unsigned)ldc_b + chunk16,
-                            __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)dst));
-        }
-      } else if (all_cache || all_chunk) {  // workgroup-uniform
-        const bool from_cache = all_cache && !GATHER;  // (a gathered all-cache tile took the branch above)
-        // scalar address arithmetic: 32 x 32 -> 64-bit products (row strides are below 4 GiB), which the scalar
-        // unit has; a 64 x 64-bit product would be done on the vector ALU and leave the base in vector registers
-        const unsigned ld_b = (unsigned)(from_cache ? ldc_b : ldn_b);
-        const char* tile_base = (from_cache ? base_c : base_n) + (unsigned long long)(unsigned)key0 * ld_b;
-        const unsigned off = from_cache ? offc : offn;
-#pragma unroll
-        for (int j = 0; j < LPT; ++j) {
-          lds_byte* dst = ring + stage * STILEB + (wave + kAtWaves * j) * 1024;
-          dma_row_chunks_at(tile_base + (unsigned long long)(unsigned)(j * kAtWaves * RPI) * ld_b, off,
-                            __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)dst));
-        }
-      } else {
-#pragma unroll
-        for (int j = 0; j < LPT; ++j) {
-          const int row = (wave + kAtWaves * j) * RPI + lane / SCH;
-          const int slot = lane % SCH;
-          const int ch = KV8 ? slot : (is_v ? slot ^ (4 * ((row / RPB) & (CH / 4 - 1))) : slot ^ ((row / RPB) & (CH - 1)));
-          int kidx = key0 + row;
-          kidx = kidx < n_total ? kidx : n_total - 1;
-          const bool in_cache = kidx < p.n_kept;
-          if (GATHER && in_cache) kidx = tile_id(tile, row);
-          const char* src = (in_cache ? base_c : base_n) +
-                            (unsigned long long)(unsigned)kidx * (unsigned long long)(in_cache ? ldc_b : ldn_b) + ch * 16;
-          lds_byte* dst = ring + stage * STILEB + (wave + kAtWaves * j) * 1024;
-          dma_row_chunks(src, __builtin_amdgcn_readfirstlane((unsigned)(uintptr_t)dst));
-        }
+      for (int j = 0; j < LPT; ++j) {
+        const int row = (r.wave + kAtWaves * j) * RPI + r.lane / SCH;
+        int kidx = tile * kAtTileKeys + row;
+        kidx = kidx < keys ? kidx : keys - 1;
+        const bool in_cache = kidx < kept;
+        if (GATHER && in_cache) kidx = tile_id(tile, row);
+        const char* src = (in_cache ? base_c : base_n) +
+                          (unsigned long long)(unsigned)kidx * (in_cache ? ldc_b : ldn_b) +
+                          lane_chunk(r.wave, r.lane, is_v) * 16;
+        dma_row_chunks(src, lds_wave + lds_slot(is_v, slot, j));
       }
     };
-    // Step t (relative to the segment) reads K tile tb+t+1 and V tile tb+t-1.  During it K(t+S) and V(t+S-2) are
-    // issued into the slots of K(t) and V(t-2), whose last readers finished in step t-1.  Tiles past the end of the
-    // key axis hold clamped rows and are masked or never read.
-    // In the gather variant the ids of tiles kt and kt-2 must already be visible in the ids ring.
-    auto issue_k_tile = [&](int kt) { issue_one(tb + kt, L.Kc, L.Kn, k_land, k_offc, k_offn, false); };
-    auto issue_v_tile = [&](int kt) {
-      if (kt >= 2) issue_one(tb + kt - 2, L.Vc, L.Vn, v_land, v_offc, v_offn, true);
+    // The common copy: `left` tiles from the scalar address `base` on are full and lie inside one key segment, `half` bytes
+    // from load to load (or lie past the end of the keys: then the last row stands in for all of theirs).  All that a step
+    // does for it is to count, add and issue.  Worked out anew for each tile from the kernel arguments it was 45 scalar
+    // instructions per tensor and step, and the scalar loads among them waited for all LDS reads in flight (one counter
+    // for both): together with the fragment addresses of four ring slots in the reads' offset fields a whole step takes
+    // 602 us instead of 635 (12 heads of 128, 4680 queries, 21060 keys), with the 8-bit cache 477 instead of 512 (17160 keys).
+    struct TileStream {
+      const char* base;
+      unsigned half, off;
+      int left;
     };
-    auto issue_tiles = [&](int kt) {  // kt relative to the segment
-      issue_k_tile(kt);
-      issue_v_tile(kt);
+    TileStream ks, vs;
+    auto seek = [&](TileStream& s, int tile, bool is_v) {  // prepares the copies from `tile` on; left = 0: not a full tile
+      const Rare r = rare();
+      const int kept = r.a->p.n_kept, keys = kept + r.a->p.Lc;
+      const int key0 = tile * kAtTileKeys;
+      const bool cache = key0 + kAtTileKeys <= kept, past = key0 >= keys;
+      const bool chunk = key0 >= kept && key0 + kAtTileKeys <= keys;
+      s.left = uniform_i32(past ? 0x7fffffff
+                                : cache && !GATHER ? kept / kAtTileKeys - tile : chunk ? keys / kAtTileKeys - tile : 0);
+      const unsigned ld_b = (unsigned)((cache ? r.a->p.ld_c : r.a->p.ld_n) * ELB);
+      const unsigned step = past ? 0u : ld_b;
+      s.half = (unsigned)uniform_i32((int)((unsigned)(kAtWaves * RPI) * step));
+      s.base = reinterpret_cast<const char*>(
+          uniform_i64((long long)reinterpret_cast<uintptr_t>(head_base(r, is_v, !cache)) +
+                      (long long)((unsigned long long)(unsigned)(past ? keys - 1 : key0) * ld_b)));
+      s.off = (unsigned)(r.wave * RPI + r.lane / SCH) * step + lane_chunk(r.wave, r.lane, is_v) * 16;
     };
-    auto k_addr = [&](int t) { return k_ring + ((tb + t) % CK) * TILEB + k_off; };
-    auto v_addr = [&](int t) { return v_ring + ((tb + t) % CK) * TILEB + v_off; };
-    // 8-bit K/V: this wave's 1 KB of raw tile t (the part it copied itself, so only its own copies must have landed)
-    // -> bf16, into the slot of tile t.  Lane l holds 16 codes of key row w * RPI + l / SCH, d = 16 (l % SCH) .. + 16:
-    // two 16-byte chunks of the bf16 row, stored with the swizzle of the fragment reads.
-    auto cook = [&](int t, bool is_v) {
+    auto copy_tile = [&](TileStream& s, int tile, int slot, bool is_v) {
+      if (GATHER && (tile + 1) * kAtTileKeys <= p.n_kept) {  // workgroup-uniform
+        // Registers are scarce here, so nothing per-lane is kept between steps: the swizzled chunk is recomputed and the
+        // address is the head's base plus a 32-bit offset (the host rejects caches of 4 GiB or more per tensor for this
+        // variant).
+        const unsigned chunk16 = (unsigned)lane_chunk(wave, lane, is_v) << 4;
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+          const int id = tile_id(tile, (wave + kAtWaves * j) * RPI + lane / SCH);
+          dma_row_chunks_at(static_cast<const char*>(is_v ? L.Vc : L.Kc) + head_off * ELB, (unsigned)id * (unsigned)(p.ld_c * ELB) + chunk16, lds_wave,
+                            lds_slot(is_v, slot, j));
+        }
+        return;
+      }
+      auto copy = [&] {
+        --s.left;
+#pragma unroll
+        for (int j = 0; j < LPT; ++j) {
+          // (the gather variant keeps the stream in vector registers: most of its tiles are none of a stream's)
+          const char* base = GATHER ? reinterpret_cast<const char*>(uniform_i64((long long)reinterpret_cast<uintptr_t>(s.base)))
+                                    : s.base;
+          dma_row_chunks_at(base, s.off, lds_wave, lds_slot(is_v, slot, j));
+          s.base = base + s.half;
+        }
+      };
+      if (__builtin_expect(s.left > 0, 1)) {
+        copy();
+      } else {
+        seek(s, tile, is_v);
+        if (s.left > 0) copy();
+        else copy_rows(tile, slot, is_v);
+      }
+    };
+    // Step t (relative to the segment) reads K tile t+1 and V tile t-1.  During it K(t+S) and V(t+S-2) are issued into the
+    // slots of K(t) and V(t-2), whose last readers finished in step t-1.  Tiles past the end of the key axis hold clamped
+    // rows and are masked or never read.
+    // In the gather variant the ids of the two tiles must already be visible in the ids ring.
+    auto issue_k_tile = [&](int kt, int slot) { copy_tile(ks, tb + kt, slot, false); };
+    auto issue_v_tile = [&](int vt, int slot) { copy_tile(vs, tb + vt, slot, true); };
+    // 8-bit K/V: this wave's 1 KB of a raw tile (the part it copied itself, so only its own copies must have landed)
+    // -> bf16, from raw slot `from` into bf16 slot `to`.  Lane l holds 16 codes of key row w * RPI + l / SCH,
+    // d = 16 (l % SCH) .. + 16: two 16-byte chunks of the bf16 row, stored with the swizzle of the fragment reads.
+    auto cook = [&](int from, int to, bool is_v) {
       typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
-      const int tile = tb + t;
-      const u32x4 raw = *(const lds_u32x4*)((is_v ? v_land : k_land) + (tile % kAtStages) * STILEB + wave * 1024 + lane * 16);
+      const u32x4 raw = *(const lds_u32x4*)((is_v ? v_land : k_land) + from * STILEB + wave * 1024 + lane * 16);
       const int row = wave * RPI + lane / SCH, chunk = lane % SCH;
       const int sw = is_v ? 4 * ((row / RPB) & (CH / 4 - 1)) : (row / RPB) & (CH - 1);
-      lds_byte* dst = (is_v ? v_ring : k_ring) + (tile % CK) * TILEB + row * ROWB;
+      lds_byte* dst = (is_v ? v_ring : k_ring) + to * TILEB + row * ROWB;
       const float scl = is_v ? p.v_scale : p.k_scale;
       u32x4 lo, hi;
 #pragma unroll
@@ -634,10 +684,11 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       *(lds_u32x4*)(dst + (((2 * chunk) ^ sw) << 4)) = lo;
       *(lds_u32x4*)(dst + (((2 * chunk + 1) ^ sw) << 4)) = hi;
     };
-    // what a step does for the 8-bit tiles: K(t+2) and V(t) become bf16 one step before they are read
-    auto cook_step = [&](int t, int n_tiles_seg) {
-      if (t + 2 < n_tiles_seg) cook(t + 2, false);
-      if (t > 0) cook(t, true);
+    // what step t (with t % kAtStages == ph) does for the 8-bit tiles: K(t+2) and V(t) become bf16 one step before they are
+    // read
+    auto cook_step = [&](int ph, int t) {
+      if (t + 2 < 2 * n_iter) cook((ph + 2) % kAtStages, ph % CK, false);
+      cook(ph % kAtStages, ph % CK, true);
     };
 
     // Q^T fragments (B operand): lane (query c, half g) holds Q[q][16 kk + 8 g .. +8]
@@ -656,16 +707,30 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       wait_vmcnt<0>();
       __builtin_amdgcn_s_barrier();
     }
+    ks = vs = TileStream{nullptr, 0u, 0u, 0};
+#pragma unroll 1
+    for (int i = 0; i < kAtStages; ++i) {
+      issue_k_tile(i, i);
+      if (i >= 2) issue_v_tile(i - 2, i - 2);
+    }
+    // step 0 adds the V tile in front of the first one, with weights of zero: what it reads must be finite
+    {
+      typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+      const u32x4 none = {0u, 0u, 0u, 0u};
+      lds_byte* z = v_ring + (CK - 1) * TILEB + tid * 16;
 #pragma unroll
-    for (int i = 0; i < kAtStages; ++i) issue_tiles(i);
+      for (int i = 0; i < TILEB / 16 / kAtThreads; ++i) *(lds_u32x4*)(z + i * kAtThreads * 16) = none;
+    }
     wait_vmcnt<0>();
-    if (KV8) {  // the first product needs K(0), step 0 reads K(1) and (with P = 0) V(0)
-      cook(0, false);
-      cook(1, false);
-      cook(0, true);
-      __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): the bf16 rows are written before the barrier lets others read
+    if (KV8) {  // the first product needs K(0), step 0 reads K(1)
+      cook(0, 0, false);
+      cook(1, 1, false);
+    }
+    __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): what was written is there before the barrier lets others read
+    if (KV8) {
       // the raw ring has kAtStages slots: K(kAtStages) goes where this wave's part of K(0) was, now that it is converted
-      issue_tiles(kAtStages);
+      issue_k_tile(kAtStages, 0);
+      issue_v_tile(kAtStages - 2, kAtStages - 2);
     }
     __builtin_amdgcn_s_barrier();
 
@@ -676,9 +741,12 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
 #pragma unroll 1
       for (int t = 0; t < 2 * n_iter; ++t) {
         if (GATHER) issue_ids(tb + t + kAtStages + kAtIdLead);
-        if (!kAblateLoads) issue_tiles(t + LEAD);
+        if (!kAblateLoads) {
+          issue_k_tile(t + LEAD, (t + LEAD) % kAtStages);
+          issue_v_tile(t + LEAD - 2, (t + LEAD - 2) % kAtStages);
+        }
         if (KV8) {
-          cook_step(t, 2 * n_iter);
+          cook_step(t % kAtStages, t);
           __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
         }
         wait_vmcnt<(kAtStages - 2) * (2 * LPT + (GATHER ? 1 : 0))>();
@@ -706,7 +774,7 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
         for (int r = 0; r < 16; ++r) s_a[kb][r] = 0.f;
 #pragma unroll
         for (int kk = 0; kk < KD; ++kk) {
-          const bf16x8 a = lds_read_k(k_addr(0) + kb * 32 * ROWB + (((2 * kk) ^ kx2) << 4));
+          const bf16x8 a = lds_read_k(k_at[kk] + kb * 32 * ROWB);
           s_a[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[kk], s_a[kb], 0, 0, 0);
         }
       }
@@ -728,45 +796,40 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
         msc = fmaxf(msc, half_swap_max(mx) * sc);
       }
 
-      // Step t: S^T(t+1) into the "next" registers, softmax of S^T(t), O^T += tile t-1.  Iteration T runs step 2T
-      // (s_a -> p_a, next into s_b, adds p_b) and step 2T+1 (s_b -> p_b, next into s_a, adds p_a).  A segment always
-      // holds an even number of tiles: a tile past the end is fully masked and contributes nothing.  Before the first
-      // tile p_b is zero, and when there is no next tile the S^T product re-reads the current one (its result is
-      // never used).  After each step: K(t+2) and V(t) must have landed before the next step; only the loads of the
-      // last two steps may stay in flight.
+      // Step t: S^T(t+1) into the "next" registers, softmax of S^T(t), O^T += tile t-1.  Even steps go from s_a to p_a, odd
+      // ones from s_b to p_b.  A segment always holds an even number of tiles: a tile past the end is fully masked and
+      // contributes nothing.  Before the first tile p_b is zero, and the S^T product of the last step is never used.
+      // After each step: K(t+2) and V(t) must have landed before the next step; only the loads of the last two steps may
+      // stay in flight.  The steps of a turn of the ring are written out, so that every slot is a constant.
+      auto step = [&](auto phase, int t, f32x16(&s_cur)[2], f32x16(&s_nxt)[2], const u32x4(&p_prev)[4], u32x4(&p_cur)[4]) {
+        constexpr int PH = decltype(phase)::value;
+        if (GATHER) issue_ids(tb + t + kAtStages + kAtIdLead);
+        if (KV8) cook_step(PH, t);
+        if (__builtin_expect((tb + t + 1) * kAtTileKeys > lim_min, 0)) attn_mask(s_cur, (tb + t) * kAtTileKeys, lim, g);
+        attn_step<D, (PH + 1) % CK * TILEB, (PH + CK - 1) % CK * TILEB>(
+            s_cur, s_nxt, p_prev, p_cur, o, qf, msc, l_run, k_at, v_at, sc,
+            [&] { if (!kAblateLoads) issue_k_tile(t + LEAD, (PH + LEAD) % kAtStages); },
+            [&] { if (!kAblateLoads) issue_v_tile(t + LEAD - 2, (PH + LEAD - 2) % kAtStages); });
+        if (KV8) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this step's bf16 rows are written
+        wait_vmcnt<(kAtStages - 2) * (2 * LPT + (GATHER ? 1 : 0))>();
+        __builtin_amdgcn_s_barrier();
+      };
+      static_assert(kAtStages == 4, "a turn of the ring is four steps");
 #pragma unroll 1
-      for (int T = 0; T < n_iter; ++T) {
-        {
-          const int t = 2 * T;
-          if (GATHER) issue_ids(tb + t + kAtStages + kAtIdLead);
-          if (KV8) cook_step(t, 2 * n_iter);
-          if (T > 0 && (tb + t + 1) * kAtTileKeys > lim_min) attn_mask(s_a, (tb + t) * kAtTileKeys, lim, g);
-          attn_step<D>(
-              s_a, s_b, p_b, p_a, o, qf, msc, l_run, k_addr(t + 1), v_addr(t > 0 ? t - 1 : 0), kx2, vx2, sc,
-              [&] { if (!kAblateLoads) issue_k_tile(t + LEAD); }, [&] { if (!kAblateLoads) issue_v_tile(t + LEAD); });
-          if (KV8) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this step's bf16 rows are written
-          wait_vmcnt<(kAtStages - 2) * (2 * LPT + (GATHER ? 1 : 0))>();
-          __builtin_amdgcn_s_barrier();
-        }
-        {
-          const int t = 2 * T + 1;
-          if (GATHER) issue_ids(tb + t + kAtStages + kAtIdLead);
-          if (KV8) cook_step(t, 2 * n_iter);
-          if ((tb + t + 1) * kAtTileKeys > lim_min) attn_mask(s_b, (tb + t) * kAtTileKeys, lim, g);
-          attn_step<D>(
-              s_b, s_a, p_a, p_b, o, qf, msc, l_run, k_addr(T + 1 < n_iter ? t + 1 : t), v_addr(t - 1), kx2, vx2, sc,
-              [&] { if (!kAblateLoads) issue_k_tile(t + LEAD); }, [&] { if (!kAblateLoads) issue_v_tile(t + LEAD); });
-          if (KV8) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0)
-          wait_vmcnt<(kAtStages - 2) * (2 * LPT + (GATHER ? 1 : 0))>();
-          __builtin_amdgcn_s_barrier();
-        }
+      for (int t = 0;; t += 4) {
+        step(Phase<0>{}, t, s_a, s_b, p_b, p_a);
+        step(Phase<1>{}, t + 1, s_b, s_a, p_a, p_b);
+        if (t + 2 >= 2 * n_iter) break;
+        step(Phase<2>{}, t + 2, s_a, s_b, p_b, p_a);
+        step(Phase<3>{}, t + 3, s_b, s_a, p_a, p_b);
+        if (t + 4 >= 2 * n_iter) break;
       }
       // the last tile's contribution
       {
-        const lds_byte* vt = v_addr(2 * n_iter - 1);
+        const int last = (2 * n_iter - 1) % CK * TILEB;
 #pragma unroll
         for (int m = 0; m < 4 * DB; ++m) {
-          const bf16x8 a = lds_read_vt(vt + (16 * (m / DB)) * ROWB + (((4 * (m % DB)) ^ vx2) << 4), 8 * ROWB);
+          const bf16x8 a = lds_read_vt(v_at[m % DB] + last + (16 * (m / DB)) * ROWB, 8 * ROWB);
           o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(p_b[m / DB]), o[m % DB], 0, 0, 0);
         }
       }

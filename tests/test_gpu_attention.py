@@ -57,6 +57,32 @@ def test_attention_matches_oracle(n, Lc, N, D, L_B):
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
 
 
+# One item's tiles around the turns of the four-slot ring: segments of 1 to 11 tiles that end in each slot, with and
+# without a tile that straddles the two key segments, chunks shorter than a tile, behind one another in one workgroup's
+# run (with a workspace).  The gathered form reads the same rows through an index list: the same bits without a cut.
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 128, 191, 256, 320, 449, 512])
+def test_attention_tile_counts_and_boundaries(n, D):
+    N = 2
+    for Lc, L_B in [(1, 1), (63, 63), (64, 20), (65, 65), (130, 64)]:
+        Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n * 131 + Lc)
+        want = orc.chunk_attention(Q, Kc, Vc, Kn, Vn, block_len=L_B)
+        plain = _run(Q, Kc, Vc, Kn, Vn, L_B)
+        for got in (plain, _run(Q, Kc, Vc, Kn, Vn, L_B, ws=attention_workspace(D))):
+            max_abs, rel = attn_errors(got, want)
+            assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (Lc, L_B, max_abs, rel)
+        if n > 0:
+            rows = 2 * n + 1
+            at = np.sort(np.random.Generator(np.random.PCG64(n)).permutation(rows)[:n]).astype(np.int32)
+            K, V = (torch.full((rows, N, D), 7.0, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+            d_at = torch.from_numpy(at).to(DEV)
+            K[d_at.long()], V[d_at.long()] = dev(Kc, "bf16"), dev(Vc, "bf16")
+            O = torch.empty(Lc, N, D, device=DEV, dtype=torch.bfloat16)
+            B.pafu_chunk_attention_gather(dev(Q, "bf16"), K, V, d_at, n, dev(Kn, "bf16"), dev(Vn, "bf16"), L_B, O)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(O), plain), (Lc, L_B)
+
+
 def test_attention_peaked_softmax_and_fp32_output():
     # queries scaled x8: the softmax is peaked, |O| ~ 1, so the max-abs bound bites
     n, Lc, N, D = 500, 192, 2, 128
