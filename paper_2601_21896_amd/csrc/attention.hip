@@ -355,7 +355,8 @@ struct AttnWork {
   int n_items;        // heads of all layers * n_qt
   int n_whole;        // workgroup g < n_whole takes item g
   int n_runs;         // equal runs over the units of the items from n_whole on
-  long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list
+  long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list; U below 2^31
+  int h0, r0;         // head of unit u0, and the units of that head in front of it
   float* part_o;      // [2 n_runs][kAtBQ][D] fp32
   float* part_ml;     // [2 n_runs][2][kAtBQ] fp32: reference (log2 domain), row sum
 };
@@ -366,8 +367,7 @@ __host__ __device__ inline int attn_units(int qt, int Lq, int n_kept, int Lc, in
   const int vis = n_kept + (int)(e < Lc ? e : Lc);
   return ((vis + kAtTileKeys - 1) / kAtTileKeys + 1) / 2;
 }
-// first unit of run g when U units are cut into G runs
-__host__ __device__ inline long long attn_run_begin(long long g, long long U, long long G) { return g * U / G; }
+// (Run g of G begins with unit floor(g U / G).)
 
 struct AttnArgs {
   AttnParams p;
@@ -483,65 +483,64 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
   const float sc = p.scale_log2;
   int* const id_ring = reinterpret_cast<int*>(lds_raw + 2 * kAtStages * TILEB);  // gather variant (bf16 K/V only)
 
-  // ---- this workgroup's run of units [u, u_end) in the flattened (head, query tile, unit) list
-  long long u, u_end;
-  int qt, h, pre;  // current item and the units of its head that precede it
+  // ---- this workgroup's units: from unit `from` of item (h, qt) on, `room` of them.  (The setup is straight-line code that
+  // every launch fetches anew, so divisions and what only some launches need are kept out of the way of the others.)
+  const bool masked = L_B < p.Lc;
+  // (fetched with the other arguments: behind the divisions it would be another round trip to memory)
+  AttnLayer first_layer = args.layer[0];
+  asm volatile("" : "+s"(first_layer.Q), "+s"(first_layer.Kc), "+s"(first_layer.Vc), "+s"(first_layer.Kn), "+s"(first_layer.Vn), "+s"(first_layer.O));
+  int h, qt, from = 0, room = 0x7fffffff;
   if (is_run) {
-    u = uniform_i64(wk.u0 + attn_run_begin(wg, wk.U, wk.n_runs));
-    u_end = uniform_i64(wk.u0 + attn_run_begin(wg + 1, wk.U, wk.n_runs));
-    h = uniform_i32((int)(u / wk.units_head));
-    const int r = (int)(u - (long long)h * wk.units_head);
+    const int U = (int)wk.U, q = U / wk.n_runs, r = U - q * wk.n_runs;  // g U / G = g q + g r / G, G at most kAtMaxRuns
+    const int begin = wg * q + (int)((unsigned)(wg * r) / (unsigned)wk.n_runs);
+    room = uniform_i32((wg + 1) * q + (int)((unsigned)((wg + 1) * r) / (unsigned)wk.n_runs) - begin);
+    h = uniform_i32(wk.h0 + (wk.r0 + begin) / wk.units_head);
+    from = uniform_i32(wk.r0 + begin - (h - wk.h0) * wk.units_head);
     if (wk.uniform) {
-      qt = uniform_i32(r / wk.uniform);
-      pre = qt * wk.uniform;
+      qt = uniform_i32(from / wk.uniform);
+      from -= qt * wk.uniform;
     } else {
-      qt = 0;
-      pre = 0;
-      for (;;) {
+      for (qt = 0;; ++qt) {
         const int cq = attn_units(qt, p.Lq, p.n_kept, p.Lc, L_B);
-        if (pre + cq > r) break;
-        pre += cq;
-        ++qt;
+        if (from < cq) break;
+        from -= cq;
       }
     }
   } else {
     h = uniform_i32(wg / wk.n_qt);
     qt = wg - h * wk.n_qt;
-    pre = 0;
-    if (wk.uniform) pre = qt * wk.uniform;
-    else
-      for (int q2 = 0; q2 < qt; ++q2) pre += attn_units(q2, p.Lq, p.n_kept, p.Lc, L_B);
-    u = (long long)h * wk.units_head + pre;
-    u_end = u + attn_units(qt, p.Lq, p.n_kept, p.Lc, L_B);
   }
   bool first_segment = true;
 
 #pragma unroll 1
-  while (u < u_end) {
+  for (;;) {
     // ---- segment: units [pa, pb) of item (h, qt) = key tiles [2 pa, 2 pb)
-    const int units = __builtin_amdgcn_readfirstlane(attn_units(qt, p.Lq, p.n_kept, p.Lc, L_B));
-    const int pa = __builtin_amdgcn_readfirstlane((int)(u - ((long long)h * wk.units_head + pre)));
-    const long long room = u_end - u;
-    const int pb = __builtin_amdgcn_readfirstlane(room < units - pa ? pa + (int)room : units);
+    const int units = wk.uniform ? wk.uniform : uniform_i32(attn_units(qt, p.Lq, p.n_kept, p.Lc, L_B));
+    const int pa = uniform_i32(from);
+    const int pb = uniform_i32(room < units - pa ? pa + room : units);
     const bool whole = pa == 0 && pb == units;
     const int n_iter = pb - pa;
     const int tb = 2 * pa;  // first key tile of the segment
     const int i_first = uniform_i32(qt) * kAtBQ;
-    const int layer = uniform_i32(h / p.N_heads);
-    const AttnLayer& L = args.layer[layer];
+    const int layer = h < p.N_heads ? 0 : uniform_i32(h / p.N_heads);
+    AttnLayer L = first_layer;
+    if (layer != 0) L = args.layer[layer];
     const long long head_off = (long long)uniform_i32(h - layer * p.N_heads) * D;
 
     // number of visible keys: per lane (its query) and the tile's first query, both cut at the segment's end
-    auto visible = [&](int i) {
-      const long long e = ((long long)(i / L_B) + 1) * L_B;
-      return p.n_kept + (int)(e < p.Lc ? e : p.Lc);
-    };
     const int key_end = 2 * pb * kAtTileKeys;
     const int q_row = i_first + qblk * 32 + c;
-    const int lim_q = visible(q_row < p.Lq ? q_row : p.Lq - 1);
-    const int lim = lim_q < key_end ? lim_q : key_end;
-    const int lim_first = visible(i_first);
-    const int lim_min = lim_first < key_end ? lim_first : key_end;
+    int lim = p.n_kept + p.Lc, lim_min = lim;
+    if (masked) {
+      auto visible = [&](int i) {
+        const long long e = ((long long)(i / L_B) + 1) * L_B;
+        return p.n_kept + (int)(e < p.Lc ? e : p.Lc);
+      };
+      lim = visible(q_row < p.Lq ? q_row : p.Lq - 1);
+      lim_min = visible(i_first);
+    }
+    lim = lim < key_end ? lim : key_end;
+    lim_min = lim_min < key_end ? lim_min : key_end;
 
     // ids ring (gather variant): slot u % kAtIdStages holds the 64 ids of tile u, clamped to the list's end
     auto issue_ids = [&](int tile) {
@@ -559,6 +558,13 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       const int id = ((const __attribute__((address_space(3))) int*)id_ring)[(tile % kAtIdStages) * kAtTileKeys + row];
       return id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1);
     };
+    // gather variant: the cache segment's full tiles, this layer's and head's rows, this lane's place in the ids ring
+    const int gather_tiles = GATHER ? p.n_kept / kAtTileKeys : 0;
+    const unsigned gather_ld = (unsigned)(p.ld_c * ELB);
+    const char* const k_rows = GATHER ? static_cast<const char*>(L.Kc) + head_off * ELB : nullptr;
+    const char* const v_rows = GATHER ? static_cast<const char*>(L.Vc) + head_off * ELB : nullptr;
+    const lds_byte* const id_at = (const lds_byte*)id_ring + (wave * RPI + lane / SCH) * 4;
+    const unsigned k_chunk16 = (unsigned)lane_chunk(wave, lane, false) << 4, v_chunk16 = (unsigned)lane_chunk(wave, lane, true) << 4;
     // Tile t of the segment goes to ring slot t % kAtStages.
     auto lds_slot = [&](bool is_v, int slot, int j) {  // this wave's load j of a slot, from lds_wave on
       return (int)((is_v ? v_land : k_land) - (lds_byte*)lds_raw) + slot * STILEB + kAtWaves * j * 1024;
@@ -575,17 +581,19 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       asm volatile("" : "+s"(r.wave));
       return r;
     };
-    auto head_base = [&](const Rare& r, bool is_v, bool chunk) {  // row 0 of the key axis of this head
-      const auto& l = r.a->layer[layer];
-      const void* t = is_v ? (chunk ? l.Vn : l.Vc) : (chunk ? l.Kn : l.Kc);
-      return static_cast<const char*>(t) + head_off * ELB - (chunk ? (long long)r.a->p.n_kept * r.a->p.ld_n * ELB : 0);
+    // row 0 of the key axis of this head, in either segment
+    auto cache_base = [&](const void* t) { return static_cast<const char*>(t) + head_off * ELB; };
+    auto chunk_base = [&](const void* t, int kept, long long ld_n) {
+      return static_cast<const char*>(t) + head_off * ELB - (long long)kept * ld_n * ELB;
     };
     // The general copy works row by row: a tile that straddles the two key segments, or the end of the keys (rows past it
     // are masked later, so they read a valid one instead).
     auto copy_rows = [&](int tile, int slot, bool is_v) {
       const Rare r = rare();
-      const char *base_c = head_base(r, is_v, false), *base_n = head_base(r, is_v, true);
+      const auto& l = r.a->layer[layer];
       const int kept = r.a->p.n_kept, keys = kept + r.a->p.Lc;
+      const char* base_c = cache_base(is_v ? l.Vc : l.Kc);
+      const char* base_n = chunk_base(is_v ? l.Vn : l.Kn, kept, r.a->p.ld_n);
       const unsigned ldc_b = (unsigned)(r.a->p.ld_c * ELB), ldn_b = (unsigned)(r.a->p.ld_n * ELB);  // (below 4 GiB)
 #pragma unroll
       for (int j = 0; j < LPT; ++j) {
@@ -612,32 +620,45 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       int left;
     };
     TileStream ks, vs;
-    auto seek = [&](TileStream& s, int tile, bool is_v) {  // prepares the copies from `tile` on; left = 0: not a full tile
-      const Rare r = rare();
-      const int kept = r.a->p.n_kept, keys = kept + r.a->p.Lc;
+    // prepares the copies from `tile` on; left = 0: not a full tile
+    auto seek_in = [&](TileStream& s, int tile, bool is_v, const void* cache_t, const void* chunk_t, int kept, int Lc,
+                       long long ld_c, long long ld_n, int wave, int lane) {
+      const int keys = kept + Lc;
       const int key0 = tile * kAtTileKeys;
       const bool cache = key0 + kAtTileKeys <= kept, past = key0 >= keys;
       const bool chunk = key0 >= kept && key0 + kAtTileKeys <= keys;
       s.left = uniform_i32(past ? 0x7fffffff
                                 : cache && !GATHER ? kept / kAtTileKeys - tile : chunk ? keys / kAtTileKeys - tile : 0);
-      const unsigned ld_b = (unsigned)((cache ? r.a->p.ld_c : r.a->p.ld_n) * ELB);
+      const unsigned ld_b = (unsigned)((cache ? ld_c : ld_n) * ELB);
       const unsigned step = past ? 0u : ld_b;
       s.half = (unsigned)uniform_i32((int)((unsigned)(kAtWaves * RPI) * step));
       s.base = reinterpret_cast<const char*>(
-          uniform_i64((long long)reinterpret_cast<uintptr_t>(head_base(r, is_v, !cache)) +
+          uniform_i64((long long)reinterpret_cast<uintptr_t>(cache ? cache_base(cache_t) : chunk_base(chunk_t, kept, ld_n)) +
                       (long long)((unsigned long long)(unsigned)(past ? keys - 1 : key0) * ld_b)));
-      s.off = (unsigned)(r.wave * RPI + r.lane / SCH) * step + lane_chunk(r.wave, r.lane, is_v) * 16;
+      s.off = (unsigned)(wave * RPI + lane / SCH) * step + lane_chunk(wave, lane, is_v) * 16;
+    };
+    auto seek = [&](TileStream& s, int tile, bool is_v) {
+      const Rare r = rare();
+      const auto& l = r.a->layer[layer];
+      seek_in(s, tile, is_v, is_v ? l.Vc : l.Kc, is_v ? l.Vn : l.Kn, r.a->p.n_kept, r.a->p.Lc, r.a->p.ld_c, r.a->p.ld_n,
+              r.wave, r.lane);
+    };
+    // Gather variant: the cache rows behind a tile's rows, read from the ids ring some slots before their copies are started
+    // (right in front of them the wave waited for the LDS twice per tensor and step).
+    unsigned row_ids[LPT];
+    auto read_ids = [&](int tile) {
+      const lds_byte* at = id_at + (tile % kAtIdStages) * (kAtTileKeys * 4);
+#pragma unroll
+      for (int j = 0; j < LPT; ++j)
+        row_ids[j] = *(const __attribute__((address_space(3))) unsigned*)(at + kAtWaves * RPI * 4 * j);
     };
     auto copy_tile = [&](TileStream& s, int tile, int slot, bool is_v) {
-      if (GATHER && (tile + 1) * kAtTileKeys <= p.n_kept) {  // workgroup-uniform
-        // Registers are scarce here, so nothing per-lane is kept between steps: the swizzled chunk is recomputed and the
-        // address is the head's base plus a 32-bit offset (the host rejects caches of 4 GiB or more per tensor for this
-        // variant).
-        const unsigned chunk16 = (unsigned)lane_chunk(wave, lane, is_v) << 4;
+      if (GATHER && tile < gather_tiles) {  // workgroup-uniform
+        // the head's base plus a 32-bit offset (the host rejects caches of 4 GiB or more per tensor for this variant)
 #pragma unroll
         for (int j = 0; j < LPT; ++j) {
-          const int id = tile_id(tile, (wave + kAtWaves * j) * RPI + lane / SCH);
-          dma_row_chunks_at(static_cast<const char*>(is_v ? L.Vc : L.Kc) + head_off * ELB, (unsigned)id * (unsigned)(p.ld_c * ELB) + chunk16, lds_wave,
+          const unsigned id = row_ids[j] < (unsigned)p.n_cache ? row_ids[j] : (int)row_ids[j] < 0 ? 0u : (unsigned)p.n_cache - 1;
+          dma_row_chunks_at(is_v ? v_rows : k_rows, id * gather_ld + (is_v ? v_chunk16 : k_chunk16), lds_wave,
                             lds_slot(is_v, slot, j));
         }
         return;
@@ -666,8 +687,14 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
     // finished in the group before.  8-bit: step t copies K(t+5) and V(t+3) into the raw slots that step t-1 has converted.
     // Tiles past the end of the key axis hold clamped rows and are masked or never read.
     // In the gather variant the ids of the tiles must already be visible in the ids ring.
-    auto issue_k_tile = [&](int kt, int slot) { copy_tile(ks, tb + kt, slot, false); };
-    auto issue_v_tile = [&](int vt, int slot) { copy_tile(vs, tb + vt, slot, true); };
+    auto issue_k_tile = [&](int kt, int slot, bool ids_read = false) {
+      if (GATHER && !ids_read) read_ids(tb + kt);
+      copy_tile(ks, tb + kt, slot, false);
+    };
+    auto issue_v_tile = [&](int vt, int slot, bool ids_read = false) {
+      if (GATHER && !ids_read) read_ids(tb + vt);
+      copy_tile(vs, tb + vt, slot, true);
+    };
     // 8-bit K/V: this wave's 1 KB of a raw tile (the part it copied itself, so only its own copies must have landed)
     // -> bf16, from raw slot `from` into bf16 slot `to`.  Lane l holds 16 codes of key row w * RPI + l / SCH,
     // d = 16 (l % SCH) .. + 16: two 16-byte chunks of the bf16 row, stored with the swizzle of the fragment reads.
@@ -712,7 +739,8 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       wait_vmcnt<0>();
       __builtin_amdgcn_s_barrier();
     }
-    ks = vs = TileStream{nullptr, 0u, 0u, 0};
+    seek_in(ks, tb, false, L.Kc, L.Kn, p.n_kept, p.Lc, p.ld_c, p.ld_n, wave, lane);
+    seek_in(vs, tb, true, L.Vc, L.Vn, p.n_kept, p.Lc, p.ld_c, p.ld_n, wave, lane);
 #pragma unroll 1
     for (int i = 0; i < (KV8 ? 4 : 3); ++i) {
       issue_k_tile(i, i);
@@ -829,10 +857,14 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
                 if (i == KI) issue_k_tile(t + 5, (PH + 5) % kAtStages);
                 if (i == VI) issue_v_tile(t + 3, (PH + 3) % kAtStages);
               } else if (first) {
-                if (i == KI) issue_k_tile(t + 3, (PH + 3) % kAtStages);
-                if (i == 2 * KI) issue_k_tile(t + 4, PH);
-                if (i == VI) issue_v_tile(t + 1, (PH + 1) % kAtStages);
-                if (i == VI + KI) issue_v_tile(t + 2, (PH + 2) % kAtStages);
+                if (GATHER && i == KI - 2) read_ids(tb + t + 3);
+                if (i == KI) issue_k_tile(t + 3, (PH + 3) % kAtStages, true);
+                if (GATHER && i == 2 * KI - 1) read_ids(tb + t + 4);
+                if (i == 2 * KI) issue_k_tile(t + 4, PH, true);
+                if (GATHER && i == VI - 1) read_ids(tb + t + 1);
+                if (i == VI) issue_v_tile(t + 1, (PH + 1) % kAtStages, true);
+                if (GATHER && i == VI + KI - 1) read_ids(tb + t + 2);
+                if (i == VI + KI) issue_v_tile(t + 2, (PH + 2) % kAtStages, true);
               }
             });
         if (KV8) __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this step's bf16 rows are written
@@ -902,13 +934,12 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       }
     }
     // ---- next segment: the next item of the list, from its first unit
-    u += n_iter;
     first_segment = false;
-    if (u < u_end) {
-      __builtin_amdgcn_s_barrier();  // every wave has finished reading the ring before it is refilled
-      pre += units;
-      if (++qt == wk.n_qt) { qt = 0; pre = 0; ++h; }
-    }
+    room -= n_iter;
+    if (!is_run || room <= 0) break;
+    __builtin_amdgcn_s_barrier();  // every wave has finished reading the ring before it is refilled
+    from = 0;
+    if (++qt == wk.n_qt) { qt = 0; ++h; }
   }
 }
 
@@ -1045,6 +1076,7 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
   w.n_whole = (int)items;
   w.n_runs = 0;
   w.u0 = w.U = 0;
+  w.h0 = w.r0 = 0;
   w.part_o = nullptr;
   w.part_ml = nullptr;
   // Cut the last round when it fills at most four fifths of the CUs (above that the launch is limited by power, not by CU
@@ -1074,12 +1106,14 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
       if (2 * run <= 2 * ((U + runs - 1) / runs) + 3) runs = per_item * last;
     }
     const size_t need = (size_t)2 * runs * ((size_t)kAtBQ * D + 2 * kAtBQ) * sizeof(float);
-    if (runs > last && longest - (U + runs - 1) / runs >= kAtMinCutGain && workspace_bytes >= need &&
+    if (runs > last && longest - (U + runs - 1) / runs >= kAtMinCutGain && U < 1ll << 30 && workspace_bytes >= need &&
         (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
       w.n_whole = first_cut;
       w.n_runs = (int)runs;
       w.u0 = u0;
       w.U = U;
+      w.h0 = first_cut / w.n_qt;
+      w.r0 = (int)(u0 - (long long)w.h0 * units_head);
       w.part_o = static_cast<float*>(workspace);
       w.part_ml = w.part_o + (size_t)2 * runs * kAtBQ * D;
     }
