@@ -1012,6 +1012,220 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
   }
 }
 
+// ---- few queries over few keys --------------------------------------------------------------------------------------
+// A workgroup takes 32 queries of one head and its eight waves every eighth tile of 64 keys; their results are merged through
+// LDS.  Such a call is bound by latency: of arguments, of the first loads, of code that has to be fetched.  So everything a
+// wave needs for a tile is asked for at once (K and V rows into registers, from there through its own piece of LDS), there is
+// no ring and no pipeline, and the code is an eighth of the long kernel's. 
+// (Inside the smallest step, 2 heads of 64, 64 queries over 192 keys, the long kernel spent 2.6 k clocks per 64 keys, because
+// every step's code was new to the CU.)
+constexpr int kSmWaves = 8;
+constexpr int kSmQ = 32;                       // queries per workgroup
+// Where it is used: up to kSmTiles key tiles and kSmGroups workgroups.  A workgroup takes in all keys of its head, at what one
+// CU moves; the long kernel shares long lists among CUs.  Calls back to back, this / long: 16 tiles of D = 64, 40 workgroups
+// 10.0 / 15.1 us, 240 workgroups 15.2 / 20.0; 24 tiles, 40 workgroups 12.6 / 16.5; 32 tiles 15.2 / 13.9.  D = 128: 6 tiles, 48
+// workgroups 11.2 / 15.9, 80 workgroups 15.5 / 14.3; 13 tiles 27.8 / 21.4.  (All the forms of a call, gathered or not, take
+// the same side, so that they keep giving the same bits.)
+constexpr int kSmTiles64 = 24, kSmGroups64 = 256;
+constexpr int kSmTiles128 = 6, kSmGroups128 = 64;
+template <int D>
+constexpr int kSmRow = D + 4;                  // floats per merged row: a pad against bank conflicts
+template <int D>
+constexpr int small_lds_bytes() { return kSmWaves * kSmQ * kSmRow<D> * 4 + 2 * kSmWaves * kSmQ * 4; }
+static_assert(kSmQ * kSmRow<64> * 4 >= kAtTileKeys * 64 * 2 && kSmQ * kSmRow<128> * 4 >= kAtTileKeys * 128 * 2,
+              "a wave's V tile lies where its results go");
+
+template <int D, bool OUT_F32, bool GATHER>
+__global__ __launch_bounds__(kSmWaves * 64, 1) void attn_small_kernel(AttnArgs args) {
+  constexpr int ROWB = 2 * D, CH = D / 8, RPB = 256 / ROWB, KD = D / 16, DB = D / 32;
+  constexpr int VR = 64 / CH, VL = kAtTileKeys / VR;  // V: rows per wave-wide load, loads per tile
+  typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
+  typedef __attribute__((address_space(3))) float lds_float;
+  extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  const AttnParams& p = args.p;
+  AttnLayer L = args.layer[0];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int g = lane >> 5, c = lane & 31;
+  const int n_qb = (p.Lq + kSmQ - 1) / kSmQ;
+  const int h = uniform_i32((int)blockIdx.x / n_qb), q0 = ((int)blockIdx.x - h * n_qb) * kSmQ;
+  const int layer = h < p.N_heads ? 0 : uniform_i32(h / p.N_heads);
+  if (layer != 0) L = args.layer[layer];
+  const long long head_off = (long long)(h - layer * p.N_heads) * D;
+  const int n_total = p.n_kept + p.Lc;
+  const int q_row = q0 + c < p.Lq ? q0 + c : p.Lq - 1;
+  int lim = n_total, vis = n_total;  // visible keys: of this lane's query, of the workgroup's last one
+  if (p.block_len < p.Lc) {
+    auto visible = [&](int i) {
+      const long long e = ((long long)(i / p.block_len) + 1) * p.block_len;
+      return p.n_kept + (int)(e < p.Lc ? e : p.Lc);
+    };
+    lim = visible(q_row);
+    vis = uniform_i32(visible(q0 + kSmQ - 1 < p.Lq ? q0 + kSmQ - 1 : p.Lq - 1));
+  }
+  const int tiles = (vis + kAtTileKeys - 1) / kAtTileKeys;
+  lds_byte* const mine = (lds_byte*)lds_raw + wave * (kSmQ * kSmRow<D> * 4);
+  lds_float* const merge_ml = (lds_float*)((lds_byte*)lds_raw + kSmWaves * kSmQ * kSmRow<D> * 4);
+
+  if (wave < tiles) {
+    auto row_at = [&](const void* cache, const void* chunk, int key) {  // (rows past the end are masked: a valid one instead)
+      key = key < n_total ? key : n_total - 1;
+      const bool in_cache = key < p.n_kept;
+      if (GATHER && in_cache) {  // a row through the index list, never outside the cache
+        const int id = p.ids[key];
+        return static_cast<const unsigned short*>(cache) + head_off +
+               (long long)(id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1)) * p.ld_c;
+      }
+      return static_cast<const unsigned short*>(in_cache ? cache : chunk) + head_off +
+             (long long)(in_cache ? key : key - p.n_kept) * (in_cache ? p.ld_c : p.ld_n);
+    };
+    const unsigned short* qp = static_cast<const unsigned short*>(L.Q) + (long long)q_row * p.ld_q + head_off + 8 * g;
+    bf16x8 qf[KD];
+#pragma unroll
+    for (int kk = 0; kk < KD; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + 16 * kk);
+    f32x16 o[DB];
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
+    float msc = kAtNoMax, l_run = 0.f;
+    const float sc = p.scale_log2;
+    // K and V^T fragments: as in the long kernel
+    const int kx2 = g ^ ((c / RPB) & (CH - 1));
+    const lds_byte* const k_rd = mine + c * ROWB;
+    const int i16 = lane & 15, rr = 4 * g + (i16 >> 2);
+    const int vx2 = 4 * ((rr / RPB) & (CH / 4 - 1));
+    const lds_byte* const v_rd = mine + rr * ROWB + ((i16 & 1) << 3) + ((2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1)) << 4);
+
+#pragma unroll 1
+    for (int t = wave; t < tiles; t += kSmWaves) {
+      const int key0 = t * kAtTileKeys;
+      u32x4 kv[VL], vv[VL];
+#pragma unroll
+      for (int j = 0; j < VL; ++j)
+        kv[j] = *reinterpret_cast<const u32x4*>(row_at(L.Kc, L.Kn, key0 + VR * j + lane / CH) + 8 * (lane % CH));
+#pragma unroll
+      for (int j = 0; j < VL; ++j)
+        vv[j] = *reinterpret_cast<const u32x4*>(row_at(L.Vc, L.Vn, key0 + VR * j + lane / CH) + 8 * (lane % CH));
+      auto to_lds = [&](const u32x4(&x)[VL], bool is_v) {  // with the swizzles of the long kernel
+#pragma unroll
+        for (int j = 0; j < VL; ++j) {
+          const int row = VR * j + lane / CH;
+          const int ch = (lane % CH) ^ (is_v ? 4 * ((row / RPB) & (CH / 4 - 1)) : (row / RPB) & (CH - 1));
+          *(lds_u32x4*)(mine + row * ROWB + (ch << 4)) = x[j];
+        }
+        __builtin_amdgcn_wave_barrier();  // (one wave's LDS operations keep their order)
+      };
+      to_lds(kv, false);
+      f32x16 s[2];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb) {
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[kb][r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KD; ++kk)
+          s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read_k(k_rd + kb * 32 * ROWB + (((2 * kk) ^ kx2) << 4)), qf[kk],
+                                                          s[kb], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+      to_lds(vv, true);
+      attn_mask(s, key0, lim, g);
+      float mx = s[0][0];
+#pragma unroll
+      for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+      const float msc_new = fmaxf(msc, half_swap_max(mx) * sc);
+      const float down = __builtin_amdgcn_exp2f(msc - msc_new);
+      msc = msc_new;
+      float psum = 0.f;
+      u32x4 pw[4];
+#pragma unroll
+      for (int e = 0; e < 32; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][e & 15], sc, -msc));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][(e & 15) + 1], sc, -msc));
+        psum += p0;
+        psum += p1;
+        pw[e >> 3][(e & 7) >> 1] = pack_bf16(p0, p1);
+      }
+      l_run = fmaf(l_run, down, psum);
+#pragma unroll
+      for (int b = 0; b < DB; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[b][r] *= down;
+#pragma unroll
+      for (int m = 0; m < 4 * DB; ++m) {
+        const bf16x8 a = lds_read_vt(v_rd + (16 * (m / DB)) * ROWB + (((4 * (m % DB)) ^ vx2) << 4), 8 * ROWB);
+        o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pw[m / DB]), o[m % DB], 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    // this wave's result: lane holds query c, d = 32 b + 8 (r/4) + 4 g + (r%4)
+    const float l_tot = half_swap_sum(l_run);
+    if (g == 0) {
+      merge_ml[wave * kSmQ + c] = msc;
+      merge_ml[(kSmWaves + wave) * kSmQ + c] = l_tot;
+    }
+#pragma unroll
+    for (int b = 0; b < DB; ++b)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        const u32x4 v = {__float_as_uint(o[b][4 * q4]), __float_as_uint(o[b][4 * q4 + 1]), __float_as_uint(o[b][4 * q4 + 2]),
+                         __float_as_uint(o[b][4 * q4 + 3])};
+        *(lds_u32x4*)(mine + (c * kSmRow<D> + 32 * b + 8 * q4 + 4 * g) * 4) = v;
+      }
+  }
+  __syncthreads();
+  // merge, in the order of the waves: 16 threads per query, D / 16 outputs each
+  const int row = tid / 16, n_w = tiles < kSmWaves ? tiles : kSmWaves;
+  float m = kAtNoMax;
+  for (int w = 0; w < n_w; ++w) m = fmaxf(m, merge_ml[w * kSmQ + row]);
+  float l = 0.f;
+  float acc[D / 16];
+#pragma unroll
+  for (int i = 0; i < D / 16; ++i) acc[i] = 0.f;
+  for (int w = 0; w < n_w; ++w) {
+    const float wgt = __builtin_amdgcn_exp2f(merge_ml[w * kSmQ + row] - m);
+    l = fmaf(merge_ml[(kSmWaves + w) * kSmQ + row], wgt, l);
+#pragma unroll
+    for (int q4 = 0; q4 < D / 64; ++q4) {
+      const lds_byte* at = (const lds_byte*)lds_raw + ((w * kSmQ + row) * kSmRow<D> + 64 * q4 + 4 * (tid % 16)) * 4;
+      const u32x4 v = *(const lds_u32x4*)at;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[4 * q4 + i] = fmaf(__uint_as_float(v[i]), wgt, acc[4 * q4 + i]);
+    }
+  }
+  if (q0 + row >= p.Lq) return;
+  const float inv = 1.0f / l;
+#pragma unroll
+  for (int q4 = 0; q4 < D / 64; ++q4) {
+    const long long off = (long long)(q0 + row) * p.ld_o + head_off + 64 * q4 + 4 * (tid % 16);
+    if (OUT_F32) {
+      *reinterpret_cast<float4*>(static_cast<float*>(L.O) + off) =
+          make_float4(acc[4 * q4] * inv, acc[4 * q4 + 1] * inv, acc[4 * q4 + 2] * inv, acc[4 * q4 + 3] * inv);
+    } else {
+      bf16x4 ob;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) ob[i] = (__bf16)(acc[4 * q4 + i] * inv);
+      *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(L.O) + off) = ob;
+    }
+  }
+}
+
+template <int D, bool OUT_F32, bool GATHER>
+int launch_small(hipStream_t st, const AttnArgs& a, int heads) {
+  static LdsLimit lds_limit;
+  const int rc = set_lds_limit(lds_limit, attn_small_kernel<D, OUT_F32, GATHER>, small_lds_bytes<D>());
+  if (rc != PAFU_OK) return rc;
+  hipLaunchKernelGGL((attn_small_kernel<D, OUT_F32, GATHER>), dim3(heads * ((a.p.Lq + kSmQ - 1) / kSmQ)),
+                     dim3(kSmWaves * 64), small_lds_bytes<D>(), st, a);
+  return check_launch();
+}
+template <bool GATHER>
+int launch_small_dims(hipStream_t st, const AttnArgs& a, int heads, int D, bool f32) {
+  if (D == 128) return f32 ? launch_small<128, true, GATHER>(st, a, heads) : launch_small<128, false, GATHER>(st, a, heads);
+  return f32 ? launch_small<64, true, GATHER>(st, a, heads) : launch_small<64, false, GATHER>(st, a, heads);
+}
+
 template <int D, bool OUT_F32, bool GATHER, bool KV8 = false>
 int launch_variant(hipStream_t st, const AttnArgs& a) {
   static LdsLimit lds_limit;
@@ -1056,6 +1270,13 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
   p.scale_log2 = scale * 1.44269504088896340736f;
   p.k_scale = k_scale;
   p.v_scale = v_scale;
+
+  const bool f32 = out_dtype == PAFU_F32, gather = ids != nullptr && n_kept > 0;
+  const long long tiles = ((long long)n_kept + Lc + kAtTileKeys - 1) / kAtTileKeys;
+  const long long groups = (long long)N * n_layers * ((Lq + kSmQ - 1) / kSmQ);
+  if (kv_dtype == PAFU_BF16 && tiles <= (D == 64 ? kSmTiles64 : kSmTiles128) &&
+      groups <= (D == 64 ? kSmGroups64 : kSmGroups128))
+    return gather ? launch_small_dims<true>(st, a, N * n_layers, D, f32) : launch_small_dims<false>(st, a, N * n_layers, D, f32);
 
   AttnWork& w = a.w;
   w.n_qt = (Lq + kAtBQ - 1) / kAtBQ;
@@ -1118,10 +1339,9 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
       w.part_ml = w.part_o + (size_t)2 * runs * kAtBQ * D;
     }
   }
-  const bool f32 = out_dtype == PAFU_F32;
   if (kv_dtype == PAFU_FP8_E4M3)  // validated by the caller: head dim 128, no index list
     return f32 ? launch_variant<128, true, false, true>(st, a) : launch_variant<128, false, false, true>(st, a);
-  return ids != nullptr && n_kept > 0 ? launch_dims<true>(st, a, D, f32) : launch_dims<false>(st, a, D, f32);
+  return gather ? launch_dims<true>(st, a, D, f32) : launch_dims<false>(st, a, D, f32);
 }
 
 }  // namespace pafu

@@ -83,6 +83,33 @@ def test_attention_tile_counts_and_boundaries(n, D):
             assert np.array_equal(host(O), plain), (Lc, L_B)
 
 
+# Both sides of the line between the kernel for few queries over few keys and the long one (24 tiles and 256 groups of 32
+# queries at head dim 64, 6 and 64 at 128), with all forms of output, block masks, and the gathered form's bits.
+@pytest.mark.parametrize("n,Lc,N,D,L_B,odt", [
+    (1472, 64, 2, 64, 64, torch.float32), (1473, 64, 2, 64, 64, torch.float32),     # 24 and 25 tiles
+    (1400, 100, 4, 64, 33, torch.bfloat16), (40, 33, 128, 64, 5, torch.bfloat16),   # three tiles per wave; 256 groups
+    (40, 33, 130, 64, 5, torch.bfloat16), (0, 130, 64, 64, 130, torch.bfloat16),    # 260 and 320
+    (65, 130, 64, 64, 64, torch.bfloat16), (191, 130, 64, 64, 7, torch.float32), (512, 130, 64, 64, 130, torch.bfloat16),
+    (254, 130, 2, 128, 40, torch.float32), (255, 130, 2, 128, 40, torch.float32),   # 6 and 7 tiles
+    (65, 130, 12, 128, 130, torch.bfloat16), (65, 130, 13, 128, 130, torch.bfloat16),  # 60 and 65 groups
+])
+def test_attention_few_queries_over_few_keys(n, Lc, N, D, L_B, odt):
+    # a peaked softmax in fp32 only: |O| passes 4 there, where half a unit of a bf16 result (2^-6) and the rounding of the
+    # weights (2^-9 |V|, |V| up to 4.8) already add up to 0.025
+    for gain in (1.0, 8.0) if odt == torch.float32 else (1.0,):
+        Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n + 3 * Lc + N, q_gain=gain)
+        got = _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=odt)
+        max_abs, rel = attn_errors(got, orc.chunk_attention(Q, Kc, Vc, Kn, Vn, block_len=L_B))
+        assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (gain, max_abs, rel)
+        if n > 0:
+            ids = torch.arange(n, dtype=torch.int32, device=DEV)
+            O = torch.empty(Lc, N, D, device=DEV, dtype=odt)
+            B.pafu_chunk_attention_gather(dev(Q, "bf16"), dev(Kc, "bf16"), dev(Vc, "bf16"), ids, n, dev(Kn, "bf16"),
+                                          dev(Vn, "bf16"), L_B, O)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(O), got), gain
+
+
 def test_attention_peaked_softmax_and_fp32_output():
     # queries scaled x8: the softmax is peaked, |O| ~ 1, so the max-abs bound bites
     n, Lc, N, D = 500, 192, 2, 128
