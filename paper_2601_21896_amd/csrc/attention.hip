@@ -985,22 +985,45 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
   const int slot_first = 2 * g_first + (attn_div(g_first * U, G, U * G) >= s ? 0 : 1);
   auto slot_of = [&](int gg) { return gg == g_first ? slot_first : 2 * gg; };
   const int d0 = 4 * (threadIdx.x % (D / 4));
+  // All that is needed of up to kAhead runs is asked for at once (run by run it was a wait for memory each, twice); most items
+  // have no more.  1560 queries (12 heads of 128, three runs per item) 10.5 -> 8.4 us, 3121 (unequal items) 16.5 -> 13.9.
+  constexpr int kAhead = 4;
+  struct Run {
+    float m, l;
+    float4 v;
+  };
+  auto fetch = [&](int gg, bool with_v) {
+    const long long sl = slot_of(gg < g_last ? gg : g_last);
+    const float* ml = wk.part_ml + sl * 2 * kAtBQ + row;
+    Run r;
+    r.m = ml[0];
+    r.l = with_v ? ml[kAtBQ] : 0.f;
+    r.v = with_v ? *reinterpret_cast<const float4*>(wk.part_o + (sl * kAtBQ + row) * D + d0) : make_float4(0.f, 0.f, 0.f, 0.f);
+    return r;
+  };
+  Run first[kAhead];
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) first[i] = fetch(g_first + i, true);
   float m = kAtNoMax;
-  for (int gg = g_first; gg <= g_last; ++gg) m = fmaxf(m, wk.part_ml[(long long)slot_of(gg) * 2 * kAtBQ + row]);
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i) m = fmaxf(m, first[i].m);  // (the last run again where there are fewer)
+#pragma unroll 4
+  for (int gg = g_first + kAhead; gg <= g_last; ++gg) m = fmaxf(m, fetch(gg, false).m);
   float l = 0.f;
   float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  auto add = [&](const Run& r) {
+    const float wgt = __builtin_amdgcn_exp2f(r.m - m);
+    l += r.l * wgt;
+    acc.x = fmaf(r.v.x, wgt, acc.x); acc.y = fmaf(r.v.y, wgt, acc.y);
+    acc.z = fmaf(r.v.z, wgt, acc.z); acc.w = fmaf(r.v.w, wgt, acc.w);
+  };
+#pragma unroll
+  for (int i = 0; i < kAhead; ++i)
+    if (g_first + i <= g_last) add(first[i]);
 #pragma unroll 4
-  for (int gg = g_first; gg <= g_last; ++gg) {
-    const long long sl = slot_of(gg);
-    const float* ml = wk.part_ml + sl * 2 * kAtBQ + row;
-    const float4 v = *reinterpret_cast<const float4*>(wk.part_o + (sl * kAtBQ + row) * D + d0);
-    const float wgt = __builtin_amdgcn_exp2f(ml[0] - m);
-    l += ml[kAtBQ] * wgt;
-    acc.x = fmaf(v.x, wgt, acc.x); acc.y = fmaf(v.y, wgt, acc.y);
-    acc.z = fmaf(v.z, wgt, acc.z); acc.w = fmaf(v.w, wgt, acc.w);
-  }
+  for (int gg = g_first + kAhead; gg <= g_last; ++gg) add(fetch(gg, true));
   const float inv = 1.0f / l;
-  const int layer = h / p.N_heads;
+  const int layer = h < p.N_heads ? 0 : h / p.N_heads;
   void* const O = args.layer[layer].O;
   const long long off = (long long)q_row * p.ld_o + (long long)(h - layer * p.N_heads) * D + d0;
   if (OUT_F32) {
