@@ -7,7 +7,8 @@
 // prefix scans provide, so the result depends only on the score bits, never on atomic arrival order.
 //
 // The whole score list is a few hundred KB at most (one fp32 per cached token), so the work is
-// latency-bound and one workgroup handles one list.  Lists of up to 98304 scores use the bit-sliced
+// latency-bound and one workgroup handles one list (one wave, up to 2048 scores: its passes need no barrier; 64 to 2048
+// scores 6.2-7.2 -> 5.0-5.6 us, equal ones 10.5 -> 7.7, against four waves).  Lists of up to 98304 scores use the bit-sliced
 // kernel: each thread loads its 32 W consecutive keys ONCE and transposes them into 32 bit-planes of W
 // words; a radix-2 pass is then two instructions per word (and + popcount) plus one block-wide sum, and
 // the "greater" and "equal" masks the emit needs fall out of the 32 passes.  Longer lists fall back to
@@ -181,7 +182,8 @@ int launch_select_batch(hipStream_t st, const SelectJob* jobs, int count) {
     if (rc_ != PAFU_OK) return rc_;                                                                               \
     hipLaunchKernelGGL((select_bitslice_kernel<W, NT>), dim3(m), dim3(NT), select_bitslice_lds_bytes(NT), st, B); \
   } while (0)
-    if (n_max <= 256 * 32) PAFU_SELECT_CASE(1, 256);
+    if (n_max <= 64 * 32) PAFU_SELECT_CASE(1, 64);
+    else if (n_max <= 256 * 32) PAFU_SELECT_CASE(1, 256);
     else if (n_max <= 512 * 32 * 2) PAFU_SELECT_CASE(2, 512);
     else if (n_max <= 1024 * 32 * 2) PAFU_SELECT_CASE(2, 1024);
     else if (n_max <= 1024 * 32 * 3) PAFU_SELECT_CASE(3, 1024);

@@ -169,11 +169,15 @@ __device__ __forceinline__ void select_bitslice_body(const SelectProblem& P) {
 #pragma unroll
     for (int w = 0; w < W; ++w) cnt += __builtin_popcount(cand[w] & plane[w][p]);
     const int wsum = wave_sum(cnt);
-    if (lane == 0) part[(p & 1) * kWaves + wave] = wsum;
-    __syncthreads();
     int over = missing;  // candidates with the bit set, minus the places
+    if constexpr (kWaves == 1) {  // nobody to wait for: neither LDS nor a barrier in a pass
+      over += wsum;
+    } else {
+      if (lane == 0) part[(p & 1) * kWaves + wave] = wsum;
+      __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kWaves; ++i) over += part[(p & 1) * kWaves + i];
+      for (int i = 0; i < kWaves; ++i) over += part[(p & 1) * kWaves + i];
+    }
     if (over >= 0) {  // the k-th key has this bit set
       surplus = over;
 #pragma unroll

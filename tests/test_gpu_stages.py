@@ -127,6 +127,24 @@ def test_select_matches_oracle_with_ties(n):
             assert np.array_equal(got, orc.select_topk(s, k)), (n, k)
 
 
+# both sides of the line between one wave and four, with ties, special values and a pinned prefix
+@pytest.mark.parametrize("n", [33, 1985, 2016, 2047, 2048, 2049])
+def test_select_lists_for_one_wave(n):
+    rng = np.random.default_rng(3 * n)
+    s = (rng.integers(-5, 6, size=n) * 0.25).astype(np.float32)
+    special = np.array([np.nan, np.inf, -np.inf, 0.0, -0.0, 1e-45, 3.4e38], dtype=np.float32)
+    mixed = s.copy()
+    mixed[rng.choice(n, size=n // 6, replace=False)] = special[rng.integers(0, len(special), size=n // 6)]
+    mixed[-1] = np.nan
+    for x in (s, mixed, rng.standard_normal(n).astype(np.float32)):
+        for k in (1, 31, n // 2, n - 2, n - 1):
+            assert np.array_equal(_run_select(x, k), orc.select_topk(x, k)), (n, k)
+            out = torch.empty(k, dtype=torch.int32, device=DEV)
+            B.pafu_select_topk_pinned(torch.from_numpy(x).to(DEV), k, n // 5, out, None)
+            torch.cuda.synchronize()
+            assert np.array_equal(out.cpu().numpy(), orc.select_topk(x, k, n // 5)), (n, k)
+
+
 @pytest.mark.parametrize("n,k,n_pinned", [(1000, 400, 100), (1000, 50, 100), (4097, 2000, 1560), (32760, 16380, 1560),
                                          (32760, 16380, 0), (60000, 20000, 4680), (75600, 22680, 1560),
                                          (300, 300, 10), (300, 10, 300), (64, 0, 5)])
