@@ -25,7 +25,7 @@
 // reference, with the rescale of O^T, is a rare out-of-line event.
 //
 // K/V tiles (64 keys) stream from global memory straight into a 4-deep LDS ring (global_load_lds, no
-// staging registers) three tiles ahead of their use; rows are stored with an XOR swizzle of their
+// staging registers) two to four tiles ahead of their use; rows are stored with an XOR swizzle of their
 // 16-byte chunks so that both the b128 K reads and the transposing V reads are bank-conflict free
 // without padding.  The two key segments (retained cache, chunk) are addressed row by row, so no
 // concatenated copy exists.
