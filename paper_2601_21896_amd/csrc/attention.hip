@@ -142,6 +142,51 @@ __device__ __forceinline__ bf16x8 lds_read_vt(const lds_byte* p, int row_bytes8)
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// Raises the reference msc of the queries whose tile has outgrown it (the sum of its weights, psum, has passed kAtMaxTileSum in
+// either lane half) and scales the tile's weights, their sum and the sum so far by it; returns what O^T is to be scaled by.
+__device__ __forceinline__ float attn_raise(const f32x16 (&s_cur)[2], u32x4 (&p_cur)[4], float sc, float& msc, float& l_run,
+                                            float& psum) {
+  float alpha = 1.f;
+  // far above the reference (the first tile that a query sees, behind masked ones): take its own maximum
+  if (__builtin_amdgcn_ballot_w64(psum > kAtMaxScaledSum) != 0) {
+    const bool grow = half_swap_max(psum > kAtMaxTileSum ? 1.f : 0.f) != 0.f;  // both halves of a query together
+    float mx = s_cur[0][0];
+#pragma unroll
+    for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[kb][r]);
+    mx = half_swap_max(mx);
+    const float msc_new = grow ? fmaxf(msc, mx * sc) : msc;
+    const float down = __builtin_amdgcn_exp2f(msc - msc_new);
+    msc = msc_new;
+    alpha = down;
+    l_run *= down;
+    psum = 0.f;
+#pragma unroll
+    for (int e = 0; e < 32; e += 2) {
+      const float pe0 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][e & 15], sc, -msc_new));
+      const float pe1 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][(e & 15) + 1], sc, -msc_new));
+      psum += pe0;
+      psum += pe1;
+      p_cur[e >> 3][(e & 7) >> 1] = pack_bf16(pe0, pe1);
+    }
+  }
+  const float up = half_swap_max(psum > kAtMaxTileSum ? (float)__builtin_amdgcn_frexp_expf(psum) : 0.f);
+  const float scale = __builtin_amdgcn_exp2f(-up);
+  msc += up;
+  l_run *= scale;
+  psum *= scale;
+  alpha *= scale;
+  const unsigned exponent = (unsigned)up * 0x00800080u;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    unsigned w = p_cur[i >> 2][i & 3];
+    asm("v_pk_sub_u16 %0, %0, %1 clamp" : "+v"(w) : "v"(exponent));
+    p_cur[i >> 2][i & 3] = w;
+  }
+  return alpha;
+}
+
 // Pipeline step t for one wave (32 queries), one straight-line block:
 //   matrix pipe : S^T(t+1) = K(t+1) Q^T into s_nxt;  O^T += V(t-1)^T P(t-1)^T from p_prev
 //   vector pipe : online softmax of s_cur = S^T(t) -> p_cur = P^T(t), running max / sum,
@@ -274,44 +319,7 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   // (An else branch that left P^T alone, or a shift that was not done in place, put copies of P^T into every step: + 4 %.
   // Laid out inside the loop, all this cost the 8-bit variant 1 %.)
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0, 0)) {
-    float alpha = 1.f;
-    // far above the reference (the first tile that a query sees, behind masked ones): take its own maximum
-    if (__builtin_amdgcn_ballot_w64(psum > kAtMaxScaledSum) != 0) {
-      const bool grow = half_swap_max(psum > kAtMaxTileSum ? 1.f : 0.f) != 0.f;  // both halves of a query together
-      float mx = s_cur[0][0];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s_cur[kb][r]);
-      mx = half_swap_max(mx);
-      const float msc_new = grow ? fmaxf(msc, mx * sc) : msc;
-      const float down = __builtin_amdgcn_exp2f(msc - msc_new);
-      msc = msc_new;
-      alpha = down;
-      l_run *= down;
-      psum = 0.f;
-#pragma unroll
-      for (int e = 0; e < 32; e += 2) {
-        const float pe0 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][e & 15], sc, -msc_new));
-        const float pe1 = __builtin_amdgcn_exp2f(fmaf(s_cur[e >> 4][(e & 15) + 1], sc, -msc_new));
-        psum += pe0;
-        psum += pe1;
-        p_cur[e >> 3][(e & 7) >> 1] = pack_bf16(pe0, pe1);
-      }
-    }
-    const float up = half_swap_max(psum > kAtMaxTileSum ? (float)__builtin_amdgcn_frexp_expf(psum) : 0.f);
-    const float scale = __builtin_amdgcn_exp2f(-up);
-    msc += up;
-    l_run *= scale;
-    psum *= scale;
-    alpha *= scale;
-    const unsigned exponent = (unsigned)up * 0x00800080u;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      unsigned w = p_cur[i >> 2][i & 3];
-      asm("v_pk_sub_u16 %0, %0, %1 clamp" : "+v"(w) : "v"(exponent));
-      p_cur[i >> 2][i & 3] = w;
-    }
+    const float alpha = attn_raise(s_cur, p_cur, sc, msc, l_run, psum);
 #pragma unroll
     for (int b = 0; b < DB; ++b)
 #pragma unroll
@@ -1036,110 +1044,214 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
 }
 
 // ---- few queries over few keys --------------------------------------------------------------------------------------
-// A workgroup takes 32 queries of one head and its eight waves every eighth tile of 64 keys; their results are merged through
-// LDS.  Such a call is bound by latency: of arguments, of the first loads, of code that has to be fetched.  So everything a
-// wave needs for a tile is asked for at once (K and V rows into registers, from there through its own piece of LDS), there is
-// no ring and no pipeline, and the code is an eighth of the long kernel's. 
-// (Inside the smallest step, 2 heads of 64, 64 queries over 192 keys, the long kernel spent 2.6 k clocks per 64 keys, because
-// every step's code was new to the CU.)
+// A workgroup takes 32 queries of one head.  Such a call is bound by latency: of arguments, of the first loads, of code that has
+// to be fetched.  So each of the eight waves asks for all of one key tile at once (K and V rows into registers, from there
+// through its own piece of LDS), there is no ring and no pipeline, and the code is a fraction of the long kernel's.  (2 heads of
+// 64, 64 queries over 192 keys: the long kernel spends 2.6 k clocks per 64 keys, because every step's code is new to the CU.)
+//
+// The arithmetic is the long kernel's, operation for operation, so that a query's result has the same bits whichever of the two
+// takes it (how many heads, layers or queries share a launch decides that): the reference is the first tile's maximum, S^T and
+// the weights of up to eight tiles are formed side by side, and O^T and the sum of the weights take the tiles in order, in one
+// wave per 32 rows of O^T.  A tile that outgrows the reference is rare: then the waves work out the weights of these tiles once
+// more, one tile after the other.
+//
+// What bounds it: the chain of launch, arguments, rows (and ids in front of them), two barriers, and the tiles of a turn in
+// order.  Each wave on its own over every eighth tile, with its own reference, and the eight results merged, gave other bits
+// than the long kernel, and gathered rows, whose addresses were worked out in 64 bits for K and again for V, spilled 24
+// registers at head dim 128.  That form / this one, calls back to back: 2 heads of 64, 64 queries over 192 keys 4.9 / 4.5 us
+// (gathered 7.5 / 4.7), 32 heads, 256 over 1536 keys 22.5 / 12.7 (39.1 / 14.0; now by XCD), 16 heads of 128, 128 over 328
+// keys 11.1 / 7.9 (15.7 / 8.3).
 constexpr int kSmWaves = 8;
 constexpr int kSmQ = 32;                       // queries per workgroup
-// Where it is used: up to kSmTiles key tiles and kSmGroups workgroups.  A workgroup takes in all keys of its head, at what one
-// CU moves; the long kernel shares long lists among CUs.  Calls back to back, this / long: 16 tiles of D = 64, 40 workgroups
-// 10.0 / 15.1 us, 240 workgroups 15.2 / 20.0; 24 tiles, 40 workgroups 12.6 / 16.5; 32 tiles 15.2 / 13.9.  D = 128: 6 tiles, 48
-// workgroups 11.2 / 15.9, 80 workgroups 15.5 / 14.3; 13 tiles 27.8 / 21.4.  (All the forms of a call, gathered or not, take
-// the same side, so that they keep giving the same bits.)
+// Where it is used: up to kSmTiles key tiles and kSmGroups workgroups (gathered or not, with a workspace or without).  Calls back
+// to back, this / the long kernel whole / cut with a workspace: head dim 64, 24 tiles, 4 workgroups 11.7 / 17.0 / 10.9 us, 256
+// (one per CU) 12.5 / 25.7 / 21.3, gathered 14.2 / 29.7 / 22.7, and 320 (two on some CUs) 23.5 / 26.0 / 22.4; 32 tiles, 4
+// workgroups 14.6 / 21.0 / 10.6: a workgroup takes in all keys of its head, the cut shares them among CUs.  Head dim 128 (its
+// calls are too short to be cut), 64 workgroups: 3 tiles 6.7 / 14.2, 6 tiles 7.6 / 13.7, gathered 8.0 / 16.1.
 constexpr int kSmTiles64 = 24, kSmGroups64 = 256;
 constexpr int kSmTiles128 = 6, kSmGroups128 = 64;
 template <int D>
-constexpr int kSmRow = D + 4;                  // floats per merged row: a pad against bank conflicts
-template <int D>
-constexpr int small_lds_bytes() { return kSmWaves * kSmQ * kSmRow<D> * 4 + 2 * kSmWaves * kSmQ * 4; }
-static_assert(kSmQ * kSmRow<64> * 4 >= kAtTileKeys * 64 * 2 && kSmQ * kSmRow<128> * 4 >= kAtTileKeys * 128 * 2,
-              "a wave's V tile lies where its results go");
+struct SmallLds {  // bytes from the start of the LDS
+  static constexpr int slots = D == 64 ? kSmWaves : kSmTiles128;        // tiles side by side
+  static constexpr int rounds = D == 64 ? (kSmTiles64 + kSmWaves - 1) / kSmWaves : 1;
+  static constexpr int tile = kAtTileKeys * 2 * D;
+  static constexpr int weights = slots * tile;                          // [slot][key slice][lane] 16 bytes: P^T fragments
+  static constexpr int sums = weights + slots * 4 * 64 * 16;            // [slot][lane] fp32: sums of the weights
+  static constexpr int alphas = sums + slots * 64 * 4;                  // [slot][query] fp32: what a raise scales O^T by
+  static constexpr int msc = alphas + slots * kSmQ * 4;                 // [query] fp32: the reference
+  static constexpr int outgrown = msc + kSmQ * 4;                       // [wave]: has its tile outgrown the reference?
+  static constexpr int bytes = outgrown + kSmWaves * 4;
+  static_assert(slots <= kSmWaves && bytes <= 160 * 1024, "");
+};
+static_assert(kSmTiles128 <= SmallLds<128>::slots, "head dim 128: all tiles side by side");
 
 template <int D, bool OUT_F32, bool GATHER>
 __global__ __launch_bounds__(kSmWaves * 64, 1) void attn_small_kernel(AttnArgs args) {
   constexpr int ROWB = 2 * D, CH = D / 8, RPB = 256 / ROWB, KD = D / 16, DB = D / 32;
-  constexpr int VR = 64 / CH, VL = kAtTileKeys / VR;  // V: rows per wave-wide load, loads per tile
+  constexpr int VR = 64 / CH, VL = kAtTileKeys / VR;  // rows per wave-wide load, loads per tile
+  typedef SmallLds<D> Lds;
   typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
   typedef __attribute__((address_space(3))) float lds_float;
+  typedef __attribute__((address_space(3))) int lds_int;
   extern __shared__ __attribute__((aligned(1024))) unsigned char lds_raw[];
+  lds_byte* const lds = (lds_byte*)lds_raw;
+  lds_float* const msc_of = (lds_float*)(lds + Lds::msc);
+  lds_int* const outgrown = (lds_int*)(lds + Lds::outgrown);
   const AttnParams& p = args.p;
   AttnLayer L = args.layer[0];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int g = lane >> 5, c = lane & 31;
+  // XCD x (workgroups x, x + 8, ...) takes one contiguous range of the groups, head by head: its L2 then sees the K/V of an
+  // eighth of the heads
+  const int xcd = blockIdx.x % kAtXcds, per_xcd = gridDim.x / kAtXcds, more = gridDim.x % kAtXcds;
+  const int group = xcd * per_xcd + (xcd < more ? xcd : more) + blockIdx.x / kAtXcds;
   const int n_qb = (p.Lq + kSmQ - 1) / kSmQ;
-  const int h = uniform_i32((int)blockIdx.x / n_qb), q0 = ((int)blockIdx.x - h * n_qb) * kSmQ;
+  const int h = uniform_i32(group / n_qb), q0 = (group - h * n_qb) * kSmQ;
   const int layer = h < p.N_heads ? 0 : uniform_i32(h / p.N_heads);
   if (layer != 0) L = args.layer[layer];
   const long long head_off = (long long)(h - layer * p.N_heads) * D;
   const int n_total = p.n_kept + p.Lc;
   const int q_row = q0 + c < p.Lq ? q0 + c : p.Lq - 1;
-  int lim = n_total, vis = n_total;  // visible keys: of this lane's query, of the workgroup's last one
+  int lim = n_total, vis_first = n_total, vis = n_total;  // visible keys: of this lane's query, the first one, the last one
   if (p.block_len < p.Lc) {
     auto visible = [&](int i) {
       const long long e = ((long long)(i / p.block_len) + 1) * p.block_len;
       return p.n_kept + (int)(e < p.Lc ? e : p.Lc);
     };
     lim = visible(q_row);
+    vis_first = uniform_i32(visible(q0));
     vis = uniform_i32(visible(q0 + kSmQ - 1 < p.Lq ? q0 + kSmQ - 1 : p.Lq - 1));
   }
   const int tiles = (vis + kAtTileKeys - 1) / kAtTileKeys;
-  lds_byte* const mine = (lds_byte*)lds_raw + wave * (kSmQ * kSmRow<D> * 4);
-  lds_float* const merge_ml = (lds_float*)((lds_byte*)lds_raw + kSmWaves * kSmQ * kSmRow<D> * 4);
+  lds_byte* const tile_lds = lds + wave * Lds::tile;  // (head dim 128: waves past the last slot have no tile)
+  // what a wave has written to the LDS is there, and no access moves over the line; loads from global memory stay in flight
+  auto sync = [] {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  auto in_order = [] { asm volatile("" ::: "memory"); };  // (one wave's LDS operations keep the order they are written in)
 
-  if (wave < tiles) {
-    auto row_at = [&](const void* cache, const void* chunk, int key) {  // (rows past the end are masked: a valid one instead)
-      key = key < n_total ? key : n_total - 1;
-      const bool in_cache = key < p.n_kept;
-      if (GATHER && in_cache) {  // a row through the index list, never outside the cache
-        const int id = p.ids[key];
-        return static_cast<const unsigned short*>(cache) + head_off +
-               (long long)(id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1)) * p.ld_c;
+  // ---- a tile's rows: 16 bytes of row VR j + lane / CH per load
+  u32x4 kv[VL], vv[VL];
+  int ids = 0;  // GATHER: lane l holds the cache row behind row l of the wave's next tile, never outside the cache
+  auto fetch_ids = [&](int t) {
+    if (!GATHER) return;
+    const int at = t * kAtTileKeys + lane;
+    const int id = p.ids[at < p.n_kept ? at : p.n_kept - 1];
+    ids = id < 0 ? 0 : (id < p.n_cache ? id : p.n_cache - 1);
+  };
+  auto fetch = [&](int t) {
+    const int key0 = t * kAtTileKeys;
+    const unsigned ldc_b = (unsigned)(p.ld_c * 2), ldn_b = (unsigned)(p.ld_n * 2);  // (64 rows span less than 4 GiB)
+    const unsigned chunk16 = 16 * (lane % CH);
+    const bool cache = key0 + kAtTileKeys <= p.n_kept;
+    const int from = key0 < p.n_kept ? 0 : key0 - p.n_kept;  // chunk row that the chunk's offsets count from
+    const char* const kc = static_cast<const char*>(L.Kc) + 2 * head_off + (GATHER ? 0 : (long long)key0 * ldc_b);
+    const char* const vc = static_cast<const char*>(L.Vc) + 2 * head_off + (GATHER ? 0 : (long long)key0 * ldc_b);
+    const char* const kn = static_cast<const char*>(L.Kn) + 2 * head_off + (long long)from * ldn_b;
+    const char* const vn = static_cast<const char*>(L.Vn) + 2 * head_off + (long long)from * ldn_b;
+    if (cache || (key0 >= p.n_kept && key0 + kAtTileKeys <= n_total)) {  // one segment: scalar bases
+      const char *const kb = cache ? kc : kn, *const vb = cache ? vc : vn;
+      const unsigned ld_b = cache ? ldc_b : ldn_b;
+      unsigned off[VL];
+#pragma unroll
+      for (int j = 0; j < VL; ++j) {
+        const unsigned row = GATHER && cache ? (unsigned)__shfl(ids, VR * j + lane / CH) : (unsigned)(VR * j + lane / CH);
+        off[j] = row * ld_b + chunk16;  // (a gathered cache is smaller than 4 GiB)
       }
-      return static_cast<const unsigned short*>(in_cache ? cache : chunk) + head_off +
-             (long long)(in_cache ? key : key - p.n_kept) * (in_cache ? p.ld_c : p.ld_n);
-    };
+#pragma unroll
+      for (int j = 0; j < VL; ++j) kv[j] = *reinterpret_cast<const u32x4*>(kb + off[j]);
+#pragma unroll
+      for (int j = 0; j < VL; ++j) vv[j] = *reinterpret_cast<const u32x4*>(vb + off[j]);
+    } else {  // both segments, or the end of the keys (rows past it are masked: a valid one instead)
+      unsigned off[VL];
+      unsigned in_cache = 0;
+#pragma unroll
+      for (int j = 0; j < VL; ++j) {
+        int key = key0 + VR * j + lane / CH;
+        key = key < n_total ? key : n_total - 1;
+        const bool old = key < p.n_kept;
+        const unsigned cache_row = GATHER ? (unsigned)__shfl(ids, VR * j + lane / CH) : (unsigned)(key - key0);
+        off[j] = (old ? cache_row * ldc_b : (unsigned)(key - p.n_kept - from) * ldn_b) + chunk16;
+        in_cache |= old ? 1u << j : 0u;
+      }
+#pragma unroll
+      for (int j = 0; j < VL; ++j) {
+        kv[j] = *reinterpret_cast<const u32x4*>((in_cache >> j & 1 ? kc : kn) + off[j]);
+        in_order();  // (all addresses at once would be more than the registers hold)
+      }
+#pragma unroll
+      for (int j = 0; j < VL; ++j) {
+        vv[j] = *reinterpret_cast<const u32x4*>((in_cache >> j & 1 ? vc : vn) + off[j]);
+        in_order();
+      }
+    }
+    in_order();
+  };
+  auto to_lds = [&](const u32x4(&x)[VL], bool is_v) {  // with the swizzles of the long kernel
+#pragma unroll
+    for (int j = 0; j < VL; ++j) {
+      const int row = VR * j + lane / CH;
+      const int ch = (lane % CH) ^ (is_v ? 4 * ((row / RPB) & (CH / 4 - 1)) : (row / RPB) & (CH - 1));
+      *(lds_u32x4*)(tile_lds + row * ROWB + (ch << 4)) = x[j];
+    }
+    in_order();
+  };
+
+  if (wave < tiles) fetch_ids(wave);
+  bf16x8 qf[KD];
+  {
     const unsigned short* qp = static_cast<const unsigned short*>(L.Q) + (long long)q_row * p.ld_q + head_off + 8 * g;
-    bf16x8 qf[KD];
 #pragma unroll
     for (int kk = 0; kk < KD; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + 16 * kk);
-    f32x16 o[DB];
+  }
+  if (wave < tiles) {
+    fetch(wave);
+    if (Lds::rounds > 1 && wave + kSmWaves < tiles) fetch_ids(wave + kSmWaves);
+  }
+  // K and V^T fragments: as in the long kernel
+  const int kx2 = g ^ ((c / RPB) & (CH - 1));
+  const lds_byte* const k_rd = tile_lds + c * ROWB;
+  const int i16 = lane & 15, rr = 4 * g + (i16 >> 2);
+  const int vx2 = 4 * ((rr / RPB) & (CH / 4 - 1));
+  const int d_block = wave < DB ? wave : 0;  // rows of O^T that this wave adds up
+  const lds_byte* const v_rd = lds + rr * ROWB + ((i16 & 1) << 3) + ((2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1)) << 4) +
+                               (((4 * d_block) ^ vx2) << 4);
+  lds_u32x4* const p_at = (lds_u32x4*)(lds + Lds::weights) + lane;  // + (4 slot + key slice) * 64
+  lds_float* const sum_at = (lds_float*)(lds + Lds::sums) + lane;   // + 64 slot
+  lds_float* const alpha_at = (lds_float*)(lds + Lds::alphas) + c;  // + kSmQ slot
+  const float sc = p.scale_log2;
+  f32x16 o;
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[b][r] = 0.f;
-    float msc = kAtNoMax, l_run = 0.f;
-    const float sc = p.scale_log2;
-    // K and V^T fragments: as in the long kernel
-    const int kx2 = g ^ ((c / RPB) & (CH - 1));
-    const lds_byte* const k_rd = mine + c * ROWB;
-    const int i16 = lane & 15, rr = 4 * g + (i16 >> 2);
-    const int vx2 = 4 * ((rr / RPB) & (CH / 4 - 1));
-    const lds_byte* const v_rd = mine + rr * ROWB + ((i16 & 1) << 3) + ((2 * ((lane >> 4) & 1) + ((i16 & 3) >> 1)) << 4);
+  for (int r = 0; r < 16; ++r) o[r] = 0.f;
+  float l_run = 0.f;
 
 #pragma unroll 1
-    for (int t = wave; t < tiles; t += kSmWaves) {
-      const int key0 = t * kAtTileKeys;
-      u32x4 kv[VL], vv[VL];
+  for (int t0 = 0;; t0 += kSmWaves) {
+    const int t = t0 + wave, n_here = tiles - t0 < kSmWaves ? tiles - t0 : kSmWaves;
+    const bool busy = t < tiles;
+    f32x16 s[2];
+    u32x4 pw[4];
+    float msc = kAtNoMax, psum = 0.f;
+    auto weigh = [&] {  // the tile's weights relative to msc, in the order of the long kernel
+      psum = 0.f;
 #pragma unroll
-      for (int j = 0; j < VL; ++j)
-        kv[j] = *reinterpret_cast<const u32x4*>(row_at(L.Kc, L.Kn, key0 + VR * j + lane / CH) + 8 * (lane % CH));
+      for (int e = 0; e < 32; e += 2) {
+        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][e & 15], sc, -msc));
+        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][(e & 15) + 1], sc, -msc));
+        psum += p0;
+        psum += p1;
+        pw[e >> 3][(e & 7) >> 1] = pack_bf16(p0, p1);
+      }
+    };
+    auto hand_over = [&] {
 #pragma unroll
-      for (int j = 0; j < VL; ++j)
-        vv[j] = *reinterpret_cast<const u32x4*>(row_at(L.Vc, L.Vn, key0 + VR * j + lane / CH) + 8 * (lane % CH));
-      auto to_lds = [&](const u32x4(&x)[VL], bool is_v) {  // with the swizzles of the long kernel
-#pragma unroll
-        for (int j = 0; j < VL; ++j) {
-          const int row = VR * j + lane / CH;
-          const int ch = (lane % CH) ^ (is_v ? 4 * ((row / RPB) & (CH / 4 - 1)) : (row / RPB) & (CH - 1));
-          *(lds_u32x4*)(mine + row * ROWB + (ch << 4)) = x[j];
-        }
-        __builtin_amdgcn_wave_barrier();  // (one wave's LDS operations keep their order)
-      };
+      for (int ks = 0; ks < 4; ++ks) p_at[(4 * wave + ks) * 64] = pw[ks];
+      sum_at[64 * wave] = psum;
+    };
+    if (busy) {
       to_lds(kv, false);
-      f32x16 s[2];
 #pragma unroll
       for (int kb = 0; kb < 2; ++kb) {
 #pragma unroll
@@ -1149,86 +1261,98 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void attn_small_kernel(AttnArgs a
           s[kb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read_k(k_rd + kb * 32 * ROWB + (((2 * kk) ^ kx2) << 4)), qf[kk],
                                                           s[kb], 0, 0, 0);
       }
-      __builtin_amdgcn_wave_barrier();
+      in_order();
       to_lds(vv, true);
-      attn_mask(s, key0, lim, g);
-      float mx = s[0][0];
-#pragma unroll
-      for (int kb = 0; kb < 2; ++kb)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
-      const float msc_new = fmaxf(msc, half_swap_max(mx) * sc);
-      const float down = __builtin_amdgcn_exp2f(msc - msc_new);
-      msc = msc_new;
-      float psum = 0.f;
-      u32x4 pw[4];
-#pragma unroll
-      for (int e = 0; e < 32; e += 2) {
-        const float p0 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][e & 15], sc, -msc));
-        const float p1 = __builtin_amdgcn_exp2f(fmaf(s[e >> 4][(e & 15) + 1], sc, -msc));
-        psum += p0;
-        psum += p1;
-        pw[e >> 3][(e & 7) >> 1] = pack_bf16(p0, p1);
+      if ((t + 1) * kAtTileKeys > vis_first) attn_mask(s, t * kAtTileKeys, lim, g);
+      if (Lds::rounds > 1 && t + kSmWaves < tiles) {
+        fetch(t + kSmWaves);
+        if (t + 2 * kSmWaves < tiles) fetch_ids(t + 2 * kSmWaves);
       }
-      l_run = fmaf(l_run, down, psum);
-#pragma unroll
-      for (int b = 0; b < DB; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[b][r] *= down;
-#pragma unroll
-      for (int m = 0; m < 4 * DB; ++m) {
-        const bf16x8 a = lds_read_vt(v_rd + (16 * (m / DB)) * ROWB + (((4 * (m % DB)) ^ vx2) << 4), 8 * ROWB);
-        o[m % DB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, as_bf16x8(pw[m / DB]), o[m % DB], 0, 0, 0);
-      }
-      __builtin_amdgcn_wave_barrier();
     }
-    // this wave's result: lane holds query c, d = 32 b + 8 (r/4) + 4 g + (r%4)
-    const float l_tot = half_swap_sum(l_run);
-    if (g == 0) {
-      merge_ml[wave * kSmQ + c] = msc;
-      merge_ml[(kSmWaves + wave) * kSmQ + c] = l_tot;
-    }
+    if (t0 == 0) {  // the reference starts with the maximum of the first tile
+      if (wave == 0) {
+        float mx = s[0][0];
 #pragma unroll
-    for (int b = 0; b < DB; ++b)
+        for (int kb = 0; kb < 2; ++kb)
 #pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const u32x4 v = {__float_as_uint(o[b][4 * q4]), __float_as_uint(o[b][4 * q4 + 1]), __float_as_uint(o[b][4 * q4 + 2]),
-                         __float_as_uint(o[b][4 * q4 + 3])};
-        *(lds_u32x4*)(mine + (c * kSmRow<D> + 32 * b + 8 * q4 + 4 * g) * 4) = v;
+          for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kb][r]);
+        msc = fmaxf(kAtNoMax, half_swap_max(mx) * sc);
+        if (g == 0) msc_of[c] = msc;
       }
+      sync();
+    }
+    msc = msc_of[c];
+    bool over = false;
+    if (busy) {
+      weigh();
+      hand_over();
+      over = __builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0;
+    }
+    if (lane == 0) outgrown[wave] = over;
+    sync();
+    int any = 0;
+#pragma unroll
+    for (int w = 0; w < kSmWaves; ++w) any |= outgrown[w];
+    const bool raised = uniform_i32(any) != 0;
+    if (raised) {
+#pragma unroll 1
+      for (int w = 0; w < n_here; ++w) {
+        if (w == wave) {
+          msc = msc_of[c];
+          weigh();
+          float alpha = 1.f, unused = 0.f;
+          if (__builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0) alpha = attn_raise(s, pw, sc, msc, unused, psum);
+          hand_over();
+          if (g == 0) {
+            alpha_at[kSmQ * w] = alpha;
+            msc_of[c] = msc;
+          }
+        }
+        sync();
+      }
+    }
+    if (wave < DB) {
+      u32x4 pf[4];
+      bf16x8 vf[4];
+      auto read = [&](int w, int ks) {
+        pf[ks] = p_at[(4 * w + ks) * 64];
+        vf[ks] = lds_read_vt(v_rd + w * Lds::tile + 16 * ks * ROWB, 8 * ROWB);
+      };
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) read(0, ks);
+#pragma unroll 1
+      for (int w = 0; w < n_here; ++w) {
+        const int w_next = w + 1 < n_here ? w + 1 : w;
+        if (raised) {
+          const float alpha = alpha_at[kSmQ * w];
+          l_run *= alpha;
+#pragma unroll
+          for (int r = 0; r < 16; ++r) o[r] *= alpha;
+        }
+#pragma unroll
+        for (int ks = 0; ks < 4; ++ks) {
+          o = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[ks], as_bf16x8(pf[ks]), o, 0, 0, 0);
+          read(w_next, ks);
+        }
+        l_run += sum_at[64 * w];
+      }
+    }
+    if (Lds::rounds == 1 || t0 + kSmWaves >= tiles) break;
+    sync();  // the tiles and their weights have been used
   }
-  __syncthreads();
-  // merge, in the order of the waves: 16 threads per query, D / 16 outputs each
-  const int row = tid / 16, n_w = tiles < kSmWaves ? tiles : kSmWaves;
-  float m = kAtNoMax;
-  for (int w = 0; w < n_w; ++w) m = fmaxf(m, merge_ml[w * kSmQ + row]);
-  float l = 0.f;
-  float acc[D / 16];
+  if (wave >= DB || q0 + c >= p.Lq) return;
+  // lane holds query c, d = 32 wave + 8 (r/4) + 4 g + (r%4)
+  const float inv = 1.0f / half_swap_sum(l_run);
 #pragma unroll
-  for (int i = 0; i < D / 16; ++i) acc[i] = 0.f;
-  for (int w = 0; w < n_w; ++w) {
-    const float wgt = __builtin_amdgcn_exp2f(merge_ml[w * kSmQ + row] - m);
-    l = fmaf(merge_ml[(kSmWaves + w) * kSmQ + row], wgt, l);
-#pragma unroll
-    for (int q4 = 0; q4 < D / 64; ++q4) {
-      const lds_byte* at = (const lds_byte*)lds_raw + ((w * kSmQ + row) * kSmRow<D> + 64 * q4 + 4 * (tid % 16)) * 4;
-      const u32x4 v = *(const lds_u32x4*)at;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) acc[4 * q4 + i] = fmaf(__uint_as_float(v[i]), wgt, acc[4 * q4 + i]);
-    }
-  }
-  if (q0 + row >= p.Lq) return;
-  const float inv = 1.0f / l;
-#pragma unroll
-  for (int q4 = 0; q4 < D / 64; ++q4) {
-    const long long off = (long long)(q0 + row) * p.ld_o + head_off + 64 * q4 + 4 * (tid % 16);
+  for (int q4 = 0; q4 < 4; ++q4) {
+    const long long off = (long long)q_row * p.ld_o + head_off + 32 * wave + 8 * q4 + 4 * g;
     if (OUT_F32) {
       *reinterpret_cast<float4*>(static_cast<float*>(L.O) + off) =
-          make_float4(acc[4 * q4] * inv, acc[4 * q4 + 1] * inv, acc[4 * q4 + 2] * inv, acc[4 * q4 + 3] * inv);
+          make_float4(o[4 * q4] * inv, o[4 * q4 + 1] * inv, o[4 * q4 + 2] * inv, o[4 * q4 + 3] * inv);
     } else {
       bf16x4 ob;
 #pragma unroll
-      for (int i = 0; i < 4; ++i) ob[i] = (__bf16)(acc[4 * q4 + i] * inv);
+      for (int i = 0; i < 4; ++i) ob[i] = (__bf16)(o[4 * q4 + i] * inv);
       *reinterpret_cast<bf16x4*>(static_cast<unsigned short*>(L.O) + off) = ob;
     }
   }
@@ -1237,10 +1361,10 @@ __global__ __launch_bounds__(kSmWaves * 64, 1) void attn_small_kernel(AttnArgs a
 template <int D, bool OUT_F32, bool GATHER>
 int launch_small(hipStream_t st, const AttnArgs& a, int heads) {
   static LdsLimit lds_limit;
-  const int rc = set_lds_limit(lds_limit, attn_small_kernel<D, OUT_F32, GATHER>, small_lds_bytes<D>());
+  const int rc = set_lds_limit(lds_limit, attn_small_kernel<D, OUT_F32, GATHER>, SmallLds<D>::bytes);
   if (rc != PAFU_OK) return rc;
   hipLaunchKernelGGL((attn_small_kernel<D, OUT_F32, GATHER>), dim3(heads * ((a.p.Lq + kSmQ - 1) / kSmQ)),
-                     dim3(kSmWaves * 64), small_lds_bytes<D>(), st, a);
+                     dim3(kSmWaves * 64), SmallLds<D>::bytes, st, a);
   return check_launch();
 }
 template <bool GATHER>

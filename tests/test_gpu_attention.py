@@ -110,6 +110,46 @@ def test_attention_few_queries_over_few_keys(n, Lc, N, D, L_B, odt):
             assert np.array_equal(host(O), got), gain
 
 
+# A query's result has the same bits whichever kernel takes it.  The heads of the whole call pass the line of the kernel for few
+# queries over few keys (256 groups of 32 queries); two of them alone do not.  Scores that grow from tile to tile or jump by
+# hundreds of powers of two raise the softmax reference in both.
+@pytest.mark.parametrize("n,Lc,N,D,L_B", [
+    (128, 64, 130, 64, 64), (0, 130, 52, 64, 33), (700, 300, 26, 64, 77), (1403, 130, 52, 64, 130),
+    (128, 64, 130, 128, 64), (0, 384, 22, 128, 100), (65, 130, 52, 128, 130), (251, 130, 52, 128, 64),
+])
+@pytest.mark.parametrize("kind", ["plain", "growing", "jump", "nan query"])
+def test_attention_bits_do_not_depend_on_what_shares_the_launch(n, Lc, N, D, L_B, kind):
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n + Lc + D)
+    draw = lambda rows: torch.randn(rows, N, D, device=DEV, generator=g)
+    Q, Kc, Vc, Kn, Vn = draw(Lc), draw(n), draw(n), draw(Lc), draw(Lc)
+    tile = (torch.arange(n + Lc, device=DEV) // 64)[:, None, None].float()
+    if kind == "growing":
+        Kc, Kn = Kc * (0.1 * 2.0 ** tile[:n]), Kn * (0.1 * 2.0 ** tile[n:])
+    elif kind == "jump":  # the queries' common direction meets keys that go up by 300 powers of two in the second tile
+        Q = 0.3 * Q + 1.0
+        step = 300 / (np.log2(np.e) * np.sqrt(D))
+        Kc, Kn = 0.3 * Kc + step * tile[:n].clamp(max=1), 0.3 * Kn + step * tile[n:].clamp(max=1)
+    elif kind == "nan query":
+        Q[::29] = float("nan")
+    Q, Kc, Vc, Kn, Vn = (x.to(torch.bfloat16) for x in (Q, Kc, Vc, Kn, Vn))
+    O = torch.empty(Lc, N, D, device=DEV, dtype=torch.float32)
+    B.pafu_chunk_attention(Q, Kc if n else None, Vc if n else None, n, Kn, Vn, L_B, O)
+    torch.cuda.synchronize()
+    for heads in (slice(0, 2), slice(N - 2, N)):
+        few = torch.empty(Lc, 2, D, device=DEV, dtype=torch.float32)
+        q, kc, vc, kn, vn = (x[:, heads] if heads.start == 0 else x[:, heads].contiguous() for x in (Q, Kc, Vc, Kn, Vn))
+        B.pafu_chunk_attention(q, kc if n else None, vc if n else None, n, kn, vn, L_B, few)
+        torch.cuda.synchronize()
+        assert np.array_equal(host(few), host(O[:, heads]), equal_nan=True)
+        if n:
+            ids = torch.arange(n, dtype=torch.int32, device=DEV)
+            again = torch.empty_like(few)
+            B.pafu_chunk_attention_gather(q, kc, vc, ids, n, kn, vn, L_B, again)
+            torch.cuda.synchronize()
+            assert np.array_equal(host(again), host(few), equal_nan=True)
+
+
 def test_attention_peaked_softmax_and_fp32_output():
     # queries scaled x8: the softmax is peaked, |O| ~ 1, so the max-abs bound bites
     n, Lc, N, D = 500, 192, 2, 128

@@ -68,3 +68,33 @@ def test_layers_that_share_launches_match_the_oracle(layers, n, Lc, L_B, N, D, k
         O_want = orc.chunk_attention(Q, rows[0][:k], rows[1][:k], rows[0][k:], rows[1][k:], block_len=L_B)
         max_abs, rel = attn_errors(host(O), O_want)
         assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (l, max_abs, rel)
+
+
+# A layer alone takes the attention kernel for few queries over few keys, the layers together pass its line: the same bits
+@pytest.mark.parametrize("layers,N,D", [(6, 12, 128), (10, 7, 64)])
+def test_short_layers_have_the_bits_of_single_steps(layers, N, D):
+    n, Lc, k, M = 400, 128, 200, 64
+    g = torch.Generator(device=DEV)
+    g.manual_seed(layers)
+    draw = lambda *s: torch.randn(*s, device=DEV, generator=g)
+    bf = lambda *s: draw(*s).to(torch.bfloat16)
+
+    def args(t):
+        out = dict(scores=torch.zeros(n + Lc, device=DEV), ids=torch.zeros(k, dtype=torch.int32, device=DEV),
+                   K_out=torch.zeros(k, N, D, device=DEV, dtype=torch.bfloat16),
+                   V_out=torch.zeros(k, N, D, device=DEV, dtype=torch.bfloat16), SL_out=torch.zeros(k, device=DEV),
+                   O=torch.zeros(Lc, N, D, device=DEV))
+        return out, B.make_step_args(B.PAFU_MODE_SINGLE, N, D, n, Lc, k, 50, t["xc"], t["x"], t["W1"], None, t["W2"], None,
+                                     t["K"], t["V"], None, t["Q"], t["Kn"], t["Vn"], out["scores"], out["ids"],
+                                     out["K_out"], out["V_out"], out["SL_out"], out["O"])
+
+    given = [dict(xc=bf(n, 64), x=bf(Lc, 64), W1=bf(M, 64), W2=draw(1, M), K=bf(n, N, D), V=bf(n, N, D), Q=bf(Lc, N, D),
+                  Kn=bf(Lc, N, D), Vn=bf(Lc, N, D)) for _ in range(layers)]
+    together = [args(t) for t in given]
+    B.pafu_step_layers([a for _, a in together])
+    for t, (out, _) in zip(given, together):
+        alone, a = args(t)
+        B.pafu_step(a)
+        torch.cuda.synchronize()
+        for key in alone:
+            assert torch.equal(alone[key], out[key]), key
