@@ -1063,13 +1063,15 @@ __global__ __launch_bounds__(256) void attn_combine_kernel(AttnArgs args) {
 // keys 11.1 / 7.9 (15.7 / 8.3).
 constexpr int kSmWaves = 8;
 constexpr int kSmQ = 32;                       // queries per workgroup
-// Where it is used: up to kSmTiles key tiles and kSmGroups workgroups (gathered or not, with a workspace or without).  Calls back
-// to back, this / the long kernel whole / cut with a workspace: head dim 64, 24 tiles, 4 workgroups 11.7 / 17.0 / 10.9 us, 256
-// (one per CU) 12.5 / 25.7 / 21.3, gathered 14.2 / 29.7 / 22.7, and 320 (two on some CUs) 23.5 / 26.0 / 22.4; 32 tiles, 4
-// workgroups 14.6 / 21.0 / 10.6: a workgroup takes in all keys of its head, the cut shares them among CUs.  Head dim 128 (its
-// calls are too short to be cut), 64 workgroups: 3 tiles 6.7 / 14.2, 6 tiles 7.6 / 13.7, gathered 8.0 / 16.1.
-constexpr int kSmTiles64 = 24, kSmGroups64 = 256;
-constexpr int kSmTiles128 = 6, kSmGroups128 = 64;
+// Where it is used: up to kSmGroups workgroups (one per CU: two of them on some CUs take twice as long) and kSmTiles key tiles (a
+// workgroup takes in all keys of its head, where the long kernel, with a workspace, shares them among CUs; at head dim 128 no
+// more fit the LDS side by side), gathered or not, with a workspace or without.  Calls back to back, this / the long kernel
+// whole / cut with a workspace.  Head dim 64, 24 tiles: 4 workgroups 11.7 / 17.0 / 10.9 us, 256 12.5 / 25.7 / 21.3 (gathered
+// 14.2 / 29.7 / 22.7), 320 23.5 / 26.0 / 22.4; 32 tiles: 4 workgroups 14.6 / 21.0 / 10.6, 40 15.0 / 29.4 / 14.0.  Head dim
+// 128 (too short to be cut): 3 tiles, 64 workgroups 6.7 / 14.2; 7 tiles, 64 8.2 / 16.2, 256 8.7 / 16.2 (gathered 9.3 / 18.8);
+// 6 tiles, 256 8.0 / 13.7, 320 14.8 / 14.5.
+constexpr int kSmGroups = 256;
+constexpr int kSmTiles64 = 24, kSmTiles128 = 7;
 template <int D>
 struct SmallLds {  // bytes from the start of the LDS
   static constexpr int slots = D == 64 ? kSmWaves : kSmTiles128;        // tiles side by side
@@ -1421,8 +1423,7 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
   const bool f32 = out_dtype == PAFU_F32, gather = ids != nullptr && n_kept > 0;
   const long long tiles = ((long long)n_kept + Lc + kAtTileKeys - 1) / kAtTileKeys;
   const long long groups = (long long)N * n_layers * ((Lq + kSmQ - 1) / kSmQ);
-  if (kv_dtype == PAFU_BF16 && tiles <= (D == 64 ? kSmTiles64 : kSmTiles128) &&
-      groups <= (D == 64 ? kSmGroups64 : kSmGroups128))
+  if (kv_dtype == PAFU_BF16 && tiles <= (D == 64 ? kSmTiles64 : kSmTiles128) && groups <= kSmGroups)
     return gather ? launch_small_dims<true>(st, a, N * n_layers, D, f32) : launch_small_dims<false>(st, a, N * n_layers, D, f32);
 
   AttnWork& w = a.w;

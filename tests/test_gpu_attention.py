@@ -83,15 +83,17 @@ def test_attention_tile_counts_and_boundaries(n, D):
             assert np.array_equal(host(O), plain), (Lc, L_B)
 
 
-# Both sides of the line between the kernel for few queries over few keys and the long one (24 tiles and 256 groups of 32
-# queries at head dim 64, 6 and 64 at 128), with all forms of output, block masks, and the gathered form's bits.
+# Both sides of the line between the kernel for few queries over few keys and the long one (256 groups of 32 queries; 24 tiles
+# at head dim 64, 7 at 128), with all forms of output, block masks, and the gathered form's bits.
 @pytest.mark.parametrize("n,Lc,N,D,L_B,odt", [
     (1472, 64, 2, 64, 64, torch.float32), (1473, 64, 2, 64, 64, torch.float32),     # 24 and 25 tiles
     (1400, 100, 4, 64, 33, torch.bfloat16), (40, 33, 128, 64, 5, torch.bfloat16),   # three tiles per wave; 256 groups
     (40, 33, 130, 64, 5, torch.bfloat16), (0, 130, 64, 64, 130, torch.bfloat16),    # 260 and 320
     (65, 130, 64, 64, 64, torch.bfloat16), (191, 130, 64, 64, 7, torch.float32), (512, 130, 64, 64, 130, torch.bfloat16),
     (254, 130, 2, 128, 40, torch.float32), (255, 130, 2, 128, 40, torch.float32),   # 6 and 7 tiles
+    (318, 130, 2, 128, 40, torch.bfloat16), (319, 130, 2, 128, 40, torch.float32),  # 7 and 8
     (65, 130, 12, 128, 130, torch.bfloat16), (65, 130, 13, 128, 130, torch.bfloat16),  # 60 and 65 groups
+    (40, 33, 128, 128, 5, torch.bfloat16), (40, 33, 130, 128, 5, torch.bfloat16),   # 256 and 260
 ])
 def test_attention_few_queries_over_few_keys(n, Lc, N, D, L_B, odt):
     # a peaked softmax in fp32 only: |O| passes 4 there, where half a unit of a bf16 result (2^-6) and the rounding of the
@@ -115,7 +117,7 @@ def test_attention_few_queries_over_few_keys(n, Lc, N, D, L_B, odt):
 # hundreds of powers of two raise the softmax reference in both.
 @pytest.mark.parametrize("n,Lc,N,D,L_B", [
     (128, 64, 130, 64, 64), (0, 130, 52, 64, 33), (700, 300, 26, 64, 77), (1403, 130, 52, 64, 130),
-    (128, 64, 130, 128, 64), (0, 384, 22, 128, 100), (65, 130, 52, 128, 130), (251, 130, 52, 128, 64),
+    (128, 64, 130, 128, 64), (0, 384, 22, 128, 100), (65, 130, 52, 128, 130), (251, 130, 52, 128, 64), (316, 130, 52, 128, 130),
 ])
 @pytest.mark.parametrize("kind", ["plain", "growing", "jump", "nan query"])
 def test_attention_bits_do_not_depend_on_what_shares_the_launch(n, Lc, N, D, L_B, kind):
