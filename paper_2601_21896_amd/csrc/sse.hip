@@ -100,8 +100,11 @@ __device__ __forceinline__ void wait_vmcnt() {
 // the same passes one after the other (product, then reduction) 5990 us, pipelined 5242 (1100 -> 1260 TFLOP/s).
 // Raised references cost little: 12000 tokens, 8 heads of 64, 380 us; keys growing sixteenfold 394, NaN rows 388 (494 and 572
 // when a raise computed the weights once more).
+// rowstat with one group keeps to 128 registers, so that two workgroups share a CU: 11000 tokens, 12 heads of 128 896 us, with
+// 134 registers 932 (7000 tokens, 40 heads 1032 and 1066; where every workgroup has a CU of its own, 3000 tokens, 12 heads,
+// its 5 spilled registers cost 1 %: 98.8 and 97.9).
 template <int D, bool COLMAX, int HT>
-__global__ __launch_bounds__(kSseThreads, 2) void sse_pass_kernel(SseParams p) {
+__global__ __launch_bounds__(kSseThreads, HT == 1 && !COLMAX ? 4 : 2) void sse_pass_kernel(SseParams p) {
   constexpr int ROWB = 2 * D;               // bytes per row of one head
   constexpr int TILEB = kSseTile * ROWB;    // bytes per streamed tile
   constexpr int CH = D / 8;                 // 16-byte chunks per row
