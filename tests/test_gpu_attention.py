@@ -22,18 +22,30 @@ def _inputs(n, Lc, N, D, seed, q_gain=1.0):
     return Q, Kc, Vc, Kn, Vn
 
 
-def _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.bfloat16, Lq=None, ws=None):
+# Calls of up to 256 groups of 32 queries (heads times query groups) over up to 24 tiles of 64 keys (7 at head dim 128) take a
+# kernel of their own.  `copies` repeats the heads, so that a short call passes that line and takes the long kernel; the
+# copies must have the same bits (with a workspace some of them may be cut: then the last ones are returned).
+def _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.bfloat16, Lq=None, ws=None, copies=1):
     Lq = Q.shape[0] if Lq is None else Lq
     N, D = Q.shape[1], Q.shape[2]
     n = Kc.shape[0]
-    O = torch.full((Lq + 2, N, D), 55.0, device=DEV, dtype=out_dtype)
-    dQ = dev(Q[:Lq], "bf16")
-    dKc = dev(Kc, "bf16") if n else None
-    dVc = dev(Vc, "bf16") if n else None
-    B.pafu_chunk_attention(dQ, dKc, dVc, n, dev(Kn, "bf16"), dev(Vn, "bf16"), L_B, O[:Lq], workspace=ws)
+    O = torch.full((Lq + 2, N * copies, D), 55.0, device=DEV, dtype=out_dtype)
+    up = lambda x: dev(x, "bf16").repeat(1, copies, 1)
+    B.pafu_chunk_attention(up(Q[:Lq]), up(Kc) if n else None, up(Vc) if n else None, n, up(Kn), up(Vn), L_B, O[:Lq],
+                           workspace=ws)
     torch.cuda.synchronize()
     assert torch.all(O[Lq:] == 55.0)
-    return host(O[:Lq])
+    if ws is not None:
+        assert (O[:Lq].view(Lq, copies, -1) - O[:Lq, :N].reshape(Lq, 1, -1)).nan_to_num().abs().max() < 2 * ATTN_MAX_ABS
+        return host(O[:Lq, -N:])
+    return _first_copy(O[:Lq], N)
+
+
+def _first_copy(O, N):
+    same = O.view(O.shape[0], -1, N * O.shape[2])
+    bits = same.view(torch.int16 if O.dtype == torch.bfloat16 else torch.int32)
+    assert torch.equal(bits, bits[:, :1].expand_as(bits))
+    return host(O[:, :N])
 
 
 @pytest.mark.parametrize("n,Lc,N,D,L_B", [
@@ -48,6 +60,9 @@ def _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.bfloat16, Lq=None, ws=None):
     (1, 1, 1, 128, 1),
     (63, 129, 2, 64, 129),
     (1000, 520, 2, 128, 130),
+    # short calls of many heads: the long kernel
+    (128, 64, 130, 64, 16), (0, 64, 130, 64, 1), (63, 129, 52, 64, 129),
+    (0, 40, 130, 128, 7), (1, 1, 257, 128, 1), (300, 130, 52, 128, 130), (317, 130, 52, 128, 13),
 ])
 def test_attention_matches_oracle(n, Lc, N, D, L_B):
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n * 7 + Lc)
@@ -57,30 +72,33 @@ def test_attention_matches_oracle(n, Lc, N, D, L_B):
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
 
 
-# One item's tiles around the turns of the four-slot ring: segments of 1 to 11 tiles that end in each slot, with and
-# without a tile that straddles the two key segments, chunks shorter than a tile, behind one another in one workgroup's
-# run (with a workspace).  The gathered form reads the same rows through an index list: the same bits without a cut.
+# Segments of 1 to 11 tiles, with and without a tile that straddles the two key segments, chunks shorter than a tile: in the
+# long kernel (many copies of the heads: one item's tiles around the turns of the four-slot ring, ending in each slot) and in
+# the one for few queries.  The gathered form reads the same rows through an index list: the same bits.  (Items that follow one
+# another in one workgroup's run: test_attention_equal_runs_match_oracle.)
+@pytest.mark.parametrize("copies", [1, 129])
 @pytest.mark.parametrize("D", [64, 128])
 @pytest.mark.parametrize("n", [0, 1, 63, 64, 65, 128, 191, 256, 320, 449, 512])
-def test_attention_tile_counts_and_boundaries(n, D):
+def test_attention_tile_counts_and_boundaries(n, D, copies):
     N = 2
     for Lc, L_B in [(1, 1), (63, 63), (64, 20), (65, 65), (130, 64)]:
         Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n * 131 + Lc)
         want = orc.chunk_attention(Q, Kc, Vc, Kn, Vn, block_len=L_B)
-        plain = _run(Q, Kc, Vc, Kn, Vn, L_B)
-        for got in (plain, _run(Q, Kc, Vc, Kn, Vn, L_B, ws=attention_workspace(D))):
+        plain = _run(Q, Kc, Vc, Kn, Vn, L_B, copies=copies)
+        for got in (plain, _run(Q, Kc, Vc, Kn, Vn, L_B, ws=attention_workspace(D), copies=copies)):
             max_abs, rel = attn_errors(got, want)
             assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (Lc, L_B, max_abs, rel)
         if n > 0:
             rows = 2 * n + 1
             at = np.sort(np.random.Generator(np.random.PCG64(n)).permutation(rows)[:n]).astype(np.int32)
-            K, V = (torch.full((rows, N, D), 7.0, device=DEV, dtype=torch.bfloat16) for _ in range(2))
+            K, V = (torch.full((rows, N * copies, D), 7.0, device=DEV, dtype=torch.bfloat16) for _ in range(2))
             d_at = torch.from_numpy(at).to(DEV)
-            K[d_at.long()], V[d_at.long()] = dev(Kc, "bf16"), dev(Vc, "bf16")
-            O = torch.empty(Lc, N, D, device=DEV, dtype=torch.bfloat16)
-            B.pafu_chunk_attention_gather(dev(Q, "bf16"), K, V, d_at, n, dev(Kn, "bf16"), dev(Vn, "bf16"), L_B, O)
+            up = lambda x: dev(x, "bf16").repeat(1, copies, 1)
+            K[d_at.long()], V[d_at.long()] = up(Kc), up(Vc)
+            O = torch.empty(Lc, N * copies, D, device=DEV, dtype=torch.bfloat16)
+            B.pafu_chunk_attention_gather(up(Q), K, V, d_at, n, up(Kn), up(Vn), L_B, O)
             torch.cuda.synchronize()
-            assert np.array_equal(host(O), plain), (Lc, L_B)
+            assert np.array_equal(_first_copy(O, N), plain), (Lc, L_B)
 
 
 # Both sides of the line between the kernel for few queries over few keys and the long one (256 groups of 32 queries; 24 tiles
@@ -177,6 +195,8 @@ def test_attention_peaked_softmax_and_fp32_output():
     (900, 40, 1, 128, 40, torch.float32, 1.0),        # one item of 8 units in 4 runs
     (300, 1700, 40, 64, 1700, torch.bfloat16, 1.0),   # 280 items on 256 CUs: a round of whole items, 24 items cut
     (100, 1700, 38, 128, 450, torch.float32, 1.0),    # 266 items of different lengths, 10 of them cut
+    (600, 500, 150, 64, 256, torch.bfloat16, 1.0),    # 300 items of 7 and 9 units, 44 cut in runs of two that cross items
+    (600, 500, 150, 128, 256, torch.bfloat16, 1.0),
 ])
 def test_attention_equal_runs_match_oracle(n, Lc, N, D, L_B, odt, q_gain):
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=n + Lc + N, q_gain=q_gain)
@@ -203,21 +223,22 @@ def test_attention_workspace_too_small_falls_back_to_whole_query_tiles():
     assert np.array_equal(got, plain)
 
 
-def test_attention_large_key_offset_and_fewer_queries():
+@pytest.mark.parametrize("copies", [1, 65])
+def test_attention_large_key_offset_and_fewer_queries(copies):
     # a large common vector on every key shifts logits by a per-row constant: exercises the running max
     n, Lc, N, D = 200, 100, 2, 128
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=5)
     shift = wl.round_to_bf16(np.full((1, N, D), 3.0, np.float32))
     Kc2, Kn2 = wl.round_to_bf16(Kc + shift), wl.round_to_bf16(Kn + shift)
-    got = _run(Q, Kc2, Vc, Kn2, Vn, 25, Lq=70)
+    got = _run(Q, Kc2, Vc, Kn2, Vn, 25, Lq=70, copies=copies)
     want = orc.chunk_attention(Q[:70], Kc2, Vc, Kn2, Vn, block_len=25)
     max_abs, rel = attn_errors(got, want)
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
 
 
-@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("D,copies", [(64, 1), (64, 65), (128, 1)])  # (64, 1): the kernel for few queries
 @pytest.mark.parametrize("case", ["every tile", "one query", "masked start", "nan query"])
-def test_attention_running_maximum_outgrown(D, case):
+def test_attention_running_maximum_outgrown(D, copies, case):
     # the running maximum is the first tile's until a later tile outgrows it: for all queries of every tile, for single
     # queries of one tile, from a first tile in which a query sees nothing; and a NaN in one query stays in that query
     # (masked start: 12 items per head of 2 to 24 units, the last one of 23: cut in runs of two, those of the second head
@@ -237,18 +258,18 @@ def test_attention_running_maximum_outgrown(D, case):
     ok = np.setdiff1d(np.arange(Lc), bad)
     want = orc.chunk_attention(np.nan_to_num(Q), Kc, Vc, Kn, Vn, block_len=L_B)
     for ws in (None, attention_workspace(D)):
-        got = _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.float32, ws=ws)
+        got = _run(Q, Kc, Vc, Kn, Vn, L_B, out_dtype=torch.float32, ws=ws, copies=1 if case == "masked start" else copies)
         max_abs, rel = attn_errors(got[ok], want[ok])
         assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
         assert np.isnan(got[bad]).all()
 
 
-@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("D,n,copies", [(64, 384, 1), (64, 384, 65), (128, 384, 1), (128, 330, 1)])  # few, long, long, few
 @pytest.mark.parametrize("bits,stairs", [(20, 1), (26, 1), (95, 1), (104, 1), (300, 1), (30, 5), (110, 5)])
-def test_attention_reference_raised_by(D, bits, stairs):
+def test_attention_reference_raised_by(D, n, copies, bits, stairs):
     # scores that jump by up to `bits` powers of two (less for the first queries) once or in every further tile: below the
     # limit of 2^24, scaled by a power of two (up to 2^100), or computed once more
-    n, Lc, N = 384, 96, 2
+    Lc, N = 96, 2
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=D + bits + stairs)
     gain = np.linspace(0.1, 1.0, Lc, dtype=np.float32)[:, None, None]
     step = np.float32(bits / (np.log2(np.e) * np.sqrt(D)))
@@ -257,14 +278,16 @@ def test_attention_reference_raised_by(D, bits, stairs):
     Kc = wl.round_to_bf16(Kc * np.float32(0.3) + (step * level)[:, None, None].astype(np.float32))
     Kn = wl.round_to_bf16(Kn * np.float32(0.3) + step * np.float32(stairs))
     want = orc.chunk_attention(Q, Kc, Vc, Kn, Vn, block_len=Lc)
-    got = _run(Q, Kc, Vc, Kn, Vn, Lc, out_dtype=torch.float32)
+    got = _run(Q, Kc, Vc, Kn, Vn, Lc, out_dtype=torch.float32, copies=copies)
     max_abs, rel = attn_errors(got, want)
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
 
 
-def test_attention_strided_slabs():
+@pytest.mark.parametrize("N", [2, 130])  # the kernel for few queries, the long one
+@pytest.mark.parametrize("D", [64, 128])
+def test_attention_strided_slabs(N, D):
     # cache rows live in a slab with spare capacity and a wider token stride
-    n, Lc, N, D = 150, 70, 2, 64
+    n, Lc = 150, 70
     Q, Kc, Vc, Kn, Vn = _inputs(n, Lc, N, D, seed=17)
     ld = N * D + 64
     slabK = torch.zeros(n + 10, ld, device=DEV, dtype=torch.bfloat16)
@@ -291,6 +314,9 @@ def test_attention_strided_slabs():
     (400, 0, 40, 1, 128, 7, "sorted"),         # nothing kept
     (70, 1, 1, 1, 128, 1, "sorted"),
     (5000, 2560, 300, 2, 128, 300, "sorted"),  # many full tiles through the prefetched-id path
+    # short calls of many heads: the long kernel
+    (300, 128, 64, 130, 64, 64, "sorted"), (300, 100, 64, 130, 64, 16, "shuffled"), (400, 0, 40, 130, 128, 7, "sorted"),
+    (300, 100, 64, 130, 128, 16, "shuffled"), (70, 1, 1, 260, 128, 1, "sorted"), (70, 1, 1, 260, 64, 1, "sorted"),
 ])
 def test_gather_attention_matches_oracle_and_the_compacted_path(n_cache, n_kept, Lc, N, D, L_B, order):
     Q, Kc, Vc, Kn, Vn = _inputs(n_cache, Lc, N, D, seed=n_cache + n_kept)
@@ -331,17 +357,24 @@ def test_gather_attention_with_equal_runs():
     assert np.array_equal(host(O[:Lc]), plain)
 
 
-def test_gather_attention_clamps_out_of_range_ids():
+# few, long, long, few; the ids ring of the long kernel has eight tiles, the last cache tile is mixed with chunk rows
+@pytest.mark.parametrize("D,n_kept,copies", [(64, 532, 1), (64, 532, 65), (128, 532, 1), (128, 148, 1)])
+def test_gather_attention_clamps_out_of_range_ids(D, n_kept, copies):
     # ids outside the cache must not fault; rows are clamped into range (the result equals attention over those rows)
-    n_cache, Lc, N, D = 200, 64, 2, 128
+    n_cache, Lc, N = 700, 64, 2
     Q, Kc, Vc, Kn, Vn = _inputs(n_cache, Lc, N, D, seed=5)
-    ids = np.arange(128, dtype=np.int32)
-    ids[3], ids[70] = -9, 10 ** 6
+    ids = np.arange(n_kept, dtype=np.int32)
+    ids[[3, 63, 70, 127]] = -9, n_cache, 10 ** 6, -2 ** 31
+    ids[[n_kept - 1, n_kept - 3, n_kept - 20]] = n_cache, -1, 2 ** 31 - 1
+    if n_kept > 512:
+        ids[[448, 449, 511]] = -2 ** 31, 2 ** 31 - 1, -1
     eff = np.clip(ids, 0, n_cache - 1)
-    O = torch.empty(Lc, N, D, device=DEV, dtype=torch.bfloat16)
-    B.pafu_chunk_attention_gather(dev(Q, "bf16"), dev(Kc, "bf16"), dev(Vc, "bf16"), torch.from_numpy(ids).to(DEV), 128,
-                                  dev(Kn, "bf16"), dev(Vn, "bf16"), Lc, O)
+    O = torch.empty(Lc, N * copies, D, device=DEV, dtype=torch.bfloat16)
+    up = lambda x: dev(x, "bf16").repeat(1, copies, 1)
+    B.pafu_chunk_attention_gather(up(Q), up(Kc), up(Vc), torch.from_numpy(ids).to(DEV), n_kept, up(Kn), up(Vn), Lc, O)
     torch.cuda.synchronize()
+    got = _first_copy(O, N)
     want = orc.chunk_attention(Q, Kc[eff], Vc[eff], Kn, Vn, block_len=Lc)
-    max_abs, rel = attn_errors(host(O), want)
+    max_abs, rel = attn_errors(got, want)
     assert max_abs < ATTN_MAX_ABS and rel < ATTN_REL_FRO, (max_abs, rel)
+    assert np.array_equal(got, _run(Q, Kc[eff], Vc[eff], Kn, Vn, Lc, copies=copies))
