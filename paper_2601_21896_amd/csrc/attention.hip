@@ -66,8 +66,10 @@ constexpr int kAtThreads = kAtWaves * 64;
 constexpr int kAtBQ = kAtWaves * 32;  // queries per workgroup
 constexpr int kAtTileKeys = 64;       // keys per LDS tile = keys per pipeline step
 constexpr int kAtStages = 4;          // LDS ring depth (tiles)
-constexpr int kAtIdStages = 8;        // ids ring depth (gather variant): a tile's ids live from 3 steps before its
-                                      // K load to its V load two steps after that
+// Ids ring depth (gather variant).  Step t asks for the ids of tile t + 7 (kAtStages + kAtIdLead); they have landed when its
+// group of two steps ends.  Tile u's K rows are copied in the group that starts 3 (u even) or 4 (u odd) steps after that, its V
+// rows in the next group, and the slot's next ids, tile u + 8's, are asked for in the one behind.
+constexpr int kAtIdStages = 8;
 constexpr int kAtIdLead = 3;
 constexpr int kAtXcds = 8;            // accelerator dies, each with its own L2
 // A tile's weights are taken relative to a maximum of the tiles before it; a lane's 32 of them may sum up to this much
@@ -195,10 +197,8 @@ __device__ __forceinline__ float attn_raise(const f32x16 (&s_cur)[2], u32x4 (&p_
 // there is no next tile), so this is the only implementation of the step.
 // s_*[kb] = key block kb (32 keys) of the tile; p_*[ks] = 16-key slice ks of the tile.
 // What bounds it: the issue slots that 32 matrix instructions share with the vector work of 2048 scores, at a clock that
-// the power limit sets.  A search for the tile's maximum (16 three-way maxima, a swap across the lane halves and the wait
-// for both) before the first exponential cost about an eighth of the vector instructions and left the first slots without
-// exponentials; without it a whole step takes 634 us instead of 667 (12 heads of 128, 4680 queries, 21060 keys), and 6762
-// instead of 7295 (40 heads, 10800 queries, 33480 keys).
+// the power limit sets.  (With a search for the tile's maximum in front of the exponentials a whole step took 5 % longer: 12 heads
+// of 128, 4680 queries, 21060 keys, 667 us instead of 634.)
 // k_at[kk] / v_at[db]: this lane's LDS addresses of the fragments in ring slot 0; the tiles are K_TILE / V_TILE bytes on,
 // which goes into the offset field of the reads.
 // issue(i) starts this step's global -> LDS tile copies behind slot i.  They start a few slots into the step, not at
@@ -312,12 +312,10 @@ __device__ __forceinline__ void attn_step(const f32x16 (&s_cur)[2], f32x16 (&s_n
   // tile outgrew it.  Then the reference of the queries concerned is raised by the power of two in the sum (of either lane
   // half), and everything is scaled by it: the packed weights in their exponent fields, exactly but for weights that
   // vanish beside the sum.  (NaN weights go on as they are: their query's result is a NaN whatever the reference.)
-  // A search for the tile's maximum and its weights computed once more, with a limit of 2^8, made a step with a raise half
-  // as long again.  1203 queries over 2999 keys (8 heads of 64, no workspace, fp32): scores that grow eightfold along the
-  // cache 106 -> 75 us (74 without growth), one NaN query in each wave 98 -> 74 us; 4680 over 16380 keys (12 heads of 128)
-  // 640 -> 558 (542) and 656 -> 541 us.
-  // (An else branch that left P^T alone, or a shift that was not done in place, put copies of P^T into every step: + 4 %.
-  // Laid out inside the loop, all this cost the 8-bit variant 1 %.)
+  // A raise costs little: 4680 over 16380 keys (12 heads of 128), scores that grow eightfold along the cache 558 us
+  // (without growth 542), one NaN query in each wave 541.
+  // (In place, without an else branch and out of line: copies of P^T in every step cost 4 %, the code inside the loop 1 % of the
+  // 8-bit variant.)
   if (__builtin_expect(__builtin_amdgcn_ballot_w64(psum > kAtMaxTileSum) != 0, 0)) {
     const float alpha = attn_raise(s_cur, p_cur, sc, msc, l_run, psum);
 #pragma unroll
@@ -740,7 +738,8 @@ __global__ __launch_bounds__(kAtThreads, 1) void chunk_attention_kernel(AttnArgs
       for (int kk = 0; kk < KD; ++kk) qf[kk] = *reinterpret_cast<const bf16x8*>(qp + 16 * kk);
     }
 
-    // ---- prologue: fill the ring (K tiles 0..S-1, V tiles 0..S-3 of the segment), then S^T(0)
+    // ---- prologue: the first tiles of the segment, then S^T(0).  bf16: K(0..2) and V(0); step 0 starts the copies of K(3), K(4),
+    // V(1) and V(2).  8-bit: K(0..3), V(0), V(1), and, when K(0) has been converted, K(4) and V(2).
     if (GATHER) {  // ids of the tiles whose loads are issued before step kAtIdLead's ids arrive
 #pragma unroll
       for (int i = 0; i < kAtStages + kAtIdLead; ++i) issue_ids(tb + i);
