@@ -361,8 +361,8 @@ struct AttnWork {
   int n_items;        // heads of all layers * n_qt
   int n_whole;        // workgroup g < n_whole takes item g
   int n_runs;         // equal runs over the units of the items from n_whole on
-  long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list; U below 2^31
-  int h0, r0;         // head of unit u0, and the units of that head in front of it
+  long long u0, U;    // ... which are units [u0, u0 + U) of the flattened list
+  int h0, r0;         // head of unit u0, and the units of that head in front of it; r0 + U below 2^31
   float* part_o;      // [2 n_runs][kAtBQ][D] fp32
   float* part_ml;     // [2 n_runs][2][kAtBQ] fp32: reference (log2 domain), row sum
 };
@@ -1474,14 +1474,16 @@ int launch_attention(hipStream_t st, const AttnLayer* layers, int n_layers, int 
       if (2 * run <= 2 * ((U + runs - 1) / runs) + 3) runs = per_item * last;
     }
     const size_t need = (size_t)2 * runs * ((size_t)kAtBQ * D + 2 * kAtBQ) * sizeof(float);
-    if (runs > last && longest - (U + runs - 1) / runs >= kAtMinCutGain && U < 1ll << 30 && workspace_bytes >= need &&
+    const long long r0 = u0 - (long long)(first_cut / w.n_qt) * units_head;
+    // (r0 + U: the kernel finds a run's first item in 32 bits)
+    if (runs > last && longest - (U + runs - 1) / runs >= kAtMinCutGain && r0 + U < 1ll << 31 && workspace_bytes >= need &&
         (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0) {
       w.n_whole = first_cut;
       w.n_runs = (int)runs;
       w.u0 = u0;
       w.U = U;
       w.h0 = first_cut / w.n_qt;
-      w.r0 = (int)(u0 - (long long)w.h0 * units_head);
+      w.r0 = (int)r0;
       w.part_o = static_cast<float*>(workspace);
       w.part_ml = w.part_o + (size_t)2 * runs * kAtBQ * D;
     }
