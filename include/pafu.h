@@ -167,6 +167,8 @@ int pafu_compact_kv_counted(void* stream, const void* K, const void* V, const fl
  *               same result up to the rounding of the softmax weights, several times faster for short chunks over
  *               a long cache.  The contents of
  *               the workspace need not be initialised and are not kept.  Results do not depend on timing either way.
+ *               Without a cut a head's result has the same bits whatever heads (or layers) share the launch.  Calls of few
+ *               queries over few keys take a kernel that never uses the workspace and gives those bits.
  */
 size_t pafu_attention_workspace_bytes(int Lq, int N, int D);
 int pafu_chunk_attention(void* stream, const void* Q, int Lq, const void* Kc, const void* Vc, int n_kept,
